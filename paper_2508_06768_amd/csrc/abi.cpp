@@ -252,9 +252,8 @@ struct WsLayout {
     size_t rp = 0, rp_bytes = 0;       // per-ray pose partials of one table (adjoint)
     size_t zb = 0, zb_bytes = 0;       // dL/dZ per sample (adjoint)
     size_t part = 0, part_bytes = 0;   // loss partials (plan step)
-    size_t car = 0, car_bytes = 0;     // tile carries, 4 doubles per record (plan step)
-    size_t cex = 0, cex_bytes = 0;     // tile-carry exponents, one int32 per record
-    size_t cst = 0, cst_bytes = 0;     // chunk states, kStateDoubles doubles per record
+    size_t zc = 0, zc_bytes = 0;       // samples before the carry blocks, one double each (plan step)
+    size_t cst = 0, cst_bytes = 0;     // states for the adjoint, kStateFloats per carry block
     size_t gain = 0, gain_bytes = 0;   // per-pixel gains recorded by the forward (plan step)
     size_t rays = 0, rays_bytes = 0;   // ray geometry the adjoint hands the scatter, one RayRec per ray
     size_t fix = 0, fix_bytes = 0;     // deterministic plan: 64-bit fixed-point dL/dZ per voxel
@@ -326,14 +325,11 @@ WsLayout layout(const dus_fan *fans, int32_t n_poses, const dus_physics *p, int 
         for (int32_t i = 0; i < n_poses; ++i)
             if (fans[i].n_rays > 0 && fans[i].n_samples > 0)
                 rec += (size_t)dus::carry_records(fans[i].n_rays, fans[i].n_samples);
-        L.car = off;
-        L.car_bytes = std::max<size_t>(rec, 1) * 4 * sizeof(double);
-        off = align_up(off + L.car_bytes);
-        L.cex = off;
-        L.cex_bytes = std::max<size_t>(rec, 1) * sizeof(int32_t);
-        off = align_up(off + L.cex_bytes);
+        L.zc = off;
+        L.zc_bytes = std::max<size_t>(rec, 1) * sizeof(double);
+        off = align_up(off + L.zc_bytes);
         L.cst = off;
-        L.cst_bytes = std::max<size_t>(rec, 1) * dus::kStateDoubles * sizeof(double);
+        L.cst_bytes = std::max<size_t>(rec, 1) * dus::kStateFloats * sizeof(float);
         off = align_up(off + L.cst_bytes);
         if (p->speckle_on || p->atten_mode == DUS_ATTEN_POST_HOC) {
             L.gain = off;
@@ -407,21 +403,15 @@ int make_sched(const dus_schedule *sc, Sched &n)
     return DUS_OK;
 }
 
-// zero: buffers the first forward launch clears besides rendering
 int enqueue_forward(const Sched &sc, const dus::VolArgs &va, const dus::PhysArgs &pa,
                     const std::vector<dus::FanTable> &tabs, const float *poses, float *out,
-                    float *min_pivot, hipStream_t st, double *carry = nullptr, int32_t *carry_exp = nullptr,
-                    double *cstate = nullptr, float *gain = nullptr, const dus::ZeroArgs &zero = dus::ZeroArgs{},
-                    const dus::SideStream *side = nullptr)
+                    float *min_pivot, hipStream_t st)
 {
-    bool first = true;
     for (const auto &t : tabs) {
         if (t.total_rays <= 0) continue;
-        DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, out, min_pivot, 0, carry,
-                                    carry_exp, cstate, gain, st, first ? zero : dus::ZeroArgs{}, sc.span_samples,
-                                    side),
+        DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, out, min_pivot, 0, nullptr, nullptr,
+                                    nullptr, nullptr, st, dus::ZeroArgs{}, sc.span_samples, nullptr),
                 "forward kernel launch");
-        first = false;
     }
     return DUS_OK;
 }
@@ -555,12 +545,22 @@ int dus_render_bmode_backward(const float *Z, const dus_volume *vol, const float
         double *rpart = reinterpret_cast<double *>((char *)ws + L.rp);
         int64_t r0 = 0;
         for (const auto &t : tabs) {
-            DUS_HIP(dus::launch_backward(sc.bwd_chunk, sc.xcd_group, sc.scatter_rays, va, pa, t, poses,
-                                         reinterpret_cast<dus::RayRec *>((char *)ws + L.rays) + r0, src, nullptr,
-                                         grad_Z ? reinterpret_cast<float *>((char *)ws + L.zb) : nullptr, grad_Z,
-                                         grad_pose ? acc : nullptr, rpart + dus::kRayPart * r0, nullptr, nullptr,
-                                         nullptr, nullptr, nullptr, st),
+            dus::RayRec *rays = reinterpret_cast<dus::RayRec *>((char *)ws + L.rays) + r0;
+            float *zb = reinterpret_cast<float *>((char *)ws + L.zb);
+            // rays too long to gather at once: the forward's states first, in
+            // the rows that dL/dZ then overwrites
+            double *states = dus::longest_ray(t) > dus::kWholeSamples ? reinterpret_cast<double *>(zb) : nullptr;
+            if (states)
+                DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, nullptr, nullptr, 0, nullptr,
+                                            nullptr, states, nullptr, st, dus::ZeroArgs{}, sc.span_samples, nullptr),
+                        "forward kernel launch");
+            DUS_HIP(dus::launch_adjoint(sc.bwd_chunk, sc.xcd_group, va, pa, t, poses, rays, src, nullptr,
+                                        grad_Z ? zb : nullptr, grad_pose ? acc : nullptr, rpart + dus::kRayPart * r0,
+                                        nullptr, nullptr, nullptr, states, nullptr, st, sc.span_samples, nullptr),
                     "adjoint kernel launch");
+            if (grad_Z)
+                DUS_HIP(dus::launch_scatter(sc.scatter_rays, sc.xcd_group, va, t, rays, zb, grad_Z, st),
+                        "scatter kernel launch");
             r0 += t.total_rays;
         }
         if (grad_pose) {
@@ -886,10 +886,9 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     double *part = reinterpret_cast<double *>((char *)ws + p->ws.part);
     int64_t n_part = 0;
     const Sched &sc = p->sched;
-    // the forward records its tile carries, chunk states and per-pixel
-    // gains; the adjoint starts from them
-    double *car = reinterpret_cast<double *>((char *)ws + p->ws.car);
-    int32_t *cex = reinterpret_cast<int32_t *>((char *)ws + p->ws.cex);
+    // the forward records its states and per-pixel gains; the adjoint starts
+    // from them
+    double *zc = reinterpret_cast<double *>((char *)ws + p->ws.zc);
     double *cst = reinterpret_cast<double *>((char *)ws + p->ws.cst);
     float *gain = p->ws.gain_bytes ? reinterpret_cast<float *>((char *)ws + p->ws.gain) : nullptr;
     const bool blur = p->phys.blur_on != 0;
@@ -940,7 +939,7 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
             const auto &t = p->tabs[i];
             if (t.total_rays <= 0) continue;
             // the first table's forward clears dL/dZ and the pose sums
-            DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, img, nullptr, 0, car, cex, cst,
+            DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, img, nullptr, 0, zc, nullptr, cst,
                                         gain, tst(i), (i == 0 && fwd_clears) ? zero : dus::ZeroArgs{},
                                         sc.span_samples, side),
                     "forward kernel launch");
@@ -970,14 +969,21 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     if (adj)
         for (size_t i = 0; i < p->tabs.size(); ++i) {
             const auto &t = p->tabs[i];
+            // without a forward before it, the adjoint needs the records only
+            // for rays too long to gather at once
+            const bool rec = fwd || dus::longest_ray(t) > dus::kWholeSamples;
+            if (rec && !fwd)
+                DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, nullptr, nullptr, 0, zc, nullptr,
+                                            cst, gain, tst(i), dus::ZeroArgs{}, sc.span_samples, side),
+                        "forward kernel launch");
             // dL/dZ per sample is stored only for the scatter
             DUS_HIP(dus::launch_adjoint(sc.bwd_chunk, sc.xcd_group, va, pa, t, poses, gZ ? rays + r0 : nullptr, eb,
                                         blur ? nullptr : target,
                                         gZ ? zbar : nullptr,
                                         grad_pose ? acc : nullptr, rpart + dus::kRayPart * r0,
                                         (!blur && loss) ? part + n_part : nullptr,
-                                        fwd ? car : nullptr, fwd ? cex : nullptr, fwd ? cst : nullptr,
-                                        fwd ? gain : nullptr, tst(i), sc.span_samples, side),
+                                        rec ? zc : nullptr, nullptr, rec ? cst : nullptr, rec ? gain : nullptr,
+                                        tst(i), sc.span_samples, side),
                     "adjoint kernel");
             if (!blur) n_part += t.total_rays;
             r0 += t.total_rays;

@@ -29,27 +29,19 @@ struct FanRec {
 };
 static_assert(sizeof(FanRec) == 56, "FanRec layout");
 
-// Tile carries: the forward kernel records, at every 256-sample boundary of
-// a ray, the carried row vector and determinant (v0, v1, D) and the sample
-// before the boundary, in the scale of the forward tile that holds the
-// boundary.  Each record's exponent gives that scale relative to the
-// previous record's: zero inside a forward tile, the tile's renormalisation
-// (a power of two) at its first record.  The adjoint then starts its
-// reverse sweep from these records instead of re-running the forward.
+// What the forward kernel records for the adjoint, per carry block of 256
+// samples of a ray: the sample before the block, and the state
+// (w, t) = (v0 / v1, D / v1^2) at every 4th sample, two doubles side by side.
 constexpr int kCarryBlock = 256;
 inline int64_t carry_records(int32_t n_rays, int32_t n_samples)
 {
     return (int64_t)n_rays * ((n_samples + kCarryBlock - 1) / kCarryBlock);
 }
-
-// Chunk states: the forward kernel also records (v0, v1, D) at every 4th
-// sample, in the frame of that sample's carry record, so that the adjoint
-// needs neither its own chunk products nor its prefix scan.  Each carry
-// record owns kStatesPerBlock states stored component-major (all v0, all v1,
-// all D): 3 * 64 doubles per record.
 constexpr int kStateStride = 4;
-constexpr int kStatesPerBlock = kCarryBlock / kStateStride;
-constexpr int kStateDoubles = 3 * kStatesPerBlock;
+constexpr int kStateFloats = kCarryBlock / kStateStride * 4;     // in units of 4 bytes
+// rays of at most this many samples need no records: the adjoint gathers
+// them once, one wavefront per 256 samples
+constexpr int kWholeSamples = 8 * kCarryBlock;
 
 struct FanTable {
     int32_t n;              // fans in this launch
@@ -59,6 +51,14 @@ struct FanTable {
                             // another launch's (their wavefronts return at once)
     FanRec f[kMaxFans];
 };
+
+inline int longest_ray(const FanTable &t)
+{
+    int s = 0;
+    for (int f = 0; f < t.n; ++f)
+        if (t.f[f].n_samples > s) s = t.f[f].n_samples;
+    return s;
+}
 
 // A ray's geometry, written by the adjoint kernel (which sets it up from the
 // pose and the fan) for the dL/dZ scatter: sample k sits at voxel coordinate
@@ -94,9 +94,12 @@ constexpr int kRayPart = 9;
 
 // Launch wrappers (kernels.hip).  All enqueue on `st` and return the HIP
 // error of the launch.
-// carry / carry_exp: optional tile-carry records (4 doubles / 1 int each);
-// cstate: optional chunk states (kStateDoubles per carry record; needs carry);
-// gain: optional per-pixel gain (speckle x post-hoc attenuation) output
+// states: optional records for the adjoint, kStateFloats floats' room per
+// carry block, with zcar (one double per block, the sample before it); with
+// zcar NULL they lie in the rays' own rows of an image layout, without the
+// first of each ray, and may share the memory of the adjoint's zbar;
+// gain: optional per-pixel gain (speckle x post-hoc attenuation) output.
+// (The int32 pointer is not used.)
 // Buffers a kernel clears on the side (a[0..na) and b[0..nb) set to zero)
 // A second stream for the launch of the long rays (several wavefronts per
 // ray), forked from and joined back into the launch stream with two events,
@@ -117,27 +120,20 @@ struct ZeroArgs {
 // step's dL/dZ and pose accumulators), or {} for none
 hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const PhysArgs &p,
                           const FanTable &t, const float *poses, float *out,
-                          float *min_pivot, int pivot_base, double *carry, int32_t *carry_exp,
-                          double *cstate, float *gain, hipStream_t st, const ZeroArgs &zero = ZeroArgs{},
+                          float *min_pivot, int pivot_base, double *zcar, int32_t *,
+                          double *states, float *gain, hipStream_t st, const ZeroArgs &zero = ZeroArgs{},
                           int span_samples = kSpanSamples, const SideStream *side = nullptr);
-// adjoint: dL/dZ per sample into zbar (image layout), then its scatter; in
-// the fused form (target given) loss receives one partial per ray.  With
-// pose_acc (a flag here), pose_part receives kRayPart doubles per ray of the
-// table; launch_pose_reduce then adds them into the pose accumulators.
-// rays: one RayRec per ray of the table, written by the adjoint when zbar is
-// (the scatter reads them)
-hipError_t launch_backward(int chunk, int xcd_group, int scatter_rays, const VolArgs &v,
-                           const PhysArgs &p, const FanTable &t, const float *poses, RayRec *rays,
-                           const float *gsrc, const float *target, float *zbar, float *gZ,
-                           double *pose_acc, double *pose_part, double *loss, const double *carry,
-                           const int32_t *carry_exp, const double *cstate, const float *gain,
-                           hipStream_t st);
-// the two halves of launch_backward: the adjoint scan (dL/dZ per sample into
-// zbar, pose sums, fused loss partials) and the scatter of zbar into gZ
+// adjoint: dL/dZ per sample into zbar (image layout), pose sums; in the fused
+// form (target given) loss receives one partial per ray.  With pose_acc (a
+// flag here), pose_part receives kRayPart doubles per ray of the table;
+// launch_pose_reduce then adds them into the pose accumulators.  rays: one
+// RayRec per ray of the table, written by the adjoint when zbar is (the
+// scatter reads them).  states, zcar: the forward's records; NULL for tables
+// whose rays have at most kWholeSamples samples.
 hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const PhysArgs &p,
                           const FanTable &t, const float *poses, RayRec *rays, const float *gsrc,
                           const float *target, float *zbar, double *pose_acc, double *pose_part, double *loss,
-                          const double *carry, const int32_t *carry_exp, const double *cstate,
+                          const double *zcar, const int32_t *, const double *states,
                           const float *gain, hipStream_t st, int span_samples = kSpanSamples,
                           const SideStream *side = nullptr);
 // pose_acc[pose] += the sum of the table's per-ray partials, one wavefront

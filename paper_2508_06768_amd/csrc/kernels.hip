@@ -19,18 +19,18 @@
 //
 // Layout of the work: one wavefront per ray.  A ray is cut into tiles of
 // T = 64 C samples.  Phase 1 gathers 64 consecutive samples per instruction
-// (good L1/L2 locality), computes rho in FP64 and parks it in LDS.  Phase 2
-// gives each lane C consecutive interfaces: chunk product, 6-step wavefront
-// scan of 2x2 products, carry between tiles, walk emitting pixels into LDS.
-// Phase 3 stores the tile coalesced, applying post-hoc attenuation and
-// speckle.  The recurrence runs in FP64 (full rate on CDNA4 vector ALUs): the
-// |R| convention makes the system nearly singular on some rays, where FP32
-// would lose the 1e-5 agreement with the reference.
+// (good L1/L2 locality) and parks them in LDS in FP64.  Phase 2 gives each
+// lane C consecutive interfaces: rho in registers, chunk product, 6-step
+// wavefront scan of 2x2 products, carry between tiles, walk emitting pixels.
+// The recurrence runs in FP64 (full rate on CDNA4 vector ALUs): the |R|
+// convention makes the system nearly singular on some rays, where FP32 would
+// lose the 1e-5 agreement with the reference.
 //
-// The adjoint kernel recomputes the forward (no stored state), runs the
-// reverse recurrence as an associative affine suffix scan over lanes, and
-// scatters dL/dZ into the volume gradient with FP32 atomics; pose gradients
-// are reduced per ray in FP64.
+// The adjoint kernel gathers the samples again, takes the states the forward
+// recorded (or forms them itself), and runs the reverse recurrence as two
+// sums over the deeper interfaces.  dL/dZ per sample goes to a scatter kernel
+// that adds it into the volume gradient with FP32 atomics; pose gradients are
+// reduced per ray in FP64.
 #include <algorithm>
 #include <math.h>
 #include <mutex>
@@ -457,16 +457,23 @@ __device__ __forceinline__ float posthoc_coef(const PhysArgs &p, float ds)
 }
 
 // --------------------------------------------------------------------------
-// phase 1: gather samples [t0, t0+T) of a ray, interface rho of (k-1, k)
-// into s_rho[pad8(k - t0)]; optionally keep the samples in s_z, and the
-// last sample of every 256-sample block in s_zc (tile carries).  W (the
-// caller's wavefronts per ray) only keeps the callers' instances apart: the
-// compiler then derives each caller's index ranges from that caller alone.
+// phase 1: gather the samples [t0, t0+T) of a ray into LDS, 64 consecutive
+// samples per instruction: sample i of the tile at s_z[zi(i)], the sample
+// before the tile at s_z[zi(-1)].  The lanes then read their chunks of
+// consecutive samples back and form the interfaces' coefficients there: two
+// neighbours sit in one lane, so nothing is exchanged between lanes, and the
+// coefficients stay in registers.  Before a ray's first sample and past its
+// last one the samples repeat, so the coefficient there is exactly zero
+// without a select.  W (the caller's wavefronts per ray) only keeps the
+// callers' instances apart: the compiler then derives each caller's index
+// ranges from that caller alone.
 // --------------------------------------------------------------------------
-template <int C, bool KEEPZ, bool KEEPG, bool INSIDE, int W>
-__device__ __forceinline__ void gather_tile_body(const VolArgs &v, const Ray &ray, int t0, int S,
-                                                 bool absm, int lane, double &zprev, double *s_rho,
-                                                 double *s_z, float *s_g, double *s_zc, double *s_dq)
+__device__ __forceinline__ int zi(int i) { return 2 + i + (i >> 4); }
+template <int T> struct SampleTile { static constexpr int size = T + T / 16 + 2; };
+
+template <int C, bool KEEPG, bool INSIDE, int W>
+__device__ __forceinline__ double gather_tile_body(const VolArgs &v, const Ray &ray, int t0, int S, int lane,
+                                                   double *s_z, float *s_g)
 {
     constexpr int T = 64 * C;
     const int sxy = v.nx * v.ny;
@@ -476,28 +483,16 @@ __device__ __forceinline__ void gather_tile_body(const VolArgs &v, const Ray &ra
 #pragma unroll
         for (int a = 0; a < 3; ++a) ih[a] = 1.0 / (double)v.h[a];
     }
+    double z = 0.0;
 #pragma unroll GATHER_UNROLL
     for (int jj = 0; jj < C; ++jj) {
         const int i = jj * 64 + lane;
         const int k = t0 + i;
         const Stencil st = stencil_at<INSIDE>(v, ray, min(k, S - 1));
         double gu[3];
-        const double z = trilinear(v.Z, v.nx, sxy, st, KEEPG ? gu : nullptr);
-        double zm = __shfl_up(z, 1);
-        if (lane == 0) zm = zprev;
-        zprev = lane_read(z, 63);
-        // interface (k-1, k); outside [1, S) rho = 0 and dq = 0
-        const bool ok = (k >= 1) && (k < S);
-        double dq = 0.0;
-        double rho = iface_rho(zm, z, absm, KEEPZ ? &dq : nullptr);
-        rho = ok ? rho : 0.0;
-        dq = ok ? dq : 0.0;
-        s_rho[pad8(i)] = rho;
-        if (KEEPZ) {
-            s_z[pad8(i)] = z;
-            s_dq[pad8(i)] = dq;
-        }
-        if (s_zc && lane == 63 && (jj & 3) == 3) s_zc[jj >> 2] = z;
+        z = trilinear(v.Z, v.nx, sxy, st, KEEPG ? gu : nullptr);
+        s_z[zi(i)] = z;
+        if (k == 0) s_z[zi(-1)] = z;
         if (KEEPG) {
             // dZ/dp per mm (dZ/du / h, zero along an axis where the sample
             // lies outside the volume: clamped), kept in FP32 as its
@@ -518,48 +513,40 @@ __device__ __forceinline__ void gather_tile_body(const VolArgs &v, const Ray &ra
             s_g[2 * T + i] = (float)fma(gw[0], ray.bn[0], fma(gw[1], ray.bn[1], gw[2] * ray.bn[2]));
         }
     }
+    return z;      // lane 63: the tile's last sample
 }
 
-template <int C, bool KEEPZ, bool KEEPG = false, int W = 1>
-__device__ __forceinline__ void gather_tile(const VolArgs &v, const Ray &ray, int t0, int S,
-                                            bool absm, int lane, double &zprev, double *s_rho,
-                                            double *s_z, float *s_g = nullptr, double *s_zc = nullptr,
-                                            double *s_dq = nullptr)
+template <int C, bool KEEPG, int W>
+__device__ __forceinline__ double gather_tile(const VolArgs &v, const Ray &ray, int t0, int S, int lane, double *s_z,
+                                              float *s_g = nullptr)
 {
     // a tile whose samples all lie inside the volume skips the clamps (the
     // ray is the same on every lane, so the branch is uniform)
     if (segment_inside(v, ray, t0, min(t0 + 64 * C - 1, S - 1)))
-        gather_tile_body<C, KEEPZ, KEEPG, true, W>(v, ray, t0, S, absm, lane, zprev, s_rho, s_z, s_g, s_zc, s_dq);
-    else
-        gather_tile_body<C, KEEPZ, KEEPG, false, W>(v, ray, t0, S, absm, lane, zprev, s_rho, s_z, s_g, s_zc, s_dq);
+        return gather_tile_body<C, KEEPG, true, W>(v, ray, t0, S, lane, s_z, s_g);
+    return gather_tile_body<C, KEEPG, false, W>(v, ray, t0, S, lane, s_z, s_g);
 }
 
-// transfer map of interface rho (first column and determinant; the second
-// column is (rho, 1)).  VALID = false (interfaces outside [1, S), rho = 0):
-// the identity.
+// Transfer map of interface rho (first column and determinant; the second
+// column is (rho, 1)).  Interfaces outside [1, S) have rho = 0 and the map
+// diag(a^2, 1), which leaves v1 alone and scales D by a^2: past the last
+// sample that changes nothing stored, and the a^2 of the interface before
+// sample 0 is taken out of the starting D (d_start).
 struct Map {
     double m00, m10, det;
 };
 
-__device__ __forceinline__ Map make_map(double r, double a2, double sgn, bool valid)
+__device__ __forceinline__ Map make_map(double r, double a2, double sgn)
 {
     Map m;
     const double r2 = r * r;
-    m.m00 = valid ? a2 * (1.0 - r2 - sgn * r2) : 1.0;
+    m.m00 = a2 * (1.0 - r2 - sgn * r2);
     m.m10 = -a2 * sgn * r;
-    m.det = valid ? a2 * (1.0 - r2) : 1.0;
+    m.det = a2 * (1.0 - r2);
     return m;
 }
 
-// The forward takes every interface's map unselected: with rho = 0 it is
-// diag(a^2, 1), which leaves v1 alone and scales D by a^2.  Past the last
-// sample that changes nothing stored; the interface before sample 0 is the
-// first step of every ray, and its a^2 is taken out of the starting D
-// (d_start).  Dropping the selects cuts the forward's walk and chunk
-// product; the adjoint keeps them (its registers stay within 3 waves).
-__device__ __forceinline__ Map make_map(double r, double a2, double sgn) { return make_map(r, a2, sgn, true); }
-
-// D at the start of a ray for the unselected maps: D = 1 after the first step
+// D at the start of a ray: D = 1 after the first step
 __device__ __forceinline__ double d_start(double a2) { return 1.0 / a2; }
 
 struct Mat {
@@ -576,30 +563,28 @@ __device__ __forceinline__ Mat matmul(const Mat &x, const Mat &y)
     return r;
 }
 
-__device__ __forceinline__ Mat shfl_up_mat(const Mat &m, int d)
+// the matrix d lanes up (DOWN: d lanes down)
+template <bool DOWN>
+__device__ __forceinline__ Mat shfl_mat(const Mat &m, int d)
 {
     Mat r;
-    r.a = __shfl_up(m.a, d);
-    r.b = __shfl_up(m.b, d);
-    r.c = __shfl_up(m.c, d);
-    r.d = __shfl_up(m.d, d);
+    r.a = DOWN ? __shfl_down(m.a, d) : __shfl_up(m.a, d);
+    r.b = DOWN ? __shfl_down(m.b, d) : __shfl_up(m.b, d);
+    r.c = DOWN ? __shfl_down(m.c, d) : __shfl_up(m.c, d);
+    r.d = DOWN ? __shfl_down(m.d, d) : __shfl_up(m.d, d);
     return r;
 }
 
-// chunk product Q = M_first ... M_last of a lane's C interfaces, and det;
-// SEL: identity maps outside [1, S) (the adjoint), else unselected maps
-template <int C, bool SEL>
-__device__ __forceinline__ void chunk_product(const double *s_rho, int base, int t0, int S,
-                                              double a2, double sgn, Mat &Q, double &qd)
+// chunk product Q = M_first ... M_last of a lane's C interfaces, and det
+template <int C>
+__device__ __forceinline__ void chunk_product(const double (&rho)[C], double a2, double sgn, Mat &Q, double &qd)
 {
     Q = Mat{1.0, 0.0, 0.0, 1.0};
     qd = 1.0;
-    // unrolled: the C LDS reads issue together
 #pragma unroll
     for (int i = 0; i < C; ++i) {
-        const int k = t0 + base + i;
-        const double r = s_rho[pad8(base + i)];
-        const Map m = make_map(r, a2, sgn, !SEL || ((k >= 1) && (k < S)));
+        const double r = rho[i];
+        const Map m = make_map(r, a2, sgn);
         const double n00 = fma(Q.a, m.m00, Q.b * m.m10);
         const double n01 = fma(Q.a, r, Q.b);
         const double n10 = fma(Q.c, m.m00, Q.d * m.m10);
@@ -609,25 +594,28 @@ __device__ __forceinline__ void chunk_product(const double *s_rho, int base, int
     }
 }
 
-// exclusive left-to-right product scan over the 64 lanes; also returns the
-// wave total (inclusive product of lane 63)
+// exclusive product scan over the 64 lanes in depth order; also returns the
+// wave total.  The shallowest chunk is lane 0's, or lane 63's (DOWN).
+template <bool DOWN>
 __device__ __forceinline__ void scan_exclusive(int lane, Mat Q, double qd, Mat &X, double &xd,
                                                Mat &Tot, double &td)
 {
+    const int pos = DOWN ? 63 - lane : lane;
+    constexpr int last = DOWN ? 0 : 63;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        const Mat o = shfl_up_mat(Q, d);
-        const double od = __shfl_up(qd, d);
-        if (lane >= d) {
+        const Mat o = shfl_mat<DOWN>(Q, d);
+        const double od = DOWN ? __shfl_down(qd, d) : __shfl_up(qd, d);
+        if (pos >= d) {
             Q = matmul(o, Q);
             qd = od * qd;
         }
     }
-    Tot = Mat{lane_read(Q.a, 63), lane_read(Q.b, 63), lane_read(Q.c, 63), lane_read(Q.d, 63)};
-    td = lane_read(qd, 63);
-    X = shfl_up_mat(Q, 1);
-    xd = __shfl_up(qd, 1);
-    if (lane == 0) {
+    Tot = Mat{lane_read(Q.a, last), lane_read(Q.b, last), lane_read(Q.c, last), lane_read(Q.d, last)};
+    td = lane_read(qd, last);
+    X = shfl_mat<DOWN>(Q, 1);
+    xd = DOWN ? __shfl_down(qd, 1) : __shfl_up(qd, 1);
+    if (pos == 0) {
         X = Mat{1.0, 0.0, 0.0, 1.0};
         xd = 1.0;
     }
@@ -642,6 +630,62 @@ __device__ __forceinline__ int renorm_exp(double c0, double c1)
     return ilogb(m);
 }
 
+// the carried state (c0, c1, cD) through a tile's total, renormalised
+__device__ __forceinline__ void carry_through(const Mat &tot, double td, double &c0, double &c1, double &cD)
+{
+    const double n0 = fma(c0, tot.a, c1 * tot.c);
+    const double n1 = fma(c0, tot.b, c1 * tot.d);
+    const double nD = cD * td;
+    const int ex = renorm_exp(n0, n1);
+    c0 = ldexp(n0, -ex);
+    c1 = ldexp(n1, -ex);
+    cD = ldexp(nD, -2 * ex);
+}
+
+// Per-pixel gains (speckle, post-hoc attenuation) of the C consecutive
+// samples that start at k0, a multiple of 4, so that the granular variates
+// are C/4 whole Philox blocks; s_xir holds the radial cells of the tile
+// starting at t0.
+template <int C, bool SPK>
+__device__ __forceinline__ void chunk_gains(const PhysArgs &p, const GainK &gk, int k0, int t0, int j, int sid,
+                                            float postc, const float *s_xir, float (&gn)[C])
+{
+#pragma unroll
+    for (int i = 0; i < C; ++i) gn[i] = 1.0f;
+    if (SPK) {
+#pragma unroll
+        for (int q = 0; q < C / 4; ++q) {
+            float x[4];
+            granular4(p, (k0 >> 2) + q, j, sid, x);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) gn[4 * q + u] = x[u];
+        }
+        // the lane's samples are consecutive: the radial cell index of the
+        // first is exact (cell_of), the others step it
+        int c, r;
+        cell_of(p, gk, k0, c, r);
+        c -= t0 / p.cell;          // index into s_xir
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const int k = k0 + i;
+            float g = speckle_mult(p, (float)k * gk.inv_sm1, (float)r * gk.inv_cell, s_xir[c], s_xir[c + 1], gn[i]);
+            if (p.atten == 1) g *= exp2f((float)((double)k * (double)postc));
+            gn[i] = g;
+            const bool wrap = (r + 1 == p.cell);
+            c += wrap ? 1 : 0;
+            r = wrap ? 0 : r + 1;
+        }
+    } else if (p.atten == 1) {
+#pragma unroll
+        for (int i = 0; i < C; ++i) gn[i] = pixel_gain<false, true>(p, gk, k0 + i, t0, postc, 1.0f, s_xir);
+    }
+}
+
+// four floats, or two doubles, at any multiple of 4 bytes (global memory
+// takes 16-byte accesses at dword alignment)
+typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double double2_u __attribute__((ext_vector_type(2), aligned(4)));
+
 // --------------------------------------------------------------------------
 // forward kernel
 //
@@ -654,31 +698,34 @@ __device__ __forceinline__ int renorm_exp(double c0, double c1)
 // per tile, in the order and with the operations of W = 1, so the results
 // are the same bit for bit).  The sample before the tile comes from its own
 // trilinear lookup instead of the previous tile's gather.
+//
+// For the adjoint it records the state at every 4th sample as the two
+// numbers that no renormalisation changes, w = v0 / v1 and t = D / v1^2
+// (states: four floats' room each), and the sample before every 256th
+// (zcar).  With zcar NULL the states of a ray sit in its own row of an image
+// layout, that of sample 4 c at element 4 (c - 1), and the first one, a
+// constant, is left out.  out may be NULL (states, and gains if wanted).
 // --------------------------------------------------------------------------
 template <int C, bool SPK, int W>
 __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTable tab,
                                                     const float *__restrict__ poses,
                                                     float *__restrict__ out, float *__restrict__ minpiv,
-                                                    int pivot_base, double *__restrict__ carry,
-                                                    int32_t *__restrict__ carry_exp,
-                                                    double *__restrict__ cstate,
+                                                    int pivot_base, double *__restrict__ zcar,
+                                                    float *__restrict__ states,
                                                     float *__restrict__ gain_out, int xgrp, ZeroArgs zero)
 {
     constexpr int T = 64 * C;
     static_assert(T % kCarryBlock == 0, "tiles hold whole carry blocks");
     static_assert(C % kStateStride == 0, "chunks hold whole state strides");
-    constexpr int NB = T / kCarryBlock;     // carry blocks per tile
     constexpr int LB = kCarryBlock / C;     // lanes per carry block
-    __shared__ double s_rho_w[W][T + T / 16];
-    __shared__ double s_zc_w[W][NB];
+    __shared__ double s_z_w[W][SampleTile<T>::size];
     __shared__ float s_xir_w[W][SPK ? T / 4 + 8 : 1];
     __shared__ double s_tot[W > 1 ? W : 1][5];     // scan totals of a round's tiles
     __shared__ double s_piv[W > 1 ? W : 1];
 
     const int lane = (W == 1) ? (int)threadIdx.x : (int)(threadIdx.x & 63);
     const int wv = (W == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    double *s_rho = s_rho_w[wv];
-    double *s_zc = s_zc_w[wv];
+    double *s_z = s_z_w[wv];
     float *s_xir = s_xir_w[wv];
     if (zero.na > 0 || zero.nb > 0) {
         // the step's clears, spread over the forward's wavefronts: the stores
@@ -714,9 +761,9 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
     double c0 = 0.0, c1 = 1.0, cD = d_start(a2), zprev = 0.0;
     double piv = 1e300;
     const bool want_piv = (minpiv != nullptr);
-    const int nblk = (S + kCarryBlock - 1) / kCarryBlock;
-    const long long crec = (long long)fr.carry_begin + (long long)j * nblk;
-    int first_rel = 0;      // exponent of this tile's carry relative to the previous record
+    const long long crec = (long long)fr.carry_begin + (long long)j * ((S + kCarryBlock - 1) / kCarryBlock);
+    float *srow = nullptr;
+    if (states) srow = states + (zcar ? crec * kStateFloats : obase - 4);
 
     for (int r0 = 0; r0 < S; r0 += W * T) {
         const int t0 = r0 + wv * T;
@@ -725,10 +772,10 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
             const Stencil st = stencil_at<false>(v, ray, t0 - 1);
             zprev = trilinear(v.Z, v.nx, v.nx * v.ny, st, nullptr);
         }
-        const double zstart = zprev;
         if (act) {
-            gather_tile<C, false, false, W>(v, ray, t0, S, absm, lane, zprev, s_rho, nullptr, nullptr,
-                                  carry ? s_zc : nullptr);
+            if (lane == 0 && t0 > 0) s_z[zi(-1)] = zprev;
+            const double zl = gather_tile<C, false, W>(v, ray, t0, S, lane, s_z);
+            if (W == 1) zprev = lane_read(zl, 63);
             if (SPK) speckle_radial<T>(p, t0, j, fr.speckle_id, lane, s_xir);
         }
         __syncthreads();
@@ -737,10 +784,17 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
         Mat Q, X, Tot;
         double qd, xd, td;
         double tc0 = c0, tc1 = c1, tcD = cD;        // the state carried into this tile
-        int trel = first_rel;
+        double rho[C];
         if (act) {
-            chunk_product<C, false>(s_rho, base, t0, S, a2, sgn, Q, qd);
-            scan_exclusive(lane, Q, qd, X, xd, Tot, td);
+            double zl = s_z[zi(base - 1)];
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                const double zr = s_z[zi(base) + i];
+                rho[i] = iface_rho(zl, zr, absm);
+                zl = zr;
+            }
+            chunk_product<C>(rho, a2, sgn, Q, qd);
+            scan_exclusive<false>(lane, Q, qd, X, xd, Tot, td);
         }
         if (W > 1) {
             if (act && lane == 0) {
@@ -758,63 +812,35 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
                     tc0 = c0;
                     tc1 = c1;
                     tcD = cD;
-                    trel = first_rel;
                 }
                 if (r0 + u * T >= S) break;
-                const double n0 = fma(c0, s_tot[u][0], c1 * s_tot[u][2]);
-                const double n1 = fma(c0, s_tot[u][1], c1 * s_tot[u][3]);
-                const double nD = cD * s_tot[u][4];
-                const int ex = renorm_exp(n0, n1);
-                c0 = ldexp(n0, -ex);
-                c1 = ldexp(n1, -ex);
-                cD = ldexp(nD, -2 * ex);
-                first_rel = ex;
+                carry_through(Mat{s_tot[u][0], s_tot[u][1], s_tot[u][2], s_tot[u][3]}, s_tot[u][4], c0, c1, cD);
             }
         }
         if (act) {
             double v0 = fma(tc0, X.a, tc1 * X.c);
             double v1 = fma(tc0, X.b, tc1 * X.d);
             double D = tcD * xd;
-            if (carry) {
-                // state at the start of carry block m = lane / LB (lanes on a
-                // block boundary), in the tile's frame: inside a tile the
-                // records share one scale, so only a tile's first record carries
-                // an exponent (relative to the previous record)
-                const int m = lane / LB;
-                const int kb = t0 + m * kCarryBlock;
-                if ((lane % LB) == 0 && kb < S) {
-                    const long long r = crec + kb / kCarryBlock;
-                    double *q = carry + 4 * r;
-                    q[0] = v0;
-                    q[1] = v1;
-                    // the ray's first record in the adjoint's convention (identity
-                    // map before sample 0): D = 1
-                    q[2] = (kb == 0) ? 1.0 : D;
-                    q[3] = (m == 0) ? zstart : s_zc[m - 1];
-                    carry_exp[r] = (m == 0) ? trel : 0;
-                }
+            if (zcar) {
+                // the sample before every carry block of the tile
+                const int kb = t0 + base;
+                if ((lane % LB) == 0 && kb < S) zcar[crec + kb / kCarryBlock] = s_z[zi(base - 1)];
             }
-            // chunk states for the adjoint: the lane's C samples lie in one
-            // carry block (the ray's first state is taken in the adjoint's
-            // convention by the adjoint itself)
-            double *qs = nullptr;
-            if (cstate && (t0 + base) / kCarryBlock < nblk)
-                qs = cstate + (crec + (t0 + base) / kCarryBlock) * kStateDoubles + ((t0 + base) % kCarryBlock) / kStateStride;
             float pix[C];
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 // branch-free: outside [1, S) rho = 0, so the pixel is 0 and v1
                 // unchanged (make_map)
                 const int k = t0 + base + i;
-                // the chunk states and the gains below are read once, by the
-                // adjoint after the blur: non-temporal stores keep them from
-                // displacing the volume and the images in the caches
-                if ((i % kStateStride) == 0 && qs) {
-                    __builtin_nontemporal_store(v0, qs + i / kStateStride);
-                    __builtin_nontemporal_store(v1, qs + kStatesPerBlock + i / kStateStride);
-                    __builtin_nontemporal_store(D, qs + 2 * kStatesPerBlock + i / kStateStride);
+                // the states and the gains below are read once, by the adjoint
+                // after the blur: non-temporal stores keep them from displacing
+                // the volume and the images in the caches
+                if ((i % kStateStride) == 0 && srow && k < S && (k > 0 || zcar)) {
+                    const double iv = rcp64(v1);
+                    const double2_u st = {v0 * iv, D * iv * iv};
+                    __builtin_nontemporal_store(st, reinterpret_cast<double2_u *>(srow + k));
                 }
-                const double r = s_rho[pad8(base + i)];
+                const double r = rho[i];
                 const Map m = make_map(r, a2, sgn);
                 const double v1n = fma(v0, r, v1);
                 // the pixel leaves in FP32: the hardware FP64 reciprocal, without
@@ -826,75 +852,32 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
                 v1 = v1n;
                 D *= m.det;
             }
-            if (W == 1) {
-                // carry to the next tile, renormalised by a power of two
-                const double n0 = fma(c0, Tot.a, c1 * Tot.c);
-                const double n1 = fma(c0, Tot.b, c1 * Tot.d);
-                const double nD = cD * td;
-                const int ex = renorm_exp(n0, n1);
-                c0 = ldexp(n0, -ex);
-                c1 = ldexp(n1, -ex);
-                cD = ldexp(nD, -2 * ex);
-                first_rel = ex;
-            }
-            // per-pixel gains and the stores, in the lane's chunk order (the
-            // lane's C samples start at a multiple of 4: its granular variates
-            // are C/4 whole Philox blocks)
-            float gn[C];
+            // carry to the next tile, renormalised by a power of two
+            if (W == 1) carry_through(Tot, td, c0, c1, cD);
+            // per-pixel gains and the stores, in the lane's chunk order
+            if (out || gain_out) {
+                float gn[C];
+                chunk_gains<C, SPK>(p, gk, t0 + base, t0, j, fr.speckle_id, postc, s_xir, gn);
+                const bool has_gain = SPK || p.atten == 1;
+                const long long o = obase + t0 + base;
+                if (t0 + base + C <= S) {
 #pragma unroll
-            for (int i = 0; i < C; ++i) gn[i] = 1.0f;
-            if (SPK) {
-#pragma unroll
-                for (int q = 0; q < C / 4; ++q) {
-                    float x[4];
-                    granular4(p, ((t0 + base) >> 2) + q, j, fr.speckle_id, x);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) gn[4 * q + u] = x[u];
-                }
-                // the lane's samples are consecutive: the radial cell index of the
-                // first is exact (cell_of), the others step it
-                int c, r;
-                cell_of(p, gk, t0 + base, c, r);
-                c -= t0 / p.cell;          // index into s_xir
-#pragma unroll
-                for (int i = 0; i < C; ++i) {
-                    const int k = t0 + base + i;
-                    float g = speckle_mult(p, (float)k * gk.inv_sm1, (float)r * gk.inv_cell, s_xir[c], s_xir[c + 1], gn[i]);
-                    if (p.atten == 1) g *= exp2f((float)((double)k * (double)postc));
-                    gn[i] = g;
-                    const bool wrap = (r + 1 == p.cell);
-                    c += wrap ? 1 : 0;
-                    r = wrap ? 0 : r + 1;
-                }
-            } else if (p.atten == 1) {
-#pragma unroll
-                for (int i = 0; i < C; ++i)
-                    gn[i] = pixel_gain<false, true>(p, gk, t0 + base + i, t0, postc, 1.0f, s_xir);
-            }
-            const bool has_gain = SPK || p.atten == 1;
-            const long long o = obase + t0 + base;
-            const bool vec = ((reinterpret_cast<uintptr_t>(out + o) & 15) == 0) &&
-                             (!gain_out || (reinterpret_cast<uintptr_t>(gain_out + o) & 15) == 0);
-            if (vec && t0 + base + C <= S) {
-#pragma unroll
-                for (int q = 0; q < C / 4; ++q) {
-                    const int i = 4 * q;
-                    *reinterpret_cast<float4 *>(out + o + i) =
-                        make_float4(pix[i] * gn[i], pix[i + 1] * gn[i + 1], pix[i + 2] * gn[i + 2], pix[i + 3] * gn[i + 3]);
-                    if (has_gain && gain_out) {
-                        float *gq = gain_out + o + i;
-                        __builtin_nontemporal_store(gn[i], gq);
-                        __builtin_nontemporal_store(gn[i + 1], gq + 1);
-                        __builtin_nontemporal_store(gn[i + 2], gq + 2);
-                        __builtin_nontemporal_store(gn[i + 3], gq + 3);
+                    for (int i = 0; i < C; i += 4) {
+                        const float4_u px = {pix[i] * gn[i], pix[i + 1] * gn[i + 1], pix[i + 2] * gn[i + 2],
+                                             pix[i + 3] * gn[i + 3]};
+                        if (out) *reinterpret_cast<float4_u *>(out + o + i) = px;
+                        if (has_gain && gain_out) {
+                            const float4_u g4 = {gn[i], gn[i + 1], gn[i + 2], gn[i + 3]};
+                            __builtin_nontemporal_store(g4, reinterpret_cast<float4_u *>(gain_out + o + i));
+                        }
                     }
-                }
-            } else {
+                } else {
 #pragma unroll
-                for (int i = 0; i < C; ++i) {
-                    if (t0 + base + i < S) {
-                        out[o + i] = pix[i] * gn[i];
-                        if (has_gain && gain_out) gain_out[o + i] = gn[i];
+                    for (int i = 0; i < C; ++i) {
+                        if (t0 + base + i < S) {
+                            if (out) out[o + i] = pix[i] * gn[i];
+                            if (has_gain && gain_out) gain_out[o + i] = gn[i];
+                        }
                     }
                 }
             }
@@ -919,70 +902,131 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
 // --------------------------------------------------------------------------
 // adjoint kernel
 // --------------------------------------------------------------------------
-// Reverse recurrence per interface step (state before the step: v0, v1, D;
-// adjoint after the step: l0, l1, lD = dL/d(v0', v1', D')):
-//   v0' = v0 A + v1 B,  v1' = v0 R + v1,  D' = D E,  e = R D / (v1 v1')
-// gives l_before = l_after J + f with J = diag(M^T, E) and forcing f from
-// de/d(state); the rho adjoint collects dA, dB, dR, dE and de/dR = D/v1'^2.
-struct Adj {
-    double l0, l1, lD;
-};
+// The pixels depend on the state only through w = v0 / v1 and t = D / v1^2.
+// With p = 1 + w R and q = 1 / p, interface by interface,
+//   e = R t q,   w' = (A w + B) q,   t' = t E q^2,
+// and dw'/dw = dt'/dt = E q^2 = t'/t.  Scaled by t the adjoint recurrence
+// therefore has no factor left: with L = t dl/dt and O = t dl/dw (l the loss),
+//   L_k = L_{k+1} + e_k dl/de_k,   O_k = O_{k+1} - e_k (L_k + L_{k+1}),
+// two sums over the deeper interfaces, and
+//   dl/dR_k = -O_{k+1} N / (t (1 - R^2)) - 2 L_{k+1} (R / (1 - R^2) + w q)
+//             + dl/de_k t q^2,   N = w^2 - 1 + (1 + s) p^2.
+// (A wavefront's 64 lanes so add two FP64 numbers each, with register moves
+// between lanes, where the recurrence of (v0, v1, D) itself composes 2x2
+// affine maps of eight numbers.)
+//
+// Lane l takes the chunk 63 - l of the tile's interfaces, so that the sums
+// run over the lanes below.
+//
+// Bound by VALU issue and latency (161 VGPRs: 3 wavefronts per SIMD; capped
+// at 4 it spills and takes 250 us).  64 poses x 256 rays x 1024 samples with
+// the forward's records, one launch: 239 us with the (v0, v1, D) adjoint,
+// 151 us with the sums.
+//
+// Where the state (w, t) at a chunk's start comes from:
+//   WHOLE = false: the records of the forward kernel (states, zcar).
+//     W = 1: one wavefront per ray walks its tiles from the deepest up.
+//     W > 1 (rays of many tiles): W wavefronts share a ray and take W
+//     consecutive tiles at a time.
+//   WHOLE = true (rays of at most W tiles): chunk products and a lane scan of
+//     the wavefront's own tile, and the carries pushed through the tiles
+//     before it, as k_forward does it with several wavefronts: the ray is
+//     gathered once, and no forward pass comes before.
+// Tile totals are added tile by tile in the same order for every W, so dL/dZ
+// does not depend on W (bit for bit); the pose sums and the loss are added
+// over the W wavefronts in a fixed order.
+//
+// zbar and states may name the same memory (with zcar NULL): a tile's states
+// lie in its own part of the ray's row (the first in the part before it),
+// and are read before the tile's dL/dZ overwrites it.
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp_zero(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffll), CTRL, ROWS, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)((unsigned long long)b >> 32), CTRL, ROWS,
+                                                              0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 
-// W = 1: one wavefront per ray walks its tiles from the deepest up.  W > 1
-// (rays of many tiles, with the forward's carry records and chunk states):
-// W wavefronts share a ray and take W consecutive tiles at a time.  Walk 1
-// and the lanes' suffix composition need nothing from the deeper tiles; the
-// adjoint entering each tile is the round's incoming adjoint pushed through
-// the deeper tiles' affine maps (lane 1's suffix map, then lane 0's chunk
-// map, then the frame's power of two: the operations of W = 1, in its
-// order, so the results are the same bit for bit).  The sample after a
-// tile and its interface's dL/dZ factor come from the neighbouring
-// wavefront's LDS; the pose sums and the loss are added over the W
-// wavefronts in a fixed order.
-template <int C, bool SPK, bool FUSED, int W>
+// x of the lane below (UP: above); the end lane takes `edge`
+template <bool UP>
+__device__ __forceinline__ double lane_next(double x, double edge)
+{
+    constexpr int ctrl = UP ? 0x130 : 0x138;     // wave_shl:1, wave_shr:1
+    const long long b = __double_as_longlong(x), e = __double_as_longlong(edge);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp((int)(unsigned)(e & 0xffffffffll),
+                                                              (int)(unsigned)(b & 0xffffffffll), ctrl, 0xf, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp((int)(unsigned)((unsigned long long)e >> 32),
+                                                              (int)(unsigned)((unsigned long long)b >> 32), ctrl, 0xf,
+                                                              0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// sum over this lane and those below it (row_shr 1, 2, 4, 8 within the rows
+// of 16 lanes, then the rows' last lanes handed on by row_bcast)
+__device__ __forceinline__ double lanes_below(double x)
+{
+    x += dpp_zero<0x111>(x);
+    x += dpp_zero<0x112>(x);
+    x += dpp_zero<0x114>(x);
+    x += dpp_zero<0x118>(x);
+    x += dpp_zero<0x142, 0xa>(x);
+    x += dpp_zero<0x143, 0xc>(x);
+    return x;
+}
+
+__device__ __forceinline__ double lanes_sum(double x) { return lane_read(lanes_below(x), 63); }
+
+// a lane's C consecutive values from sample k0 on; `fill` past sample S
+template <int C>
+__device__ __forceinline__ void load_chunk(const float *__restrict__ row, int k0, int S, float fill, float (&x)[C])
+{
+    if (k0 + C <= S) {
+#pragma unroll
+        for (int i = 0; i < C; i += 4) {
+            const float4_u q = *reinterpret_cast<const float4_u *>(row + k0 + i);
+            x[i] = q.x;
+            x[i + 1] = q.y;
+            x[i + 2] = q.z;
+            x[i + 3] = q.w;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < C; ++i) x[i] = (k0 + i < S) ? row[k0 + i] : fill;
+    }
+}
+
+template <int C, bool SPK, bool FUSED, int W, bool WHOLE>
 __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanTable tab,
                                                  const float *__restrict__ poses,
                                                  RayRec *__restrict__ rays_out,
                                                  const float *__restrict__ gsrc,
                                                  const float *__restrict__ target,
-                                                 float *__restrict__ zbar,
+                                                 float *zbar,
                                                  double *__restrict__ pose_part,
                                                  double *__restrict__ loss_acc,
-                                                 const double *__restrict__ carry,
-                                                 const int32_t *__restrict__ carry_exp,
-                                                 const double *__restrict__ cstate,
+                                                 const double *__restrict__ zcar,
+                                                 const float *states,
                                                  const float *__restrict__ gain_in, int xgrp)
 {
     constexpr int T = 64 * C;
-    constexpr int kMaxTiles = (DUS_MAX_SAMPLES + T - 1) / T;
-    static_assert(W == 1 || !SPK, "several wavefronts per ray take the forward's gains");
-    static_assert(T % kCarryBlock == 0, "tiles hold whole carry blocks");
-    constexpr int NB = T / kCarryBlock;
-    // walks unrolled where the registers allow three wavefronts per SIMD
-    constexpr int kWalkUnroll = (C <= 4 && !SPK && !FUSED) ? C : 1;
-    __shared__ float s_g_w[W][3 * T];     // dZ/dp of every sample of the tile, in the ray's basis
-    __shared__ double s_rho_w[W][T + T / 16];
-    __shared__ double s_z_w[W][T + T / 16];
-    __shared__ double s_dq_w[W][T + T / 16];   // d rho / dZ factor of every interface of the tile
-    __shared__ float s_eb_w[W][T + T / 32];
-    __shared__ float s_gain_w[W][FUSED ? T + T / 32 : 1];
-    __shared__ float s_xig[SPK ? T : 1];
-    __shared__ float s_xir[SPK ? T / 4 + 8 : 1];
-    __shared__ double s_carry[kMaxTiles][4];
-    __shared__ int s_cexp[kMaxTiles];
-    __shared__ double s_x[W > 1 ? W : 1][16];   // a round's tiles: lane 1's suffix map, lane 0's chunk map
-    __shared__ double s_red[W > 1 ? W : 1][7];  // per-wavefront pose sums and loss
+    static_assert(C % kStateStride == 0, "a chunk starts on a recorded state");
+    __shared__ __align__(16) float s_g_w[W][3 * T];     // dZ/dp of every sample of the tile, in the ray's basis
+    __shared__ double s_z_w[W][SampleTile<T>::size];
+    __shared__ float s_xir_w[W][SPK ? T / 4 + 8 : 1];
+    __shared__ double s_tot[WHOLE ? W : 1][5];    // the tiles' scan totals
+    __shared__ double s_l[W], s_o[W], s_q[W];     // a round's tiles: sums of L and O, first interface's dL/dZ factor
+    __shared__ double s_red[W][7];                // per-wavefront pose sums and loss
 
     const int lane = (W == 1) ? (int)threadIdx.x : (int)(threadIdx.x & 63);
     const int wv = (W == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     float *s_g = s_g_w[wv];
-    double *s_rho = s_rho_w[wv];
     double *s_z = s_z_w[wv];
-    double *s_dq = s_dq_w[wv];
-    float *s_eb = s_eb_w[wv];
-    float *s_gain = s_gain_w[wv];
-    const int g = remap_block(blockIdx.x, gridDim.x, xgrp);
-    if (W == 1 && g < tab.ray0) return;          // walked by several wavefronts in another launch
+    float *s_xir = s_xir_w[wv];
+    int g = remap_block(blockIdx.x, gridDim.x, xgrp);
+    if (WHOLE) g += tab.ray0;
+    else if (W == 1 && g < tab.ray0) return;     // walked by several wavefronts in another launch
     const int fi = find_fan(tab, g);
     const FanRec fr = tab.f[fi];
     const int j = g - fr.ray_begin;
@@ -1001,442 +1045,249 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
         rays_out[g] = r;
     }
     const bool absm = (p.refl == 0);
-    const double sgn = absm ? 1.0 : -1.0;
+    const double sgn = absm ? 1.0 : -1.0, onep = 1.0 + sgn;
     const double a2 = ray.a2;
     const float postc = posthoc_coef(p, fr.ds);
     const GainK gk = gain_consts(p, fr.n_samples);
     const long long obase = fr.out_offset + (long long)j * S;
     const int ntiles = (S + T - 1) / T;
     const double inv_npix = 1.0 / ((double)fr.n_rays * (double)S);
+    const long long crec = (long long)fr.carry_begin + (long long)j * ((S + kCarryBlock - 1) / kCarryBlock);
+    const float *srow = WHOLE ? nullptr : states + (zcar ? crec * kStateFloats : obase - 4);
+    const float *src = (FUSED ? target : gsrc) + obase;
 
-    const int nblk = (S + kCarryBlock - 1) / kCarryBlock;
-    const long long rb = (long long)fr.carry_begin + (long long)j * nblk;
-    __shared__ int s_bexp[(DUS_MAX_SAMPLES + kCarryBlock - 1) / kCarryBlock];
-    if (carry) {
-        // tile starts from the forward kernel's carry records; the exponent
-        // of tile t relative to tile t - 1 sums those of its carry blocks
-        for (int b = threadIdx.x; b < nblk; b += 64 * W) {
-            s_bexp[b] = carry_exp[rb + b];
-            if (b % NB == 0) {
-                const double *q = carry + 4 * (rb + b);
-                s_carry[b / NB][0] = q[0];
-                s_carry[b / NB][1] = q[1];
-                s_carry[b / NB][2] = q[2];
-                s_carry[b / NB][3] = q[3];
-            }
-        }
-        __syncthreads();
-        // A tile's frame is its first record renormalised by a power of two
-        // (the forward's records share one scale inside a forward tile).
-        // Thread t takes tile t (ntiles <= 64): s_cexp[t] becomes the exponent
-        // of tile t's frame relative to tile t - 1's, and s_bexp[b] that of
-        // block b's record relative to its tile's frame.
-        const int t = threadIdx.x;
-        int et = 0, cex = 0, rel[NB];
-        if (t < ntiles) {
-            et = renorm_exp(s_carry[t][0], s_carry[t][1]);
-            if (t > 0) {
-                cex = et - renorm_exp(s_carry[t - 1][0], s_carry[t - 1][1]);
-#pragma unroll
-                for (int q = 0; q < NB; ++q) cex += s_bexp[(t - 1) * NB + 1 + q];
-            }
-            rel[0] = -et;
-#pragma unroll
-            for (int u = 1; u < NB; ++u) rel[u] = rel[u - 1] + s_bexp[t * NB + u];
-        }
-        __syncthreads();
-        if (t < ntiles) {
-            s_carry[t][0] = ldexp(s_carry[t][0], -et);
-            s_carry[t][1] = ldexp(s_carry[t][1], -et);
-            s_carry[t][2] = ldexp(s_carry[t][2], -2 * et);
-            s_cexp[t] = cex;
-#pragma unroll
-            for (int u = 0; u < NB; ++u) s_bexp[t * NB + u] = rel[u];
-        }
-    } else if (W == 1) {
-        // forward sweep: state at every tile start (several wavefronts per
-        // ray take the forward's carry records instead)
-        double c0 = 0.0, c1 = 1.0, cD = 1.0, zprev = 0.0;
-        for (int t = 0; t < ntiles; ++t) {
-            if (lane == 0) {
-                s_carry[t][0] = c0;
-                s_carry[t][1] = c1;
-                s_carry[t][2] = cD;
-                s_carry[t][3] = zprev;
-            }
-            if (t + 1 == ntiles) break;
-            const int t0 = t * T;
-            gather_tile<C, false>(v, ray, t0, S, absm, lane, zprev, s_rho, nullptr);
-            __syncthreads();
-            Mat Q, X, Tot;
-            double qd, xd, td;
-            chunk_product<C, true>(s_rho, lane * C, t0, S, a2, sgn, Q, qd);
-            scan_exclusive(lane, Q, qd, X, xd, Tot, td);
-            const double n0 = fma(c0, Tot.a, c1 * Tot.c);
-            const double n1 = fma(c0, Tot.b, c1 * Tot.d);
-            const double nD = cD * td;
-            const int ex = renorm_exp(n0, n1);
-            c0 = ldexp(n0, -ex);
-            c1 = ldexp(n1, -ex);
-            cD = ldexp(nD, -2 * ex);
-            if (lane == 0) s_cexp[t + 1] = ex;
-            __syncthreads();
-        }
-    }
-    __syncthreads();
-
-    // reverse sweep (W > 1: rounds of W tiles, wavefront w taking tile rt - w)
-    Adj lam{0.0, 0.0, 0.0};        // adjoint of the state at the end of the (round's deepest) tile
-    double rbar_next = 0.0;        // dL/dZ factor of the interface just after that tile
-    double z_next = 0.0;           // first sample of the tile after it
+    // the sums L and O over everything deeper than the (round's deepest)
+    // tile, and the interface factor and sample just past it
+    double l_in = 0.0, o_in = 0.0, qz_in = 0.0, z_in = 0.0;
     double loss = 0.0;
     double gsum[3] = {0.0, 0.0, 0.0}, gssum[3] = {0.0, 0.0, 0.0};
+    // wavefront w takes tile rt - w of a round
     for (int rt = ntiles - 1; rt >= 0; rt -= W) {
         // uniform over the wavefront; an idle wavefront of the last round
         // repeats tile 0 and stores nothing
         const bool act = (W == 1) || (rt - wv >= 0);
         const int t = act ? rt - wv : 0;
         const int t0 = t * T;
-        const double zstart = s_carry[t][3];
-        double zprev = zstart;
-        const int base = lane * C;
-        // wave priority 1 while this wavefront issues its chunk-state loads and
-        // its gather (its loads go out ahead of co-resident wavefronts' FP64
-        // arithmetic) and during the suffix scan over the lanes (a serial chain
-        // of cross-lane exchanges), 0 elsewhere: the adjoint 2% faster at
-        // 64 x 256 x 1024
+        const int base = (63 - lane) * C;
+        const int k0 = t0 + base;
+        // wave priority 1 while this wavefront issues its loads and its gather
+        // (they go out ahead of co-resident wavefronts' FP64 arithmetic) and
+        // during the lane sums, 0 elsewhere
         __builtin_amdgcn_s_setprio(1);
-        // the state at the lane's chunk start, from the forward's chunk
-        // states when it recorded them (loads issued before the gather)
-        double v0s = 0.0, v1s = 1.0, Ds = 1.0;
-        if (cstate) {
-            const int k = t0 + base;
-            if (k / kCarryBlock < nblk) {
-                const double *q = cstate + (rb + k / kCarryBlock) * kStateDoubles + (k % kCarryBlock) / kStateStride;
-                v0s = q[0];
-                v1s = q[kStatesPerBlock];
-                // the ray's first state in the adjoint's convention: D = 1
-                Ds = (k == 0) ? 1.0 : q[2 * kStatesPerBlock];
+        double w = 0.0, tt = d_start(a2);        // state before the ray's first interface
+        double zm = 0.0;                          // the sample before the tile
+        if (!WHOLE) {
+            const int ks = min(k0, S - 1) & ~(kStateStride - 1);
+            if (ks > 0) {
+                const double2_u st = *reinterpret_cast<const double2_u *>(srow + ks);
+                w = st.x;
+                tt = st.y;
             }
-        }
-        if (pose_part)
-            gather_tile<C, true, true, W>(v, ray, t0, S, absm, lane, zprev, s_rho, s_z, s_g, nullptr, s_dq);
-        else
-            gather_tile<C, true, false, W>(v, ray, t0, S, absm, lane, zprev, s_rho, s_z, nullptr, nullptr, s_dq);
-        if (SPK) speckle_fill<T>(p, t0, j, fr.speckle_id, lane, s_xig, s_xir);
-        __builtin_amdgcn_s_setprio(0);
-        __syncthreads();
-        // dL/de (or the target for the fused loss) staged through LDS: the C
-        // global loads are issued together, then the per-pixel gains
-        // (speckle, post-hoc attenuation) are applied in place
-        // the loads are clamped into the ray and issued together (no
-        // per-load branches, one wait); samples past the ray read as zero
-        const float *src = FUSED ? target : gsrc;
-        if (gain_in) {
-            // gains recorded by the forward kernel
-            float x[C], gn[C];
-#pragma unroll
-            for (int m = 0; m < C; ++m) {
-                const int k = min(t0 + m * 64 + lane, S - 1);
-                x[m] = src[obase + k];
-                gn[m] = gain_in[obase + k];
-            }
-#pragma unroll
-            for (int m = 0; m < C; ++m) {
-                const int i = m * 64 + lane;
-                const bool in = (t0 + i < S);
-                if (FUSED) {
-                    s_eb[pad4(i)] = in ? x[m] : 0.0f;
-                    s_gain[pad4(i)] = in ? gn[m] : 1.0f;
+            if (t0 > 0) {
+                if (zcar) {
+                    zm = zcar[crec + t0 / kCarryBlock];
                 } else {
-                    s_eb[pad4(i)] = in ? x[m] * gn[m] : 0.0f;
+                    const Stencil st = stencil_at<false>(v, ray, t0 - 1);
+                    zm = trilinear(v.Z, v.nx, v.nx * v.ny, st, nullptr);
                 }
             }
-        } else {
-            float x[C];
-#pragma unroll
-            for (int m = 0; m < C; ++m) x[m] = src[obase + min(t0 + m * 64 + lane, S - 1)];
-#pragma unroll
-            for (int m = 0; m < C; ++m) {
-                const int i = m * 64 + lane;
-                s_eb[pad4(i)] = (t0 + i < S) ? x[m] : 0.0f;
-            }
-            const bool has_gain = SPK || p.atten == 1;
-#pragma unroll 1
-            for (int m = 0; m < C; ++m) {
-                const int i = m * 64 + lane;
-                const int k = t0 + i;
-                const float gain = (has_gain && k < S) ? pixel_gain_rt<SPK>(p, gk, k, t0, postc, SPK ? s_xig[i] : 1.0f, s_xir) : 1.0f;
-                if (FUSED) s_gain[pad4(i)] = gain;
-                else s_eb[pad4(i)] *= gain;
-            }
         }
+        if (pose_part) gather_tile<C, true, W>(v, ray, t0, S, lane, s_z, s_g);
+        else gather_tile<C, false, W>(v, ray, t0, S, lane, s_z);
+        if (SPK) speckle_radial<T>(p, t0, j, fr.speckle_id, lane, s_xir);
+        __builtin_amdgcn_s_setprio(0);
         __syncthreads();
 
-        if (cstate) {
-            // from the frame of the state's block record to the tile's frame
-            // (the exponent is read here, after the barrier, so that the
-            // scaling, and the wait for the loads above, stay behind the gather)
-            const int es = s_bexp[min((t0 + base) / kCarryBlock, nblk - 1)];
-            v0s = ldexp(v0s, es);
-            v1s = ldexp(v1s, es);
-            Ds = ldexp(Ds, 2 * es);
-        } else {
-            // otherwise from the tile's carry and a prefix scan of the
-            // lanes' chunk products
+        // dL/de (or the target for the fused loss) and the per-pixel gains
+        float ebf[C], gn[C];
+        load_chunk<C>(src, k0, S, 0.0f, ebf);
+        if (gain_in) load_chunk<C>(gain_in + obase, k0, S, 1.0f, gn);
+        else chunk_gains<C, SPK>(p, gk, k0, t0, j, fr.speckle_id, postc, s_xir, gn);
+
+        // the chunk's samples, those on either side of it, and its interfaces
+        double z[C], rho[C], dq[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i) z[i] = s_z[zi(base) + i];
+        if (W > 1 && WHOLE && t > 0) zm = s_z_w[wv + 1][zi(T - 1)];
+        const double zp = (W > 1 && wv > 0) ? s_z_w[wv - 1][zi(0)] : z_in;
+        const double zl = lane_next<true>(z[C - 1], (t > 0) ? zm : z[0]);
+        const double zr = lane_next<false>(z[0], zp);
+#pragma unroll
+        for (int i = 0; i < C; ++i) rho[i] = iface_rho(i > 0 ? z[i - 1] : zl, z[i], absm, &dq[i]);
+        if (k0 == 0) dq[0] = 0.0;                 // no interface before sample 0
+
+        if (WHOLE) {
             Mat Q, X, Tot;
             double qd, xd, td;
-            chunk_product<C, true>(s_rho, base, t0, S, a2, sgn, Q, qd);
-            scan_exclusive(lane, Q, qd, X, xd, Tot, td);
-            const double c0 = s_carry[t][0], c1 = s_carry[t][1], cD = s_carry[t][2];
-            v0s = fma(c0, X.a, c1 * X.c);
-            v1s = fma(c0, X.b, c1 * X.d);
-            Ds = cD * xd;
-        }
-        // Walk 1 (forward over the lane's C interfaces): the chunk's affine
-        // adjoint map lambda_start = lambda_end J_chunk + f_chunk, with
-        // J_chunk = diag(Q^T, det) and f_chunk = sum_i f_i (Q_i^loc)^T, where
-        // Q_i^loc = M_first .. M_{i-1} and f_i is step i's forcing (adj_forcing).
-        // The walk's final Q^loc is the chunk product Q itself.
-        Adj f{0.0, 0.0, 0.0};
-        Mat Q{1.0, 0.0, 0.0, 1.0};
-        double qd = 1.0;
-        const double w1s = rcp64(v1s);     // 1 / v1 at the chunk start
-        {
-            double v0 = v0s, v1 = v1s, D = Ds, w1 = w1s;
-            Mat &QL = Q;
-            double &qdl = qd;
-            // branch-free: an interface outside [1, S) has rho = 0 (gather)
-            // and the identity map, so its step leaves the state unchanged and
-            // forces nothing (pixel 0 is zero; the loss still counts it)
-#pragma unroll kWalkUnroll
-            for (int i = 0; i < C; ++i) {
-                const int k = t0 + base + i;
-                const bool valid = (k >= 1) && (k < S);
-                const double r = s_rho[pad8(base + i)];
-                const Map m = make_map(r, a2, sgn, valid);
-                const double v1n = fma(v0, r, v1);
-                const double w1p = rcp64(v1n);
-                const double e = r * D * w1 * w1p;
-                double eb;
-                if (FUSED) {
-                    const double gn = s_gain[pad4(base + i)];
-                    const double diff = e * gn - (double)s_eb[pad4(base + i)];
-                    loss += act ? diff * diff * inv_npix : 0.0;
-                    eb = 2.0 * diff * inv_npix * gn;
-                    s_eb[pad4(base + i)] = (float)eb;
-                } else {
-                    eb = s_eb[pad4(base + i)];
+            chunk_product<C>(rho, a2, sgn, Q, qd);
+            scan_exclusive<true>(lane, Q, qd, X, xd, Tot, td);
+            double c0 = 0.0, c1 = 1.0, cD = d_start(a2);
+            if (W > 1) {
+                if (act && lane == 0) {
+                    s_tot[wv][0] = Tot.a;
+                    s_tot[wv][1] = Tot.b;
+                    s_tot[wv][2] = Tot.c;
+                    s_tot[wv][3] = Tot.d;
+                    s_tot[wv][4] = td;
                 }
-                const double f0 = -eb * e * r * w1p;
-                const double f1 = -eb * e * (w1 + w1p);
-                const double fD = eb * r * w1 * w1p;
-                f.l0 = fma(f0, QL.a, fma(f1, QL.b, f.l0));
-                f.l1 = fma(f0, QL.c, fma(f1, QL.d, f.l1));
-                f.lD = fma(fD, qdl, f.lD);
-                const double n00 = fma(QL.a, m.m00, QL.b * m.m10), n01 = fma(QL.a, r, QL.b);
-                const double n10 = fma(QL.c, m.m00, QL.d * m.m10), n11 = fma(QL.c, r, QL.d);
-                QL = Mat{n00, n01, n10, n11};
-                qdl *= m.det;
-                const double v0n = fma(v0, m.m00, v1 * m.m10);
-                v0 = v0n;
-                v1 = v1n;
-                w1 = w1p;
-                D *= m.det;
+                __syncthreads();
+                for (int u = rt; u > wv && u < W; --u)      // tiles 0 .. t - 1, at wavefronts rt .. wv + 1
+                    carry_through(Mat{s_tot[u][0], s_tot[u][1], s_tot[u][2], s_tot[u][3]}, s_tot[u][4], c0, c1, cD);
             }
+            const double v0 = fma(c0, X.a, c1 * X.c), v1 = fma(c0, X.b, c1 * X.d);
+            const double iv = rcp64(v1);
+            w = v0 * iv;
+            tt = cD * xd * iv * iv;
+        }
+
+        // walk down the chunk: state, pixel and dl/de of every interface
+        double ws[C], ts[C], qs[C], eb[C], e[C];
+        double lsum = 0.0;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const double r = rho[i];
+            const double q = rcp64(fma(w, r, 1.0));
+            const double r2 = r * r, om = 1.0 - r2;
+            ws[i] = w;
+            ts[i] = tt;
+            qs[i] = q;
+            e[i] = r * tt * q;
+            if (FUSED) {
+                const double diff = fma(e[i], (double)gn[i], -(double)ebf[i]);
+                loss += act ? diff * diff * inv_npix : 0.0;
+                eb[i] = 2.0 * diff * inv_npix * (double)gn[i];
+            } else {
+                eb[i] = (double)(ebf[i] * gn[i]);
+            }
+            lsum = fma(eb[i], e[i], lsum);
+            w = fma(w, a2 * (om - sgn * r2), -a2 * sgn * r) * q;
+            tt = a2 * om * tt * q * q;
         }
         __builtin_amdgcn_s_setprio(1);
-        // suffix composition over lanes: Psi_l = Phi_l o Phi_{l+1} o ... o Phi_63
-        Mat PQ = Q;
-        double pd = qd;
-        Adj pf = f;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            Mat oq;
-            oq.a = __shfl_down(PQ.a, d);
-            oq.b = __shfl_down(PQ.b, d);
-            oq.c = __shfl_down(PQ.c, d);
-            oq.d = __shfl_down(PQ.d, d);
-            const double od = __shfl_down(pd, d);
-            const double of0 = __shfl_down(pf.l0, d), of1 = __shfl_down(pf.l1, d);
-            const double ofD = __shfl_down(pf.lD, d);
-            if (lane + d < 64) {
-                // f_new = f_{l+d} Q_l^T + f_l ;  Q_new = Q_l Q_{l+d} ; d_new = d_{l+d} d_l
-                const double n0 = fma(of0, PQ.a, fma(of1, PQ.b, pf.l0));
-                const double n1 = fma(of0, PQ.c, fma(of1, PQ.d, pf.l1));
-                const double nD = fma(ofD, pd, pf.lD);
-                PQ = matmul(PQ, oq);
-                pd = od * pd;
-                pf = Adj{n0, n1, nD};
-            }
-        }
-        // adjoint at this tile's end
-        Adj tl = lam;
-        if (W > 1) {
-            if (act && lane == 1) {
-                s_x[wv][0] = PQ.a;
-                s_x[wv][1] = PQ.b;
-                s_x[wv][2] = PQ.c;
-                s_x[wv][3] = PQ.d;
-                s_x[wv][4] = pd;
-                s_x[wv][5] = pf.l0;
-                s_x[wv][6] = pf.l1;
-                s_x[wv][7] = pf.lD;
-            }
-            if (act && lane == 0) {
-                s_x[wv][8] = Q.a;
-                s_x[wv][9] = Q.b;
-                s_x[wv][10] = Q.c;
-                s_x[wv][11] = Q.d;
-                s_x[wv][12] = qd;
-                s_x[wv][13] = f.l0;
-                s_x[wv][14] = f.l1;
-                s_x[wv][15] = f.lD;
-            }
-            __syncthreads();
-            // the round's incoming adjoint through the deeper tiles of the
-            // round (lane 0's chunk-start adjoint of each, in the previous
-            // tile's frame), then on through the round for the next one
-            Adj x = lam;
-            for (int u = 0; u < W; ++u) {
-                if (u == wv) tl = x;
-                const int tu = rt - u;
-                if (tu < 0) break;
-                const double *q = s_x[u];
-                Adj e1, c1;
-                e1.l0 = fma(x.l0, q[0], fma(x.l1, q[1], q[5]));
-                e1.l1 = fma(x.l0, q[2], fma(x.l1, q[3], q[6]));
-                e1.lD = fma(x.lD, q[4], q[7]);
-                c1.l0 = fma(e1.l0, q[8], fma(e1.l1, q[9], q[13]));
-                c1.l1 = fma(e1.l0, q[10], fma(e1.l1, q[11], q[14]));
-                c1.lD = fma(e1.lD, q[12], q[15]);
-                const int ex = (tu > 0) ? s_cexp[tu] : 0;
-                x.l0 = ldexp(c1.l0, -ex);
-                x.l1 = ldexp(c1.l1, -ex);
-                x.lD = ldexp(c1.lD, -2 * ex);
-            }
-            lam = x;
-        }
-        // adjoint at this lane's chunk end: Psi_{l+1}(lambda_tile_end)
-        Adj le;
+        // L at the chunk's end: the tiles and the chunks below
+        double l_end, lb = lanes_below(lsum);
         {
-            Mat nq;
-            nq.a = __shfl_down(PQ.a, 1);
-            nq.b = __shfl_down(PQ.b, 1);
-            nq.c = __shfl_down(PQ.c, 1);
-            nq.d = __shfl_down(PQ.d, 1);
-            const double nd = __shfl_down(pd, 1);
-            const double nf0 = __shfl_down(pf.l0, 1), nf1 = __shfl_down(pf.l1, 1);
-            const double nfD = __shfl_down(pf.lD, 1);
-            if (lane == 63) {
-                le = tl;
+            const double tot = lane_read(lb, 63);
+            double l_tile = l_in;
+            if (W == 1) {
+                l_in += tot;
             } else {
-                le.l0 = fma(tl.l0, nq.a, fma(tl.l1, nq.b, nf0));
-                le.l1 = fma(tl.l0, nq.c, fma(tl.l1, nq.d, nf1));
-                le.lD = fma(tl.lD, nd, nfD);
+                if (lane == 0) s_l[wv] = tot;
+                __syncthreads();
+                for (int u = 0; u < W; ++u) {
+                    if (u == wv) l_tile = l_in;
+                    if (rt - u < 0) break;
+                    l_in += s_l[u];
+                }
             }
+            l_end = l_tile + lane_next<false>(lb, 0.0);
+        }
+        // then O, from the true L
+        double o_end, osum = 0.0;
+        {
+            double l = l_end;
+#pragma unroll
+            for (int i = C - 1; i >= 0; --i) {
+                const double up = fma(eb[i], e[i], l);
+                osum = fma(e[i], l + up, osum);
+                l = up;
+            }
+            const double ob = lanes_below(osum);
+            const double tot = lane_read(ob, 63);
+            double o_tile = o_in;
+            if (W == 1) {
+                o_in -= tot;
+            } else {
+                if (lane == 0) s_o[wv] = tot;
+                __syncthreads();
+                for (int u = 0; u < W; ++u) {
+                    if (u == wv) o_tile = o_in;
+                    if (rt - u < 0) break;
+                    o_in -= s_o[u];
+                }
+            }
+            o_end = o_tile - lane_next<false>(ob, 0.0);
         }
         __builtin_amdgcn_s_setprio(0);
-        // adjoint at the lane's chunk start: lambda_end J_chunk + f_chunk
-        Adj lc;
-        lc.l0 = fma(le.l0, Q.a, fma(le.l1, Q.b, f.l0));
-        lc.l1 = fma(le.l0, Q.c, fma(le.l1, Q.d, f.l1));
-        lc.lD = fma(le.lD, qd, f.lD);
-        const Adj lstart = lc;
-        // Walk 2 (forward again): the adjoint after step i follows from the
-        // one before it by the exact inverse of step i,
-        //   lambda_{i+1} = (lambda_i - f_i) J_i^{-1},  det M_i = a^2 (1 - rho^2) > 0,
-        // and gives dL/drho_i (adj_rbar).
-        {
-            double v0 = v0s, v1 = v1s, D = Ds, w1 = w1s;
-#pragma unroll kWalkUnroll
-            for (int i = 0; i < C; ++i) {
-                const int k = t0 + base + i;
-                const bool valid = (k >= 1) && (k < S);
-                double qz = 0.0;
-                {   // branch-free, as walk 1 (dq = 0 outside [1, S))
-                    const double r = s_rho[pad8(base + i)];
-                    const Map m = make_map(r, a2, sgn, valid);
-                    const double v1n = fma(v0, r, v1);
-                    const double w1p = rcp64(v1n);
-                    const double e = r * D * w1 * w1p;
-                    const double eb = s_eb[pad4(base + i)];
-                    const double x0 = lc.l0 + eb * e * r * w1p;
-                    const double x1 = lc.l1 + eb * e * (w1 + w1p);
-                    const double xD = lc.lD - eb * r * w1 * w1p;
-                    const double ie = rcp64(m.det);
-                    // M = [[A, r], [B, 1]]:  x (M^T)^{-1} = (x0 - r x1, A x1 - B x0) / det
-                    const Adj la{(x0 - r * x1) * ie, fma(m.m00, x1, -m.m10 * x0) * ie, xD * ie};
-                    const double dA = -2.0 * a2 * r * (1.0 + sgn);
-                    const double dB = -a2 * sgn;
-                    const double dE = -2.0 * a2 * r;
-                    const double rb = la.l0 * fma(v0, dA, v1 * dB) + la.l1 * v0 + eb * D * w1p * w1p + la.lD * D * dE;
-                    // Eq. 1 on this interface (samples zl = Z_{k-1}, zr = Z_k):
-                    // dL/dzr = rb dq zl, dL/dzl = -rb dq zr (dq from the gather)
-                    qz = rb * s_dq[pad8(base + i)];
-                    lc = la;
-                    const double v0n = fma(v0, m.m00, v1 * m.m10);
-                    v0 = v0n;
-                    v1 = v1n;
-                    w1 = w1p;
-                    D *= m.det;
-                }
-                s_rho[pad8(base + i)] = qz;       // s_rho now holds the interfaces' dL/dZ factors
-            }
-        }
-        le = lstart;
-        // adjoint of this tile's start state, expressed for the previous tile's
-        // (un-renormalised) end state
-        if (W == 1) {
-            Adj ls{lane_read(le.l0, 0), lane_read(le.l1, 0), lane_read(le.lD, 0)};   // le = chunk-start adjoint
-            const int ex = (t > 0) ? s_cexp[t] : 0;
-            lam.l0 = ldexp(ls.l0, -ex);
-            lam.l1 = ldexp(ls.l1, -ex);
-            lam.lD = ldexp(ls.lD, -2 * ex);
-        }
-        __syncthreads();
 
-        // dL/dZ_k per sample (rho depends on the samples on both sides):
-        // sample k is the right end of interface k-1 and the left end of
-        // interface k.  Branch-free: the interface factors vanish outside
-        // [1, S), so dL/dZ is zero for k >= S and only the store is guarded.
-        // the sample after this tile and its interface's factor: the previous
-        // tile's (W = 1), the neighbouring wavefront's, or for the round's
-        // deepest tile those kept from the last round
-        double zn_t = z_next, rn_t = rbar_next;
-        if (W > 1 && wv > 0) {
-            zn_t = s_z_w[wv - 1][pad8(0)];
-            rn_t = s_rho_w[wv - 1][pad8(0)];
-        }
-#pragma unroll 1
-        for (int jj = 0; jj < C; ++jj) {
-            const int i = jj * 64 + lane;
-            const int k = t0 + i;
-            const double zl = (i > 0) ? s_z[pad8(i - 1)] : zstart;
-            const double zr = (i + 1 < T) ? s_z[pad8(i + 1)] : zn_t;
-            const double ql = s_rho[pad8(i)];
-            const double qr = (k + 1 < S) ? ((i + 1 < T) ? s_rho[pad8(i + 1)] : rn_t) : 0.0;
-            const double zb = fma(-qr, zr, ql * zl);
-            // zbar is NULL when no volume gradient is wanted (nothing reads it)
-            if (zbar && k < S && act) zbar[obase + k] = (float)zb;
-            if (pose_part && act) {
-                // dL/dp = zb dZ/dp; dL/dR accumulates (s_k dir) outer dL/dp
-                const double sk = fma((double)k, ray.ds, ray.r0);
+        // walk up: dl/dR of every interface times d rho / dZ's common factor
+        double qz[C];
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const double gp = zb * (double)s_g[a * T + i];
-                    gsum[a] += gp;
-                    gssum[a] = fma(sk, gp, gssum[a]);
+        for (int i = C - 1; i >= 0; --i) {
+            const double r = rho[i];
+            const double om = fma(-r, r, 1.0);
+            const double tom = ts[i] * om;
+            // where t itself has underflowed, O (about t^2) has long before
+            const double inv = (tom < 1e-290) ? 0.0 : rcp64(tom);
+            const double pp = fma(ws[i], r, 1.0);
+            const double N = fma(onep * pp, pp, fma(ws[i], ws[i], -1.0));
+            const double x = ts[i] * qs[i];
+            const double rl = fma(r * ts[i], inv, ws[i] * qs[i]);
+            const double rb = fma(eb[i] * x, qs[i], fma(-2.0 * l_end, rl, -(o_end * inv) * N));
+            qz[i] = rb * dq[i];
+            const double up = fma(eb[i], e[i], l_end);
+            o_end = fma(-e[i], l_end + up, o_end);
+            l_end = up;
+        }
+        // dL/dZ_k per sample (rho depends on the samples on both sides: dL/dzr
+        // = rb dq zl, dL/dzl = -rb dq zr): sample k is the right end of
+        // interface k and the left end of interface k + 1, whose factor is the
+        // lane below's, or the deeper tile's
+        double qn = qz_in;
+        if (W > 1) {
+            if (lane == 63) s_q[wv] = qz[0];
+            __syncthreads();
+            if (wv > 0) qn = s_q[wv - 1];
+        }
+        qn = lane_next<false>(qz[0], qn);
+        double zb[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            zb[i] = fma(-(i + 1 < C ? qz[i + 1] : qn), i + 1 < C ? z[i + 1] : zr, qz[i] * (i > 0 ? z[i - 1] : zl));
+        // zbar is NULL when no volume gradient is wanted (nothing reads it)
+        if (zbar && act) {
+            float *zrow = zbar + obase + k0;
+            if (k0 + C <= S) {
+#pragma unroll
+                for (int i = 0; i < C; i += 4) {
+                    const float4_u q = {(float)zb[i], (float)zb[i + 1], (float)zb[i + 2], (float)zb[i + 3]};
+                    *reinterpret_cast<float4_u *>(zrow + i) = q;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < C; ++i)
+                    if (k0 + i < S) zrow[i] = (float)zb[i];
+            }
+        }
+        if (pose_part && act) {
+            // dL/dp = zb dZ/dp; dL/dR accumulates (s_k dir) outer dL/dp
+            double sz[C];
+#pragma unroll
+            for (int i = 0; i < C; ++i) sz[i] = fma((double)(k0 + i), ray.ds, ray.r0) * zb[i];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+#pragma unroll
+                for (int i = 0; i < C; i += 4) {
+                    const float4 q = *reinterpret_cast<const float4 *>(s_g + a * T + base + i);
+                    gsum[a] = fma(zb[i], (double)q.x, gsum[a]);
+                    gsum[a] = fma(zb[i + 1], (double)q.y, gsum[a]);
+                    gsum[a] = fma(zb[i + 2], (double)q.z, gsum[a]);
+                    gsum[a] = fma(zb[i + 3], (double)q.w, gsum[a]);
+                    gssum[a] = fma(sz[i], (double)q.x, gssum[a]);
+                    gssum[a] = fma(sz[i + 1], (double)q.y, gssum[a]);
+                    gssum[a] = fma(sz[i + 2], (double)q.z, gssum[a]);
+                    gssum[a] = fma(sz[i + 3], (double)q.w, gssum[a]);
                 }
             }
         }
+        // for the next tile up, or the next round's deepest: this (round's
+        // shallowest) tile's first interface and sample
         if (W == 1) {
-            rbar_next = lane_read(s_rho[pad8(lane)], 0);
-            z_next = lane_read(s_z[pad8(lane)], 0);
+            qz_in = lane_read(qz[0], 63);
+            z_in = lane_read(z[0], 63);
         } else {
-            // for the next round's deepest tile: this round's shallowest
-            rbar_next = s_rho_w[W - 1][pad8(0)];
-            z_next = s_z_w[W - 1][pad8(0)];
+            qz_in = s_q[W - 1];
+            z_in = s_z_w[W - 1][zi(0)];
         }
         __syncthreads();
     }
@@ -1444,12 +1295,12 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
     if (pose_part) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            r[a] = wave_sum(gsum[a]);
-            r[3 + a] = wave_sum(gssum[a]);
+            r[a] = lanes_sum(gsum[a]);
+            r[3 + a] = lanes_sum(gssum[a]);
         }
     }
     double ls = 0.0;
-    if (FUSED && loss_acc) ls = wave_sum(loss);
+    if (FUSED && loss_acc) ls = lanes_sum(loss);
     if (W > 1) {
         // the wavefronts' shares added in a fixed order
         if (lane == 0) {
@@ -2589,7 +2440,7 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
 // --------------------------------------------------------------------------
 #define DUS_FWD_LAUNCH(CH, SPK, WV, NG, TAB, ZERO, STR)                                         \
     hipLaunchKernelGGL((k_forward<CH, SPK, WV>), dim3(NG), dim3(64 * WV), 0, STR, v, p, TAB, poses, out, \
-                       min_pivot, pivot_base, carry, carry_exp, cstate, gain, xcd_group, ZERO)
+                       min_pivot, pivot_base, zcar, reinterpret_cast<float *>(states), gain, xcd_group, ZERO)
 
 #define DUS_FWD_CASE(CH)                                                                       \
     case CH:                                                                                   \
@@ -2622,7 +2473,7 @@ static int auto_fwd_chunk(const FanTable &t)
 
 hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const PhysArgs &p,
                           const FanTable &t, const float *poses, float *out, float *min_pivot,
-                          int pivot_base, double *carry, int32_t *carry_exp, double *cstate, float *gain,
+                          int pivot_base, double *zcar, int32_t *, double *states, float *gain,
                           hipStream_t st, const ZeroArgs &zero, int span_samples, const SideStream *side)
 {
     if (t.total_rays <= 0) return hipSuccess;
@@ -2658,34 +2509,44 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
     return e;
 }
 
-#define DUS_BWD_LAUNCH(CH, SPK, FUSED, WV, NG, TAB, STR)                                          \
-    hipLaunchKernelGGL((k_backward<CH, SPK, FUSED, WV>), dim3(NG), dim3(64 * WV), 0, STR, v, p, TAB,   \
+#define DUS_BWD_LAUNCH(CH, SPK, FUSED, WV, WHOLE, NG, TAB, STR)                                    \
+    hipLaunchKernelGGL((k_backward<CH, SPK, FUSED, WV, WHOLE>), dim3(NG), dim3(64 * WV), 0, STR, v, p, TAB, \
                        poses, zbar ? rays : nullptr, gsrc, target, zbar, pose_acc ? pose_part : nullptr, \
-                       loss, carry, carry_exp, cstate, gain, xcd_group)
+                       loss, zcar, reinterpret_cast<const float *>(states), gain, xcd_group)
 
-// the long rays (the table's first n_span) with the forward's hand-off take
-// kSpanWaves * 4 / C wavefronts each (the LDS of C = 8 holds half as many)
+// from the forward's records: the long rays (the table's first n_span) take
+// kSpanWaves * 4 / C wavefronts each (the registers of C = 8 allow half as many)
 #define DUS_BWD_CASE(CH)                                                                       \
     case CH:                                                                                   \
         if (n_span > 0) {                                                                      \
-            if (fused) DUS_BWD_LAUNCH(CH, false, true, kSpanWaves * 4 / CH, n_span, t, sst);        \
-            else DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, n_span, t, sst);             \
+            if (fused) DUS_BWD_LAUNCH(CH, false, true, kSpanWaves * 4 / CH, false, n_span, t, sst);  \
+            else if (spk) DUS_BWD_LAUNCH(CH, true, false, kSpanWaves * 4 / CH, false, n_span, t, sst); \
+            else DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, false, n_span, t, sst);       \
         }                                                                                      \
         if (n_one > 0) {                                                                       \
-            if (fused) {                                                                       \
-                if (spk) DUS_BWD_LAUNCH(CH, true, true, 1, t.total_rays, t1, st);                     \
-                else DUS_BWD_LAUNCH(CH, false, true, 1, t.total_rays, t1, st);                        \
-            } else {                                                                           \
-                if (spk) DUS_BWD_LAUNCH(CH, true, false, 1, t.total_rays, t1, st);                    \
-                else DUS_BWD_LAUNCH(CH, false, false, 1, t.total_rays, t1, st);                       \
-            }                                                                                  \
+            if (fused) DUS_BWD_LAUNCH(CH, false, true, 1, false, t.total_rays, t1, st);               \
+            else if (spk) DUS_BWD_LAUNCH(CH, true, false, 1, false, t.total_rays, t1, st);            \
+            else DUS_BWD_LAUNCH(CH, false, false, 1, false, t.total_rays, t1, st);                    \
+        }                                                                                      \
+        break;
+
+// without records (rays of at most kWholeSamples): W wavefronts per ray, one
+// per 256 samples
+#define DUS_WHOLE_CASE(WV)                                                                     \
+    case WV:                                                                                   \
+        if (fused) {                                                                           \
+            if (spk) DUS_BWD_LAUNCH(4, true, true, WV, true, n, t1, st);                              \
+            else DUS_BWD_LAUNCH(4, false, true, WV, true, n, t1, st);                                 \
+        } else {                                                                               \
+            if (spk) DUS_BWD_LAUNCH(4, true, false, WV, true, n, t1, st);                             \
+            else DUS_BWD_LAUNCH(4, false, false, WV, true, n, t1, st);                                \
         }                                                                                      \
         break;
 
 hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const PhysArgs &p,
                           const FanTable &t, const float *poses, RayRec *rays, const float *gsrc,
                           const float *target, float *zbar, double *pose_acc, double *pose_part, double *loss,
-                          const double *carry, const int32_t *carry_exp, const double *cstate,
+                          const double *zcar, const int32_t *, const double *states,
                           const float *gain, hipStream_t st, int span_samples, const SideStream *side)
 {
     if (t.total_rays <= 0) return hipSuccess;
@@ -2694,12 +2555,30 @@ hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const Phys
     if (chunk != 4 && chunk != 8) return hipErrorInvalidValue;
     const bool fused = (target != nullptr);
     const bool spk = p.speckle && !gain;      // recorded gains replace the speckle variates
-    if (!carry) cstate = nullptr;             // chunk states are read in the frames of the carry records
-    // several wavefronts per long ray need the forward's carry records and
-    // chunk states (and its gains, when there is speckle)
-    const int n_span = (carry && cstate && !spk) ? span_rays(t, span_samples) : 0;
-    const int n_one = t.total_rays - n_span;
     FanTable t1 = t;
+    if (!states) {
+        if (longest_ray(t) > kWholeSamples) return hipErrorInvalidValue;
+        // fans of one wavefront count after the other (a table lists its fans
+        // longest first)
+        for (int f = 0; f < t.n;) {
+            int w = 1, n = 0;
+            while (w * kCarryBlock < t.f[f].n_samples) w *= 2;
+            t1.ray0 = t.f[f].ray_begin;
+            for (; f < t.n && (w == 1 || 2 * t.f[f].n_samples > w * kCarryBlock); ++f) n += t.f[f].n_rays;
+            if (n <= 0) continue;
+            switch (w) {
+                DUS_WHOLE_CASE(1)
+                DUS_WHOLE_CASE(2)
+                DUS_WHOLE_CASE(4)
+                DUS_WHOLE_CASE(8)
+            }
+        }
+        return hipGetLastError();
+    }
+    if (fused && spk) return hipErrorInvalidValue;    // the fused step records its gains
+    // several wavefronts per long ray
+    const int n_span = span_rays(t, span_samples);
+    const int n_one = t.total_rays - n_span;
     t1.ray0 = n_span;
     hipStream_t sst = st;
     if (n_span > 0 && side) {
@@ -2797,19 +2676,6 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
         return hipErrorInvalidValue;
     }
     return hipGetLastError();
-}
-
-hipError_t launch_backward(int chunk, int xcd_group, int scatter_rays, const VolArgs &v,
-                           const PhysArgs &p, const FanTable &t, const float *poses, RayRec *rays,
-                           const float *gsrc, const float *target, float *zbar, float *gZ,
-                           double *pose_acc, double *pose_part, double *loss, const double *carry,
-                           const int32_t *carry_exp, const double *cstate, const float *gain,
-                           hipStream_t st)
-{
-    hipError_t e = launch_adjoint(chunk, xcd_group, v, p, t, poses, rays, gsrc, target, zbar, pose_acc, pose_part,
-                                  loss, carry, carry_exp, cstate, gain, st);
-    if (e != hipSuccess) return e;
-    return launch_scatter(scatter_rays, xcd_group, v, t, rays, zbar, gZ, st);
 }
 
 #define DUS_BLUR_LAUNCH(MODE, TGT, IMG, LOSS)                                                       \
