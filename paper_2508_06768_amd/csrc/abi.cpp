@@ -254,6 +254,7 @@ struct WsLayout {
     size_t part = 0, part_bytes = 0;   // loss partials (plan step)
     size_t zc = 0, zc_bytes = 0;       // samples before the carry blocks, one double each (plan step)
     size_t cst = 0, cst_bytes = 0;     // states for the adjoint, kStateFloats per carry block
+    size_t geo = 0, geo_bytes = 0;     // ray geometry the forward hands the adjoint, one RayGeom per ray (plan step)
     size_t gain = 0, gain_bytes = 0;   // per-pixel gains recorded by the forward (plan step)
     size_t rays = 0, rays_bytes = 0;   // ray geometry the adjoint hands the scatter, one RayRec per ray
     size_t fix = 0, fix_bytes = 0;     // deterministic plan: 64-bit fixed-point dL/dZ per voxel
@@ -331,6 +332,9 @@ WsLayout layout(const dus_fan *fans, int32_t n_poses, const dus_physics *p, int 
         L.cst = off;
         L.cst_bytes = std::max<size_t>(rec, 1) * dus::kStateFloats * sizeof(float);
         off = align_up(off + L.cst_bytes);
+        L.geo = off;
+        L.geo_bytes = L.rp_bytes / (dus::kRayPart * sizeof(double)) * sizeof(dus::RayGeom);
+        off = align_up(off + L.geo_bytes);
         if (p->speckle_on || p->atten_mode == DUS_ATTEN_POST_HOC) {
             L.gain = off;
             L.gain_bytes = img;
@@ -932,11 +936,20 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
         DUS_HIP(hipStreamWaitEvent(p->side.st, p->side.fork, 0), "fork wait");
         forked = true;
     }
+    // the tables with the place of their rays' geometry
+    std::vector<dus::FanTable> tabs = p->tabs;
+    {
+        dus::RayGeom *geo = reinterpret_cast<dus::RayGeom *>((char *)ws + p->ws.geo);
+        for (auto &t : tabs) {
+            t.geom = geo;
+            geo += t.total_rays;
+        }
+    }
     DUS_HIP(mark(DUS_PHASE_FORWARD), "event");
     if (fwd) {
         float *img = blur ? reinterpret_cast<float *>((char *)ws + p->ws.pre) : bmode;
-        for (size_t i = 0; i < p->tabs.size(); ++i) {
-            const auto &t = p->tabs[i];
+        for (size_t i = 0; i < tabs.size(); ++i) {
+            const auto &t = tabs[i];
             if (t.total_rays <= 0) continue;
             // the first table's forward clears dL/dZ and the pose sums
             DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, img, nullptr, 0, zc, nullptr, cst,
@@ -952,8 +965,8 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
         const float *pre = reinterpret_cast<float *>((char *)ws + p->ws.pre);
         float *res = p->ws.res_bytes ? reinterpret_cast<float *>((char *)ws + p->ws.res) : nullptr;
         float *ebw = reinterpret_cast<float *>((char *)ws + p->ws.eb);
-        for (size_t i = 0; i < p->tabs.size(); ++i) {
-            const auto &t = p->tabs[i];
+        for (size_t i = 0; i < tabs.size(); ++i) {
+            const auto &t = tabs[i];
             DUS_HIP(dus::launch_blur_residual(pa, t, pre, target, bmode, res, ebw, loss ? part + n_part : nullptr,
                                               tst(i)),
                     "blur/loss kernel");
@@ -967,8 +980,8 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     const bool adj = blur ? (gZ || grad_pose) : true;
     int64_t r0 = 0;        // rays of the tables before this one (pose partials)
     if (adj)
-        for (size_t i = 0; i < p->tabs.size(); ++i) {
-            const auto &t = p->tabs[i];
+        for (size_t i = 0; i < tabs.size(); ++i) {
+            const auto &t = tabs[i];
             // without a forward before it, the adjoint needs the records only
             // for rays too long to gather at once
             const bool rec = fwd || dus::longest_ray(t) > dus::kWholeSamples;
@@ -995,15 +1008,15 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     if (adj && gZ) {
         if (fix) {
             r0 = 0;
-            for (const auto &t : p->tabs) {
+            for (const auto &t : tabs) {
                 DUS_HIP(dus::launch_abs_rows(t, zbar, fsc + 4 + r0, st), "fixed-point bound kernel");
                 r0 += t.total_rays;
             }
             DUS_HIP(dus::launch_fix_scale(fsc + 4, r0, fsc, st), "fixed-point scale kernel");
         }
         r0 = 0;
-        for (size_t i = 0; i < p->tabs.size(); ++i) {
-            const auto &t = p->tabs[i];
+        for (size_t i = 0; i < tabs.size(); ++i) {
+            const auto &t = tabs[i];
             // two chains: two scatters at a time share the wavefront budget
             DUS_HIP(dus::launch_scatter(sc.scatter_rays, sc.xcd_group, va, t, rays + r0, zbar, gZ, tst(i), fix, fsc,
                                         two ? 16384 : 32768),
@@ -1017,8 +1030,8 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     DUS_HIP(mark(DUS_PHASE_FINISH), "event");
     if (adj && grad_pose) {
         r0 = 0;
-        for (size_t i = 0; i < p->tabs.size(); ++i) {
-            const auto &t = p->tabs[i];
+        for (size_t i = 0; i < tabs.size(); ++i) {
+            const auto &t = tabs[i];
             DUS_HIP(dus::launch_pose_reduce(t, rpart + dus::kRayPart * r0, acc, tst(i)), "pose reduction kernel");
             r0 += t.total_rays;
         }

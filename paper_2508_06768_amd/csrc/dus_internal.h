@@ -43,12 +43,32 @@ constexpr int kStateFloats = kCarryBlock / kStateStride * 4;     // in units of 
 // them once, one wavefront per 256 samples
 constexpr int kWholeSamples = 8 * kCarryBlock;
 
+// A ray's geometry, written by the adjoint kernel (which sets it up from the
+// pose and the fan) for the dL/dZ scatter: sample k sits at voxel coordinate
+// u0 + k du.
+struct RayRec {
+    double u0[3], du[3];
+};
+static_assert(sizeof(RayRec) == 48, "RayRec layout");
+
+// A ray's geometry as the fused step's forward sets it up, read by its
+// adjoint: sample k sits at voxel coordinate u0 + k du; round-trip amplitude
+// a2 over one step; the probe-frame direction (dirx, 0, dirz); the ray's
+// orthonormal basis in the world, over the voxel spacing.
+struct RayGeom {
+    double u0[3], du[3], bd[3], bt[3], bn[3], a2, dirx, dirz;
+};
+static_assert(sizeof(RayGeom) == 144, "RayGeom layout");
+
 struct FanTable {
     int32_t n;              // fans in this launch
     int32_t total_rays;
     int32_t total_blur_blocks;
     int32_t ray0;           // forward and adjoint, one wavefront per ray: rays below ray0 are
                             // another launch's (their wavefronts return at once)
+    int32_t ray1;           // adjoint without records: the launch's rays are [ray0, ray1)
+    RayGeom *geom;          // forward: if not NULL, where to record the rays' geometry; adjoint with
+                            // the forward's records: where to find it (else set up again)
     FanRec f[kMaxFans];
 };
 
@@ -59,14 +79,6 @@ inline int longest_ray(const FanTable &t)
         if (t.f[f].n_samples > s) s = t.f[f].n_samples;
     return s;
 }
-
-// A ray's geometry, written by the adjoint kernel (which sets it up from the
-// pose and the fan) for the dL/dZ scatter: sample k sits at voxel coordinate
-// u0 + k du.
-struct RayRec {
-    double u0[3], du[3];
-};
-static_assert(sizeof(RayRec) == 48, "RayRec layout");
 
 struct VolArgs {
     const float *Z;

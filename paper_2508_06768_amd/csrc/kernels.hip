@@ -62,6 +62,30 @@ __device__ __forceinline__ double uniform(double x)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// the wavefront's own LDS traffic ordered (its lanes run in step and its LDS
+// accesses complete in order: only the compiler has to be held)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Adjoint with one wavefront per ray: four neighbouring rays share a block,
+// and so a CU's L1, where their stencils mostly meet (64 x 256 x 1024: 132 us,
+// against 138 us with one ray per block and 140 us with eight; the forward,
+// which issues more per load, is as fast with one, 120 us, as with four).
+constexpr int kBlockRays = 4;
+constexpr int adjoint_waves(int w) { return w == 1 ? kBlockRays : w; }
+
+// a barrier among the W wavefronts of a ray
+template <int W>
+__device__ __forceinline__ void ray_sync()
+{
+    if (W == 1) wave_sync();
+    else __syncthreads();
+}
+
 __device__ __forceinline__ double wave_sum(double x)
 {
 #pragma unroll
@@ -139,8 +163,10 @@ __device__ void rotation(const double w[3], double R[9])
         A = 1.0 - th2 / 6.0;
         B = 0.5 - th2 / 24.0;
     } else {
-        A = sin(th) / th;
-        B = (1.0 - cos(th)) / th2;
+        double sn, cs;
+        sincos(th, &sn, &cs);
+        A = sn / th;
+        B = (1.0 - cs) / th2;
     }
     // R = I + A [w]x + B [w]x^2, [w]x^2 = w w^T - |w|^2 I
     R[0] = 1.0 + B * (w[0] * w[0] - th2);
@@ -160,7 +186,8 @@ struct Ray {
     double dirx, dirz;     // probe-frame direction (y component is 0)
     double r0, ds;
     // orthonormal basis, world frame: the ray's direction D, its in-plane
-    // normal T = R (cz, 0, -sx) and the fan plane's normal N = R (0, 1, 0)
+    // normal T = R (cz, 0, -sx) and the fan plane's normal N = R (0, 1, 0),
+    // each component over the voxel spacing of its axis
     double bd[3], bt[3], bn[3];
 };
 
@@ -177,23 +204,21 @@ __device__ __forceinline__ void setup_ray(const VolArgs &v, const PhysArgs &p, c
     rotation(w, R);
     const double A = fr.aperture;
     const double th = fr.n_rays > 1 ? -0.5 * A + (double)j * A / (double)(fr.n_rays - 1) : 0.0;
-    const double sx = sin(th), cz = cos(th);
+    double sx, cz;
+    sincos(th, &sx, &cz);
     const double d[3] = {R[0] * sx + R[2] * cz, R[3] * sx + R[5] * cz, R[6] * sx + R[8] * cz};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        ray.bd[a] = d[a];
-        ray.bt[a] = R[3 * a] * cz - R[3 * a + 2] * sx;
-        ray.bn[a] = R[3 * a + 1];
-    }
     const double r0 = fr.r0, ds = fr.ds;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const double ih = 1.0 / (double)v.h[a];
         ray.u0[a] = (t[a] + r0 * d[a] - (double)v.o[a]) * ih;
         ray.du[a] = ds * d[a] * ih;
+        ray.bd[a] = d[a] * ih;
+        ray.bt[a] = (R[3 * a] * cz - R[3 * a + 2] * sx) * ih;
+        ray.bn[a] = R[3 * a + 1] * ih;
     }
     const double amp = (p.atten == 0)
-                           ? pow(10.0, -(double)p.alpha * (double)p.freq * (ds / 10.0) / 20.0)
+                           ? exp10(-(double)p.alpha * (double)p.freq * (ds / 10.0) / 20.0)
                            : 1.0;
     ray.a2 = amp * amp;
     ray.dirx = sx;
@@ -218,6 +243,49 @@ __device__ __forceinline__ void setup_ray(const VolArgs &v, const PhysArgs &p, c
         ray.bt[a] = uniform(ray.bt[a]);
         ray.bn[a] = uniform(ray.bn[a]);
     }
+}
+
+// the ray's geometry, as the forward hands it to the adjoint (one lane)
+__device__ __forceinline__ void store_geom(const Ray &ray, RayGeom *__restrict__ q)
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        q->u0[a] = ray.u0[a];
+        q->du[a] = ray.du[a];
+        q->bd[a] = ray.bd[a];
+        q->bt[a] = ray.bt[a];
+        q->bn[a] = ray.bn[a];
+    }
+    q->a2 = ray.a2;
+    q->dirx = ray.dirx;
+    q->dirz = ray.dirz;
+}
+
+// (q is the same on every lane: scalar loads; made opaque, so that each call
+// loads again)
+__device__ __forceinline__ void load_basis(const RayGeom *__restrict__ q, Ray &ray)
+{
+    asm volatile("" : "+s"(q));
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        ray.bd[a] = q->bd[a];
+        ray.bt[a] = q->bt[a];
+        ray.bn[a] = q->bn[a];
+    }
+    ray.dirx = q->dirx;
+    ray.dirz = q->dirz;
+}
+
+__device__ __forceinline__ void load_geom(const FanRec &fr, const RayGeom *__restrict__ q, Ray &ray)
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        ray.u0[a] = q->u0[a];
+        ray.du[a] = q->du[a];
+    }
+    ray.a2 = q->a2;
+    ray.r0 = fr.r0;
+    ray.ds = fr.ds;
 }
 
 // cell index (clamped) and fraction along one axis; NaN positions clamp to 0.
@@ -271,15 +339,31 @@ __device__ __forceinline__ bool segment_inside(const VolArgs &v, const Ray &ray,
 
 __device__ __forceinline__ double lerp(double a, double b, double t) { return fma(t, b - a, a); }
 
+// two neighbouring voxels, at any multiple of 4 bytes
+typedef float float2_u __attribute__((ext_vector_type(2), aligned(4)));
+
+// voxels idx and idx + 1 of the row Z points into.  NARROW: the volume spans
+// less than 4 GiB, so the offset is 32 bits beside a scalar base and the four
+// rows of a stencil share it (a 64-bit address per row takes an add each).
+template <bool NARROW>
+__device__ __forceinline__ float2_u voxel_pair(const float *__restrict__ Z, int idx)
+{
+    if (NARROW)
+        return *reinterpret_cast<const float2_u *>(reinterpret_cast<const char *>(Z) + ((unsigned)idx << 2));
+    return *reinterpret_cast<const float2_u *>(Z + idx);
+}
+
 // trilinear value (lerp along x, then y, then z), FP64 from FP32 corners
+template <bool NARROW = false>
 __device__ __forceinline__ double trilinear(const float *__restrict__ Z, int nx, int sxy,
                                             const Stencil &s, double *grad)
 {
-    const float *p = Z + s.idx;
-    const double c000 = p[0], c100 = p[1];
-    const double c010 = p[nx], c110 = p[nx + 1];
-    const double c001 = p[sxy], c101 = p[sxy + 1];
-    const double c011 = p[sxy + nx], c111 = p[sxy + nx + 1];
+    const float2_u p00 = voxel_pair<NARROW>(Z, s.idx), p10 = voxel_pair<NARROW>(Z + nx, s.idx);
+    const float2_u p01 = voxel_pair<NARROW>(Z + sxy, s.idx), p11 = voxel_pair<NARROW>(Z + sxy + nx, s.idx);
+    const double c000 = p00.x, c100 = p00.y;
+    const double c010 = p10.x, c110 = p10.y;
+    const double c001 = p01.x, c101 = p01.y;
+    const double c011 = p11.x, c111 = p11.y;
     const double a00 = lerp(c000, c100, s.fx), a10 = lerp(c010, c110, s.fx);
     const double a01 = lerp(c001, c101, s.fx), a11 = lerp(c011, c111, s.fx);
     const double b0 = lerp(a00, a10, s.fy), b1 = lerp(a01, a11, s.fy);
@@ -315,6 +399,10 @@ __device__ __forceinline__ double iface_rho(double zl, double zr, bool absm, dou
 __device__ __forceinline__ void philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                        uint32_t k0, uint32_t k1, uint32_t out[4])
 {
+    // the round keys are formed here, ten scalar adds each beside the vector
+    // work; hoisted out of the callers' loops they would hold (and spill)
+    // twenty scalar registers
+    asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         if (r > 0) {
@@ -343,7 +431,7 @@ __device__ __forceinline__ void philox(uint32_t c0, uint32_t c1, uint32_t c2, ui
 // (about 1 ulp) apply directly
 __device__ __forceinline__ float rayleigh(uint32_t x)
 {
-    const float u = (float)((x >> 8) + 1u) * 0x1p-24f;
+    const float u = fmaf((float)(x >> 8), 0x1p-24f, 0x1p-24f);      // (x >> 8) + 1 at most 2^24: exact
     return __builtin_amdgcn_sqrtf(-0.88254240061060638f * __builtin_amdgcn_logf(u));
 }
 
@@ -387,26 +475,29 @@ __device__ __forceinline__ void speckle_fill(const PhysArgs &p, int t0, int j, i
     speckle_radial<T>(p, t0, j, sid, lane, s_xir);
 }
 
-// per-launch constants of pixel_gain: 1/(S-1) and 1/cell
+// per-launch constants of pixel_gain: 1/(S-1) (1 for the one sample of S = 1,
+// whose index is 0) and 1/cell
 struct GainK {
     float inv_sm1, inv_cell;
 };
 
 __device__ __forceinline__ GainK gain_consts(const PhysArgs &p, int S)
 {
-    return GainK{S > 1 ? 1.0f / (float)(S - 1) : 0.0f, 1.0f / (float)p.cell};
+    return GainK{S > 1 ? 1.0f / (float)(S - 1) : 1.0f, 1.0f / (float)p.cell};
 }
 
 // speckle multiplier of a pixel at depth fraction zeta, cell fraction fr
 // between the radial cell values x0 and x1, granular variate xg.  zeta^gam
 // with zeta in [1/(S-1), 1] (a normal number); a power below 2^-126 may
 // flush to zero, which leaves the FP32 gain unchanged.
+// POSITIVE: the caller knows zeta > 0.
+template <bool POSITIVE = false>
 __device__ __forceinline__ float speckle_mult(const PhysArgs &p, float zeta, float fr, float x0, float x1,
                                               float xg)
 {
     const float xr = (1.0f - fr) * x0 + fr * x1;
     float pw;
-    if (zeta > 0.0f) pw = __builtin_amdgcn_exp2f(p.gam * __builtin_amdgcn_logf(zeta));
+    if (POSITIVE || zeta > 0.0f) pw = __builtin_amdgcn_exp2f(p.gam * __builtin_amdgcn_logf(zeta));
     else pw = (p.gam == 0.0f) ? 1.0f : 0.0f;
     return 1.0f + p.Ar * pw * (xr - 1.0f) + (p.Ag0 + p.Ag1 * zeta) * (xg - 1.0f);
 }
@@ -477,12 +568,6 @@ __device__ __forceinline__ double gather_tile_body(const VolArgs &v, const Ray &
 {
     constexpr int T = 64 * C;
     const int sxy = v.nx * v.ny;
-    // 1 / h once per tile, not an FP64 division per sample and axis
-    double ih[3] = {0.0, 0.0, 0.0};
-    if (KEEPG) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) ih[a] = 1.0 / (double)v.h[a];
-    }
     double z = 0.0;
 #pragma unroll GATHER_UNROLL
     for (int jj = 0; jj < C; ++jj) {
@@ -490,12 +575,13 @@ __device__ __forceinline__ double gather_tile_body(const VolArgs &v, const Ray &
         const int k = t0 + i;
         const Stencil st = stencil_at<INSIDE>(v, ray, min(k, S - 1));
         double gu[3];
-        z = trilinear(v.Z, v.nx, sxy, st, KEEPG ? gu : nullptr);
+        z = trilinear<INSIDE>(v.Z, v.nx, sxy, st, KEEPG ? gu : nullptr);
         s_z[zi(i)] = z;
         if (k == 0) s_z[zi(-1)] = z;
         if (KEEPG) {
-            // dZ/dp per mm (dZ/du / h, zero along an axis where the sample
-            // lies outside the volume: clamped), kept in FP32 as its
+            // dZ/dp per mm (dZ/du / h, the spacing taken with the basis; zero
+            // along an axis where the sample lies outside the volume:
+            // clamped), kept in FP32 as its
             // components along the ray and across it (the ray's basis), so
             // that the rounding of the large component along the ray stays
             // along the ray, where it cannot reach the rotation gradient
@@ -506,7 +592,7 @@ __device__ __forceinline__ double gather_tile_body(const VolArgs &v, const Ray &
             for (int a = 0; a < 3; ++a) {
                 const double u = fma(kk, ray.du[a], ray.u0[a]);
                 const bool inside = INSIDE || ((u >= 0.0) && (u <= (double)(n[a] - 1)));
-                gw[a] = inside ? gu[a] * ih[a] : 0.0;
+                gw[a] = inside ? gu[a] : 0.0;
             }
             s_g[i] = (float)fma(gw[0], ray.bd[0], fma(gw[1], ray.bd[1], gw[2] * ray.bd[2]));
             s_g[T + i] = (float)fma(gw[0], ray.bt[0], fma(gw[1], ray.bt[1], gw[2] * ray.bt[2]));
@@ -520,9 +606,11 @@ template <int C, bool KEEPG, int W>
 __device__ __forceinline__ double gather_tile(const VolArgs &v, const Ray &ray, int t0, int S, int lane, double *s_z,
                                               float *s_g = nullptr)
 {
-    // a tile whose samples all lie inside the volume skips the clamps (the
-    // ray is the same on every lane, so the branch is uniform)
-    if (segment_inside(v, ray, t0, min(t0 + 64 * C - 1, S - 1)))
+    // a tile whose samples all lie inside the volume skips the clamps, and
+    // takes 32-bit offsets in a volume below 4 GiB (the ray is the same on
+    // every lane, so the branch is uniform)
+    const bool narrow = (long long)v.nx * v.ny * v.nz < (1ll << 30);
+    if (narrow && segment_inside(v, ray, t0, min(t0 + 64 * C - 1, S - 1)))
         return gather_tile_body<C, KEEPG, true, W>(v, ray, t0, S, lane, s_z, s_g);
     return gather_tile_body<C, KEEPG, false, W>(v, ray, t0, S, lane, s_z, s_g);
 }
@@ -661,19 +749,26 @@ __device__ __forceinline__ void chunk_gains(const PhysArgs &p, const GainK &gk, 
             for (int u = 0; u < 4; ++u) gn[4 * q + u] = x[u];
         }
         // the lane's samples are consecutive: the radial cell index of the
-        // first is exact (cell_of), the others step it
-        int c, r;
-        cell_of(p, gk, k0, c, r);
-        c -= t0 / p.cell;          // index into s_xir
+        // first is exact (cell_of), the others step it, and the sample and
+        // remainder step as floats (whole numbers: exact)
+        int c, r0;
+        cell_of(p, gk, k0, c, r0);
+        const float *x = s_xir + (c - t0 / p.cell);
+        const float kf = (float)k0, cellf = (float)p.cell;
+        float r = (float)r0;
 #pragma unroll
         for (int i = 0; i < C; ++i) {
-            const int k = k0 + i;
-            float g = speckle_mult(p, (float)k * gk.inv_sm1, (float)r * gk.inv_cell, s_xir[c], s_xir[c + 1], gn[i]);
-            if (p.atten == 1) g *= exp2f((float)((double)k * (double)postc));
-            gn[i] = g;
-            const bool wrap = (r + 1 == p.cell);
-            c += wrap ? 1 : 0;
-            r = wrap ? 0 : r + 1;
+            const float zeta = (kf + (float)i) * gk.inv_sm1;
+            gn[i] = (i == 0) ? speckle_mult(p, zeta, r * gk.inv_cell, x[0], x[1], gn[i])
+                             : speckle_mult<true>(p, zeta, r * gk.inv_cell, x[0], x[1], gn[i]);
+            r += 1.0f;
+            const bool wrap = (r == cellf);
+            x += wrap ? 1 : 0;
+            r = wrap ? 0.0f : r;
+        }
+        if (p.atten == 1) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) gn[i] *= exp2f((float)((double)(k0 + i) * (double)postc));
         }
     } else if (p.atten == 1) {
 #pragma unroll
@@ -706,7 +801,7 @@ typedef double double2_u __attribute__((ext_vector_type(2), aligned(4)));
 // layout, that of sample 4 c at element 4 (c - 1), and the first one, a
 // constant, is left out.  out may be NULL (states, and gains if wanted).
 // --------------------------------------------------------------------------
-template <int C, bool SPK, int W>
+template <int C, bool SPK, int W, bool PIV>
 __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTable tab,
                                                     const float *__restrict__ poses,
                                                     float *__restrict__ out, float *__restrict__ minpiv,
@@ -750,6 +845,7 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
     const int S = fr.n_samples;
     Ray ray;
     setup_ray(v, p, fr, poses, j, ray);
+    if (tab.geom && threadIdx.x == 0) store_geom(ray, tab.geom + g);
     const bool absm = (p.refl == 0);
     const double sgn = absm ? 1.0 : -1.0;
     const double a2 = ray.a2;
@@ -760,7 +856,6 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
     // state carried into the round (W > 1) or the tile (W = 1)
     double c0 = 0.0, c1 = 1.0, cD = d_start(a2), zprev = 0.0;
     double piv = 1e300;
-    const bool want_piv = (minpiv != nullptr);
     const long long crec = (long long)fr.carry_begin + (long long)j * ((S + kCarryBlock - 1) / kCarryBlock);
     float *srow = nullptr;
     if (states) srow = states + (zcar ? crec * kStateFloats : obase - 4);
@@ -778,7 +873,7 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
             if (W == 1) zprev = lane_read(zl, 63);
             if (SPK) speckle_radial<T>(p, t0, j, fr.speckle_id, lane, s_xir);
         }
-        __syncthreads();
+        ray_sync<W>();
 
         const int base = lane * C;
         Mat Q, X, Tot;
@@ -804,7 +899,7 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
                 s_tot[wv][3] = Tot.d;
                 s_tot[wv][4] = td;
             }
-            __syncthreads();
+            ray_sync<W>();
             // the round's carry through the tiles before this one; then on
             // through the rest of the round for the next round's carry
             for (int u = 0; u < W; ++u) {
@@ -846,7 +941,7 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
                 // the pixel leaves in FP32: the hardware FP64 reciprocal, without
                 // the Newton step, is accurate well beyond that
                 pix[i] = (float)(r * D * __builtin_amdgcn_rcp(v1 * v1n));
-                if (want_piv) piv = (k >= 1 && k < S) ? fmin(piv, fabs(v1n * rcp64(v1))) : piv;
+                if (PIV) piv = (k >= 1 && k < S) ? fmin(piv, fabs(v1n * rcp64(v1))) : piv;
                 const double v0n = fma(v0, m.m00, v1 * m.m10);
                 v0 = v0n;
                 v1 = v1n;
@@ -882,15 +977,15 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
                 }
             }
         }
-        __syncthreads();
+        ray_sync<W>();
     }
-    if (want_piv) {
+    if (PIV) {
         piv = wave_min(piv);
         if (W == 1) {
             if (lane == 0) minpiv[pivot_base + fr.pivot_begin + j] = (float)piv;
         } else {
             if (lane == 0) s_piv[wv] = piv;
-            __syncthreads();
+            ray_sync<W>();
             if (threadIdx.x == 0) {
                 for (int u = 1; u < W; ++u) piv = fmin(piv, s_piv[u]);
                 minpiv[pivot_base + fr.pivot_begin + j] = (float)piv;
@@ -918,17 +1013,19 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
 // Lane l takes the chunk 63 - l of the tile's interfaces, so that the sums
 // run over the lanes below.
 //
-// Bound by VALU issue and latency (161 VGPRs: 3 wavefronts per SIMD; capped
-// at 4 it spills and takes 250 us).  64 poses x 256 rays x 1024 samples with
-// the forward's records, one launch: 239 us with the (v0, v1, D) adjoint,
-// 151 us with the sums.
+// Bound by memory latency and VALU issue (0.62 busy at 4 wavefronts per SIMD,
+// 128 VGPRs).  64 poses x 256 rays x 1024 samples with the forward's records,
+// one launch: 239 us with the (v0, v1, D) adjoint, 151 us with the sums, 132
+// us with the rays' geometry handed over, 32-bit gather offsets, loads ahead
+// of the gather and no barrier that drains them.
 //
-// Where the state (w, t) at a chunk's start comes from:
-//   WHOLE = false: the records of the forward kernel (states, zcar).
+// Where the state (w, t) at a chunk's start comes from (FROM):
+//   kRecords: the records of the fused step's forward (states, zcar, geom).
+//   kRows: states alone, in the rays' rows; the ray is set up again.
 //     W = 1: one wavefront per ray walks its tiles from the deepest up.
 //     W > 1 (rays of many tiles): W wavefronts share a ray and take W
 //     consecutive tiles at a time.
-//   WHOLE = true (rays of at most W tiles): chunk products and a lane scan of
+//   kWholeRay (rays of at most W tiles): chunk products and a lane scan of
 //     the wavefront's own tile, and the carries pushed through the tiles
 //     before it, as k_forward does it with several wavefronts: the ray is
 //     gathered once, and no forward pass comes before.
@@ -997,8 +1094,11 @@ __device__ __forceinline__ void load_chunk(const float *__restrict__ row, int k0
     }
 }
 
-template <int C, bool SPK, bool FUSED, int W, bool WHOLE>
-__global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanTable tab,
+enum { kRecords = 0, kRows = 1, kWholeRay = 2 };
+
+template <int C, bool SPK, bool FUSED, int W, int FROM>
+__global__ __launch_bounds__(64 * adjoint_waves(W), (C == 4 && W == 1 && FROM == kRecords && !FUSED) ? 4 : 1)
+void k_backward(VolArgs v, PhysArgs p, FanTable tab,
                                                  const float *__restrict__ poses,
                                                  RayRec *__restrict__ rays_out,
                                                  const float *__restrict__ gsrc,
@@ -1008,33 +1108,44 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
                                                  double *__restrict__ loss_acc,
                                                  const double *__restrict__ zcar,
                                                  const float *states,
+                                                 const RayGeom *__restrict__ geom,
                                                  const float *__restrict__ gain_in, int xgrp)
 {
     constexpr int T = 64 * C;
+    constexpr int NW = adjoint_waves(W);
+    constexpr bool WHOLE = FROM == kWholeRay;
     static_assert(C % kStateStride == 0, "a chunk starts on a recorded state");
-    __shared__ __align__(16) float s_g_w[W][3 * T];     // dZ/dp of every sample of the tile, in the ray's basis
-    __shared__ double s_z_w[W][SampleTile<T>::size];
-    __shared__ float s_xir_w[W][SPK ? T / 4 + 8 : 1];
+    __shared__ __align__(16) float s_g_w[NW][3 * T];     // dZ/dp of every sample of the tile, in the ray's basis
+    __shared__ double s_z_w[NW][SampleTile<T>::size];
+    __shared__ float s_xir_w[NW][SPK ? T / 4 + 8 : 1];
     __shared__ double s_tot[WHOLE ? W : 1][5];    // the tiles' scan totals
     __shared__ double s_l[W], s_o[W], s_q[W];     // a round's tiles: sums of L and O, first interface's dL/dZ factor
     __shared__ double s_red[W][7];                // per-wavefront pose sums and loss
 
-    const int lane = (W == 1) ? (int)threadIdx.x : (int)(threadIdx.x & 63);
-    const int wv = (W == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    float *s_g = s_g_w[wv];
-    double *s_z = s_z_w[wv];
-    float *s_xir = s_xir_w[wv];
+    const int lane = (int)(threadIdx.x & 63);
+    const int slot = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));     // wavefront of the block
+    const int wv = (W == 1) ? 0 : slot;                                             // wavefront of the ray
+    float *s_g = s_g_w[slot];
+    double *s_z = s_z_w[slot];
+    float *s_xir = s_xir_w[slot];
     int g = remap_block(blockIdx.x, gridDim.x, xgrp);
-    if (WHOLE) g += tab.ray0;
-    else if (W == 1 && g < tab.ray0) return;     // walked by several wavefronts in another launch
+    if (W == 1) {
+        g = g * kBlockRays + slot;
+        if (WHOLE) g += tab.ray0;
+        // (below ray0: walked by several wavefronts in another launch)
+        if (g < tab.ray0 || g >= (WHOLE ? tab.ray1 : tab.total_rays)) return;
+    } else if (WHOLE) {
+        g += tab.ray0;
+    }
     const int fi = find_fan(tab, g);
     const FanRec fr = tab.f[fi];
     const int j = g - fr.ray_begin;
     const int S = fr.n_samples;
     if (S <= 0) return;
     Ray ray;
-    setup_ray(v, p, fr, poses, j, ray);
-    if (rays_out && threadIdx.x == 0) {
+    if (FROM == kRecords) load_geom(fr, geom + g, ray);
+    else setup_ray(v, p, fr, poses, j, ray);
+    if (rays_out && lane == 0 && wv == 0) {
         // the ray's geometry for the scatter
         RayRec r;
 #pragma unroll
@@ -1053,7 +1164,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
     const int ntiles = (S + T - 1) / T;
     const double inv_npix = 1.0 / ((double)fr.n_rays * (double)S);
     const long long crec = (long long)fr.carry_begin + (long long)j * ((S + kCarryBlock - 1) / kCarryBlock);
-    const float *srow = WHOLE ? nullptr : states + (zcar ? crec * kStateFloats : obase - 4);
+    const float *srow = WHOLE ? nullptr : states + (FROM == kRecords ? crec * kStateFloats : obase - 4);
     const float *src = (FUSED ? target : gsrc) + obase;
 
     // the sums L and O over everything deeper than the (round's deepest)
@@ -1084,7 +1195,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
                 tt = st.y;
             }
             if (t0 > 0) {
-                if (zcar) {
+                if (FROM == kRecords) {
                     zm = zcar[crec + t0 / kCarryBlock];
                 } else {
                     const Stencil st = stencil_at<false>(v, ray, t0 - 1);
@@ -1092,17 +1203,28 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
                 }
             }
         }
+        // dL/de (or the target for the fused loss) and the recorded gains: on
+        // their way before the gather
+        float ebf[C], gn[C];
+        load_chunk<C>(src, k0, S, 0.0f, ebf);
+        if (FROM == kRecords) {
+            if (gain_in) {
+                load_chunk<C>(gain_in + obase, k0, S, 1.0f, gn);
+            } else {                              // the forward records them whenever there are any
+#pragma unroll
+                for (int i = 0; i < C; ++i) gn[i] = 1.0f;
+            }
+        }
+        // (the basis is needed here alone: loaded again per tile, it holds no
+        // scalar registers through the walks)
+        if (FROM == kRecords && pose_part) load_basis(geom + g, ray);
         if (pose_part) gather_tile<C, true, W>(v, ray, t0, S, lane, s_z, s_g);
         else gather_tile<C, false, W>(v, ray, t0, S, lane, s_z);
         if (SPK) speckle_radial<T>(p, t0, j, fr.speckle_id, lane, s_xir);
         __builtin_amdgcn_s_setprio(0);
-        __syncthreads();
+        ray_sync<W>();
 
-        // dL/de (or the target for the fused loss) and the per-pixel gains
-        float ebf[C], gn[C];
-        load_chunk<C>(src, k0, S, 0.0f, ebf);
-        if (gain_in) load_chunk<C>(gain_in + obase, k0, S, 1.0f, gn);
-        else chunk_gains<C, SPK>(p, gk, k0, t0, j, fr.speckle_id, postc, s_xir, gn);
+        if (FROM != kRecords) chunk_gains<C, SPK>(p, gk, k0, t0, j, fr.speckle_id, postc, s_xir, gn);
 
         // the chunk's samples, those on either side of it, and its interfaces
         double z[C], rho[C], dq[C];
@@ -1130,7 +1252,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
                     s_tot[wv][3] = Tot.d;
                     s_tot[wv][4] = td;
                 }
-                __syncthreads();
+                ray_sync<W>();
                 for (int u = rt; u > wv && u < W; --u)      // tiles 0 .. t - 1, at wavefronts rt .. wv + 1
                     carry_through(Mat{s_tot[u][0], s_tot[u][1], s_tot[u][2], s_tot[u][3]}, s_tot[u][4], c0, c1, cD);
             }
@@ -1140,28 +1262,40 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
             tt = cD * xd * iv * iv;
         }
 
-        // walk down the chunk: state, pixel and dl/de of every interface
-        double ws[C], ts[C], qs[C], eb[C], e[C];
+        // walk down the chunk: every interface's pixel e and be = e dl/de, and
+        // its dL/dZ factor qz (dl/dR times d rho / dZ's common factor) as
+        // cz - cl L - co O of the sums below it, so that the states themselves
+        // end here
+        double e[C], be[C], co[C], cl[C], qz[C];
         double lsum = 0.0;
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             const double r = rho[i];
-            const double q = rcp64(fma(w, r, 1.0));
+            const double pp = fma(w, r, 1.0);
+            const double q = rcp64(pp);
             const double r2 = r * r, om = 1.0 - r2;
-            ws[i] = w;
-            ts[i] = tt;
-            qs[i] = q;
-            e[i] = r * tt * q;
+            const double x = tt * q;
+            e[i] = r * x;
+            double eb;
             if (FUSED) {
                 const double diff = fma(e[i], (double)gn[i], -(double)ebf[i]);
                 loss += act ? diff * diff * inv_npix : 0.0;
-                eb[i] = 2.0 * diff * inv_npix * (double)gn[i];
+                eb = 2.0 * diff * inv_npix * (double)gn[i];
             } else {
-                eb[i] = (double)(ebf[i] * gn[i]);
+                eb = (double)(ebf[i] * gn[i]);
             }
-            lsum = fma(eb[i], e[i], lsum);
+            be[i] = eb * e[i];
+            lsum += be[i];
+            const double tom = tt * om;
+            // below 1e-150 O (about t^2 dl/de) over t is far under FP32's
+            // smallest number, and near t's own underflow it is 0 / 0
+            const double inv = (tom < 1e-150) ? 0.0 : rcp64(tom);
+            const double N = fma(onep * pp, pp, fma(w, w, -1.0));
+            co[i] = dq[i] * inv * N;
+            cl[i] = 2.0 * dq[i] * fma(r * tt, inv, w * q);
+            qz[i] = dq[i] * (eb * x * q);
             w = fma(w, a2 * (om - sgn * r2), -a2 * sgn * r) * q;
-            tt = a2 * om * tt * q * q;
+            tt = a2 * tom * q * q;
         }
         __builtin_amdgcn_s_setprio(1);
         // L at the chunk's end: the tiles and the chunks below
@@ -1173,7 +1307,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
                 l_in += tot;
             } else {
                 if (lane == 0) s_l[wv] = tot;
-                __syncthreads();
+                ray_sync<W>();
                 for (int u = 0; u < W; ++u) {
                     if (u == wv) l_tile = l_in;
                     if (rt - u < 0) break;
@@ -1188,7 +1322,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
             double l = l_end;
 #pragma unroll
             for (int i = C - 1; i >= 0; --i) {
-                const double up = fma(eb[i], e[i], l);
+                const double up = l + be[i];
                 osum = fma(e[i], l + up, osum);
                 l = up;
             }
@@ -1199,7 +1333,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
                 o_in -= tot;
             } else {
                 if (lane == 0) s_o[wv] = tot;
-                __syncthreads();
+                ray_sync<W>();
                 for (int u = 0; u < W; ++u) {
                     if (u == wv) o_tile = o_in;
                     if (rt - u < 0) break;
@@ -1210,22 +1344,11 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
         }
         __builtin_amdgcn_s_setprio(0);
 
-        // walk up: dl/dR of every interface times d rho / dZ's common factor
-        double qz[C];
+        // walk up: the interfaces' dL/dZ factors
 #pragma unroll
         for (int i = C - 1; i >= 0; --i) {
-            const double r = rho[i];
-            const double om = fma(-r, r, 1.0);
-            const double tom = ts[i] * om;
-            // where t itself has underflowed, O (about t^2) has long before
-            const double inv = (tom < 1e-290) ? 0.0 : rcp64(tom);
-            const double pp = fma(ws[i], r, 1.0);
-            const double N = fma(onep * pp, pp, fma(ws[i], ws[i], -1.0));
-            const double x = ts[i] * qs[i];
-            const double rl = fma(r * ts[i], inv, ws[i] * qs[i]);
-            const double rb = fma(eb[i] * x, qs[i], fma(-2.0 * l_end, rl, -(o_end * inv) * N));
-            qz[i] = rb * dq[i];
-            const double up = fma(eb[i], e[i], l_end);
+            qz[i] = fma(-co[i], o_end, fma(-cl[i], l_end, qz[i]));
+            const double up = l_end + be[i];
             o_end = fma(-e[i], l_end + up, o_end);
             l_end = up;
         }
@@ -1236,10 +1359,15 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
         double qn = qz_in;
         if (W > 1) {
             if (lane == 63) s_q[wv] = qz[0];
-            __syncthreads();
+            ray_sync<W>();
             if (wv > 0) qn = s_q[wv - 1];
         }
         qn = lane_next<false>(qz[0], qn);
+        // (the samples are read again, rather than held through the sums)
+        int zat = zi(base);
+        asm volatile("" : "+v"(zat));
+#pragma unroll
+        for (int i = 0; i < C; ++i) z[i] = s_z[zat + i];
         double zb[C];
 #pragma unroll
         for (int i = 0; i < C; ++i)
@@ -1261,9 +1389,10 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
         }
         if (pose_part && act) {
             // dL/dp = zb dZ/dp; dL/dR accumulates (s_k dir) outer dL/dp
+            const double s0 = fma((double)k0, ray.ds, ray.r0);
             double sz[C];
 #pragma unroll
-            for (int i = 0; i < C; ++i) sz[i] = fma((double)(k0 + i), ray.ds, ray.r0) * zb[i];
+            for (int i = 0; i < C; ++i) sz[i] = fma((double)i, ray.ds, s0) * zb[i];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
 #pragma unroll
@@ -1289,7 +1418,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
             qz_in = s_q[W - 1];
             z_in = s_z_w[W - 1][zi(0)];
         }
-        __syncthreads();
+        ray_sync<W>();
     }
     double r[6];
     if (pose_part) {
@@ -1308,7 +1437,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
             for (int a = 0; a < 6; ++a) s_red[wv][a] = pose_part ? r[a] : 0.0;
             s_red[wv][6] = ls;
         }
-        __syncthreads();
+        ray_sync<W>();
         if (wv == 0) {
             for (int u = 1; u < W; ++u) {
 #pragma unroll
@@ -1318,7 +1447,8 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
         }
     }
     if (pose_part) {
-        if (threadIdx.x == 0) {
+        if (FROM == kRecords) load_basis(geom + g, ray);
+        if (lane == 0 && wv == 0) {
             // this ray's share of dL/dt = sum g and dL/dR = sum g (s dir)^T,
             // dir = (sx, 0, cz), with g back from the ray's basis to the world
             // frame; k_pose_reduce sums the rays of each pose (in a fixed
@@ -1326,8 +1456,9 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
             double *pr = pose_part + (size_t)kRayPart * g;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const double gt = fma(r[0], ray.bd[a], fma(r[1], ray.bt[a], r[2] * ray.bn[a]));
-                const double gs = fma(r[3], ray.bd[a], fma(r[4], ray.bt[a], r[5] * ray.bn[a]));
+                const double h = v.h[a];      // out of the basis again
+                const double gt = h * fma(r[0], ray.bd[a], fma(r[1], ray.bt[a], r[2] * ray.bn[a]));
+                const double gs = h * fma(r[3], ray.bd[a], fma(r[4], ray.bt[a], r[5] * ray.bn[a]));
                 pr[a] = gt;
                 pr[3 + 2 * a] = gs * ray.dirx;
                 pr[4 + 2 * a] = gs * ray.dirz;
@@ -1336,7 +1467,7 @@ __global__ __launch_bounds__(64 * W) void k_backward(VolArgs v, PhysArgs p, FanT
     }
     if (FUSED && loss_acc) {
         // one partial per ray, summed by k_sum_f64 (no contended atomics)
-        if (threadIdx.x == 0) loss_acc[g] = ls;
+        if (lane == 0 && wv == 0) loss_acc[g] = ls;
     }
 }
 
@@ -2417,6 +2548,11 @@ inline int span_rays(const FanTable &t, int span_samples)
     return n;
 }
 
+// adjoint blocks for n rays of w wavefronts each, and how many consecutive
+// blocks keep `rays` consecutive rays on one XCD
+inline int ray_blocks(int w, int n) { return w == 1 ? (n + kBlockRays - 1) / kBlockRays : n; }
+inline int block_group(int w, int rays) { return w == 1 ? std::max(rays / kBlockRays, 1) : rays; }
+
 // the side stream starts after what st has queued; st waits for it at the
 // join (graph capture turns both into graph edges)
 inline hipError_t fork_side(hipStream_t st, const SideStream &s)
@@ -2438,9 +2574,16 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
 // --------------------------------------------------------------------------
 // launch wrappers
 // --------------------------------------------------------------------------
-#define DUS_FWD_LAUNCH(CH, SPK, WV, NG, TAB, ZERO, STR)                                         \
-    hipLaunchKernelGGL((k_forward<CH, SPK, WV>), dim3(NG), dim3(64 * WV), 0, STR, v, p, TAB, poses, out, \
+// the instance that also reports the smallest pivots is one of its own (the
+// others carry no test for it)
+#define DUS_FWD_LAUNCH_(CH, SPK, WV, PIV, NG, TAB, ZERO, STR)                                   \
+    hipLaunchKernelGGL((k_forward<CH, SPK, WV, PIV>), dim3(NG), dim3(64 * WV), 0, STR, v, p, TAB, poses, out, \
                        min_pivot, pivot_base, zcar, reinterpret_cast<float *>(states), gain, xcd_group, ZERO)
+#define DUS_FWD_LAUNCH(CH, SPK, WV, NG, TAB, ZERO, STR)                                         \
+    do {                                                                                        \
+        if (min_pivot) DUS_FWD_LAUNCH_(CH, SPK, WV, true, NG, TAB, ZERO, STR);                   \
+        else DUS_FWD_LAUNCH_(CH, SPK, WV, false, NG, TAB, ZERO, STR);                            \
+    } while (0)
 
 #define DUS_FWD_CASE(CH)                                                                       \
     case CH:                                                                                   \
@@ -2509,24 +2652,26 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
     return e;
 }
 
-#define DUS_BWD_LAUNCH(CH, SPK, FUSED, WV, WHOLE, NG, TAB, STR)                                    \
-    hipLaunchKernelGGL((k_backward<CH, SPK, FUSED, WV, WHOLE>), dim3(NG), dim3(64 * WV), 0, STR, v, p, TAB, \
-                       poses, zbar ? rays : nullptr, gsrc, target, zbar, pose_acc ? pose_part : nullptr, \
-                       loss, zcar, reinterpret_cast<const float *>(states), gain, xcd_group)
+#define DUS_BWD_LAUNCH(CH, SPK, FUSED, WV, FROM, NG, TAB, STR)                                    \
+    hipLaunchKernelGGL((k_backward<CH, SPK, FUSED, WV, FROM>), dim3(ray_blocks(WV, NG)), dim3(64 * adjoint_waves(WV)), \
+                       0, STR, v, p, TAB, poses, zbar ? rays : nullptr, gsrc, target, zbar, pose_acc ? pose_part : nullptr, \
+                       loss, zcar, reinterpret_cast<const float *>(states), t.geom, gain, block_group(WV, xcd_group))
 
 // from the forward's records: the long rays (the table's first n_span) take
 // kSpanWaves * 4 / C wavefronts each (the registers of C = 8 allow half as many)
 #define DUS_BWD_CASE(CH)                                                                       \
     case CH:                                                                                   \
         if (n_span > 0) {                                                                      \
-            if (fused) DUS_BWD_LAUNCH(CH, false, true, kSpanWaves * 4 / CH, false, n_span, t, sst);  \
-            else if (spk) DUS_BWD_LAUNCH(CH, true, false, kSpanWaves * 4 / CH, false, n_span, t, sst); \
-            else DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, false, n_span, t, sst);       \
+            if (fused) DUS_BWD_LAUNCH(CH, false, true, kSpanWaves * 4 / CH, kRecords, n_span, t, sst);  \
+            else if (spk) DUS_BWD_LAUNCH(CH, true, false, kSpanWaves * 4 / CH, kRows, n_span, t, sst); \
+            else if (!zcar) DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, kRows, n_span, t, sst); \
+            else DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, kRecords, n_span, t, sst);       \
         }                                                                                      \
         if (n_one > 0) {                                                                       \
-            if (fused) DUS_BWD_LAUNCH(CH, false, true, 1, false, t.total_rays, t1, st);               \
-            else if (spk) DUS_BWD_LAUNCH(CH, true, false, 1, false, t.total_rays, t1, st);            \
-            else DUS_BWD_LAUNCH(CH, false, false, 1, false, t.total_rays, t1, st);                    \
+            if (fused) DUS_BWD_LAUNCH(CH, false, true, 1, kRecords, t.total_rays, t1, st);               \
+            else if (spk) DUS_BWD_LAUNCH(CH, true, false, 1, kRows, t.total_rays, t1, st);            \
+            else if (!zcar) DUS_BWD_LAUNCH(CH, false, false, 1, kRows, t.total_rays, t1, st); \
+            else DUS_BWD_LAUNCH(CH, false, false, 1, kRecords, t.total_rays, t1, st);                    \
         }                                                                                      \
         break;
 
@@ -2535,11 +2680,11 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
 #define DUS_WHOLE_CASE(WV)                                                                     \
     case WV:                                                                                   \
         if (fused) {                                                                           \
-            if (spk) DUS_BWD_LAUNCH(4, true, true, WV, true, n, t1, st);                              \
-            else DUS_BWD_LAUNCH(4, false, true, WV, true, n, t1, st);                                 \
+            if (spk) DUS_BWD_LAUNCH(4, true, true, WV, kWholeRay, n, t1, st);                              \
+            else DUS_BWD_LAUNCH(4, false, true, WV, kWholeRay, n, t1, st);                                 \
         } else {                                                                               \
-            if (spk) DUS_BWD_LAUNCH(4, true, false, WV, true, n, t1, st);                             \
-            else DUS_BWD_LAUNCH(4, false, false, WV, true, n, t1, st);                                \
+            if (spk) DUS_BWD_LAUNCH(4, true, false, WV, kWholeRay, n, t1, st);                             \
+            else DUS_BWD_LAUNCH(4, false, false, WV, kWholeRay, n, t1, st);                                \
         }                                                                                      \
         break;
 
@@ -2566,6 +2711,7 @@ hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const Phys
             t1.ray0 = t.f[f].ray_begin;
             for (; f < t.n && (w == 1 || 2 * t.f[f].n_samples > w * kCarryBlock); ++f) n += t.f[f].n_rays;
             if (n <= 0) continue;
+            t1.ray1 = t1.ray0 + n;
             switch (w) {
                 DUS_WHOLE_CASE(1)
                 DUS_WHOLE_CASE(2)
@@ -2575,7 +2721,8 @@ hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const Phys
         }
         return hipGetLastError();
     }
-    if (fused && spk) return hipErrorInvalidValue;    // the fused step records its gains
+    // the fused step records its gains and the rays' geometry
+    if ((fused && (spk || !zcar)) || (spk && zcar) || (zcar && !t.geom)) return hipErrorInvalidValue;
     // several wavefronts per long ray
     const int n_span = span_rays(t, span_samples);
     const int n_one = t.total_rays - n_span;
