@@ -1483,13 +1483,23 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
 // box of the volume (neighbouring rays of a fan overlap); the runs go into an
 // LDS copy of that box with LDS atomics, and the box is then flushed with one
 // global atomic per touched voxel, consecutive lanes on consecutive x.  A
-// group whose box does not fit falls back to per-sample global atomics.
+// group whose box does not fit takes its rays in halves (quarters, ...), and
+// a single ray whose box does not fit goes to per-sample global atomics.
 //
 // The box holds FP64: FP64 LDS atomics (ds_add_f64) run at the rate of
 // plain LDS stores on gfx950, FP32 LDS atomics several times slower.  The
 // FP64 sum of a voxel's FP32 contributions is rounded to FP32 once, when the
 // box is flushed.
 // --------------------------------------------------------------------------
+//
+// Bound by LDS instructions: every 64-bit LDS store or atomic of a wavefront
+// takes about 8 clocks of its CU however many lanes are active (measured), and
+// a group of 256 samples issues about 32 to accumulate and 16 to flush; and by
+// the global atomics where many rays meet (40 of the bench step's 131 us).
+// 64 poses x 256 rays x 1024 samples 139 -> 134 us with half the vector
+// instructions (cells stepped in fixed point, box by register reductions, a
+// flush that steps along one axis), 63 fans of 256 x 256 and one of 64 x 16384
+// 218 -> 101 us with boxes for parts of the rays.
 constexpr int kScatterSpl = 4;     // consecutive depths per lane, at most
 
 // floor(a / b) for a >= 0, b >= 1, a + b < 2^21, from rb = rcp(b) (within
@@ -1506,6 +1516,25 @@ struct ScatterBox {
     static constexpr int cap = RB == 2 ? 4096 : (RB == 4 ? 2048 : 1024);   // FP64 entries
 };
 
+// voxel coordinate in 32.32 fixed point (floor and fraction; rounded down)
+__device__ __forceinline__ long long to_fixed(double u)
+{
+    const unsigned lo = (unsigned)(__builtin_amdgcn_fract(u) * 0x1p32);
+    return (long long)(((unsigned long long)(unsigned)(int)floor(u) << 32) | lo);
+}
+
+// smallest value over the wavefront (every lane active), in a scalar register
+__device__ __forceinline__ int wave_min_int(int x)
+{
+    x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x111, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x112, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x114, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x118, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x142, 0xa, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
 template <int RB>
 __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const RayRec *__restrict__ rays,
                                                 const float *__restrict__ zbar, float *__restrict__ gZ,
@@ -1513,10 +1542,10 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
                                                 const double *__restrict__ fscale)
 {
     constexpr int LPR = 64 / RB;                 // lanes per ray
-    constexpr int CAP = ScatterBox<RB>::cap;
+    constexpr int CAP = ScatterBox<RB>::cap - 1;
     // s_box is all zeros between groups: cleared once here, and every flush
-    // clears the entries it reads
-    __shared__ double s_box[CAP];
+    // clears the entries it reads; the last entry, outside the box, stays zero
+    __shared__ double s_box[CAP + 1];
     const int lane = threadIdx.x;
     const int slot = lane / LPR, ll = lane % LPR;
     // depth chunk of this lane, rotated by the ray slot: in one instruction
@@ -1548,21 +1577,24 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
     const int sgi = two_d ? (int)blockIdx.y : (b - acc) / nrb;
     const int j = (b - acc - (two_d ? 0 : sgi * nrb)) * RB + slot;
     const bool ray_ok = j < fr.n_rays;
+    const int jr = min(j, fr.n_rays - 1);        // lanes past the fan repeat its last ray, with zeros
     const int S = fr.n_samples;
     const int k_begin = sgi * seg;
     if (k_begin >= S) return;                   // whole wavefront: past this fan's depth
     const int k_end = min(S, k_begin + seg);
     // RB rays per wavefront, their geometry as the adjoint set it up
     Ray ray;
+    long long step[3];
     {
-        const RayRec &r = rays[fr.ray_begin + (ray_ok ? j : 0)];
+        const RayRec &r = rays[fr.ray_begin + jr];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             ray.u0[a] = r.u0[a];
             ray.du[a] = r.du[a];
+            step[a] = to_fixed(r.du[a]);
         }
     }
-    const float *zrow = zbar + fr.out_offset + (long long)(ray_ok ? j : 0) * S;
+    const float *zrow = zbar + fr.out_offset + (long long)jr * S;
     const int sxy = v.nx * v.ny;
     // depths per lane (4, 2 or 1) from the step length in voxels, so that a
     // group spans about 11 voxels along the rays and its box fits LDS also
@@ -1578,193 +1610,207 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
     // deterministic mode: 64-bit fixed-point sums (integer adds, in any
     // order the same) with the step's scale instead of FP32 atomics
     const double fsc = fix ? fscale[0] : 0.0;
-    for (int t = lane; t < CAP; t += 64) s_box[t] = 0.0;
-    // dL/dZ of the next group is loaded one group ahead; the lane's depths
-    // past spl stay zero (inactive).  The loads are clamped into the row and
-    // masked afterwards (no branch per load; spl is uniform).
-    float zn[kScatterSpl];
+    for (int t = lane; t <= CAP; t += 64) s_box[t] = 0.0;
+    // dL/dZ of the lane's depths from k on, zero past the segment and for
+    // lanes past the fan (the depths past spl stay zero)
+    auto load = [&](int k, float (&x)[kScatterSpl]) {
+        if (spl == kScatterSpl && k + kScatterSpl <= S) {
+            const float4_u q = *reinterpret_cast<const float4_u *>(zrow + k);
+            x[0] = q.x;
+            x[1] = q.y;
+            x[2] = q.z;
+            x[3] = q.w;
+        } else {
 #pragma unroll
-    for (int q = 0; q < kScatterSpl; ++q) {
-        const int k = k_begin + ch * spl + q;
-        const float x = (q < spl) ? zrow[min(k, S - 1)] : 0.0f;
-        zn[q] = (ray_ok && k < k_end) ? x : 0.0f;
-    }
+            for (int q = 0; q < kScatterSpl; ++q) x[q] = (q < spl) ? zrow[min(k + q, S - 1)] : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < kScatterSpl; ++q) x[q] = (ray_ok && q < spl && k + q < k_end) ? x[q] : 0.0f;
+    };
+    // loaded one group ahead
+    float zn[kScatterSpl];
+    load(k_begin + ch * spl, zn);
     for (int k0 = k_begin; k0 < k_end; k0 += G) {
-        // the segment's last group loads nothing ahead (the next segment
-        // belongs to another wavefront)
-        const bool ahead = k0 + G < k_end;
+        const int kl = k0 + ch * spl;            // the lane's first depth
         float zb[kScatterSpl];
 #pragma unroll
-        for (int q = 0; q < kScatterSpl; ++q) {
-            zb[q] = zn[q];
-            const int k = k0 + G + ch * spl + q;
-            const float x = (ahead && q < spl) ? zrow[min(k, S - 1)] : 0.0f;
-            zn[q] = (ray_ok && k < k_end) ? x : 0.0f;
-        }
-        Stencil st[kScatterSpl];
-        int qf = -1, ql = -1;
+        for (int q = 0; q < kScatterSpl; ++q) zb[q] = zn[q];
+        // the segment's last group loads nothing ahead (the next segment
+        // belongs to another wavefront)
+        if (k0 + G < k_end) load(kl + G, zn);
+        if (__ballot(zb[0] != 0.0f || zb[1] != 0.0f || zb[2] != 0.0f || zb[3] != 0.0f) == 0ull)
+            continue;                            // nothing to scatter in this group (uniform)
+        // Cells and weights of the lane's depths.  Inside the volume (every
+        // lane's first and last depth: the position is affine) they step in
+        // 32.32 fixed point from the first depth's FP64 position: the cell is
+        // the high word, the fraction (within 2^-30 of FP64's, and FP32 as a
+        // weight) the low word.  Lanes past the segment repeat its last depth.
+        int ci[kScatterSpl][3];
+        float wf[kScatterSpl][3];
+        {
+            const double kk = (double)min(kl, k_end - 1);
+            const int last = min(spl - 1, max(k_end - 1 - kl, 0));
+            const int n[3] = {v.nx, v.ny, v.nz};
+            bool in = true;
 #pragma unroll
-        for (int q = 0; q < kScatterSpl; ++q) {
-            st[q] = Stencil{0, 0, 0, 0, 0.0, 0.0, 0.0};
-            if (zb[q] != 0.0f) {
-                st[q] = stencil_at(v, ray, k0 + ch * spl + q);
-                if (qf < 0) qf = q;
-                ql = q;
+            for (int a = 0; a < 3; ++a) {
+                long long u = to_fixed(fma(kk, ray.du[a], ray.u0[a]));
+                const unsigned top = (unsigned)(n[a] - 1);
+                in = in && (unsigned)(int)(u >> 32) < top;
+#pragma unroll
+                for (int q = 0; q < kScatterSpl; ++q) {
+                    ci[q][a] = (int)(u >> 32);
+                    wf[q][a] = (float)(unsigned)(u & 0xffffffffll) * 0x1p-32f;
+                    if (q < last) u += step[a];
+                }
+                in = in && (unsigned)(int)(u >> 32) < top;
             }
-        }
-        // bounding box of the group's cells: cell coordinates are monotone
-        // along a straight ray, so per ray the extremes sit at its first and
-        // last active sample (first and last active chunk)
-        int fx = 0, fy = 0, fz = 0, lx = 0, ly = 0, lz = 0;
+            if (__ballot(!in) != 0ull) {         // uniform: clamped, in FP64
 #pragma unroll
-        for (int q = 0; q < kScatterSpl; ++q) {
-            if (q == qf) { fx = st[q].ix; fy = st[q].iy; fz = st[q].iz; }
-            if (q == ql) { lx = st[q].ix; ly = st[q].iy; lz = st[q].iz; }
-        }
-        const unsigned long long am = __ballot(qf >= 0);
-        if (am == 0ull) continue;  // nothing to scatter in this group (uniform)
-        int ox = 0x3fffffff, oy = 0x3fffffff, oz = 0x3fffffff, ex = -1, ey = -1, ez = -1;
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            constexpr unsigned long long msk = (1ull << LPR) - 1;
-            const unsigned long long m = (am >> (r * LPR)) & msk;
-            if (m == 0ull) continue;
-            // bit ll -> bit (ll + r SH) mod LPR: the ray's active chunks in order
-            const int sh = r * SH;
-            const unsigned long long mc = ((m << sh) | (m >> (LPR - sh))) & msk;
-            const int c0 = __builtin_ctzll(mc), c1 = 63 - __builtin_clzll(mc);
-            const int l0 = r * LPR + (c0 - sh + LPR) % LPR, l1 = r * LPR + (c1 - sh + LPR) % LPR;
-            const int ax = __builtin_amdgcn_readlane(fx, l0), bxv = __builtin_amdgcn_readlane(lx, l1);
-            const int ay = __builtin_amdgcn_readlane(fy, l0), byv = __builtin_amdgcn_readlane(ly, l1);
-            const int az = __builtin_amdgcn_readlane(fz, l0), bzv = __builtin_amdgcn_readlane(lz, l1);
-            ox = min(ox, min(ax, bxv)); ex = max(ex, max(ax, bxv));
-            oy = min(oy, min(ay, byv)); ey = max(ey, max(ay, byv));
-            oz = min(oz, min(az, bzv)); ez = max(ez, max(az, bzv));
-        }
-        const int bx = ex - ox + 2, by = ey - oy + 2, bz = ez - oz + 2;
-        // odd row and plane strides: neighbouring cells along any axis land
-        // in different LDS banks
-        const int rs = bx | 1;
-        const int ps = (rs * by) | 1;
-        const bool fits = bx <= 64 && (long long)ps * bz <= CAP;
-        if (!fits) {
-#pragma unroll
-            for (int q = 0; q < kScatterSpl; ++q) {
-                if (zb[q] == 0.0f) continue;
-                const float wx = (float)st[q].fx, wy = (float)st[q].fy, wz = (float)st[q].fz;
-                const float gx = 1.0f - wx, gy = 1.0f - wy, gz = 1.0f - wz;
-                const float w8[8] = {zb[q] * gx * gy * gz, zb[q] * wx * gy * gz, zb[q] * gx * wy * gz,
-                                     zb[q] * wx * wy * gz, zb[q] * gx * gy * wz, zb[q] * wx * gy * wz,
-                                     zb[q] * gx * wy * wz, zb[q] * wx * wy * wz};
-                const int off[8] = {0, 1, v.nx, v.nx + 1, sxy, sxy + 1, sxy + v.nx, sxy + v.nx + 1};
-                if (fix) {
-#pragma unroll
-                    for (int c = 0; c < 8; ++c)
-                        if (w8[c] != 0.0f)
-                            atomicAdd(fix + st[q].idx + off[c], (unsigned long long)__double2ll_rn((double)w8[c] * fsc));
-                } else {
-                    float *dst = gZ + st[q].idx;
-#pragma unroll
-                    for (int c = 0; c < 8; ++c)
-                        if (w8[c] != 0.0f) atomicAdd(dst + off[c], w8[c]);
+                for (int q = 0; q < kScatterSpl; ++q) {
+                    const Stencil st = stencil_at(v, ray, min(kl + min(q, last), k_end - 1));
+                    ci[q][0] = st.ix;
+                    ci[q][1] = st.iy;
+                    ci[q][2] = st.iz;
+                    wf[q][0] = (float)st.fx;
+                    wf[q][1] = (float)st.fy;
+                    wf[q][2] = (float)st.fz;
                 }
             }
-            continue;
         }
-        // runs of a lane summed in registers, one LDS atomic per corner and run
-        {
-            const int off[8] = {0, 1, rs, rs + 1, ps, ps + 1, ps + rs, ps + rs + 1};
-            float ra[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            int cur = -1;
+        // A box for all the rays at once, or for halves, quarters, ... of them
+        // where that box would not fit (rays of a coarse fan lie far apart)
+        int part = RB;
+        for (int s0 = 0; s0 < RB;) {
+            const bool mine = (unsigned)(slot - s0) < (unsigned)part;
+            // (opaque, or the weights' products would be held across the loop)
 #pragma unroll
-            for (int q = 0; q < kScatterSpl; ++q) {
-                if (zb[q] == 0.0f) continue;
-                // box offsets and strides stay far below 2^24: 24-bit multiplies
-                const int l = (int)(__umul24((unsigned)(st[q].iz - oz), (unsigned)ps) +
-                                    __umul24((unsigned)(st[q].iy - oy), (unsigned)rs)) + (st[q].ix - ox);
-                if (l != cur && cur >= 0) {
+            for (int q = 0; q < kScatterSpl; ++q)
+                asm volatile("" : "+v"(zb[q]), "+v"(wf[q][0]), "+v"(wf[q][1]), "+v"(wf[q][2]));
+            // bounding box of the rays' cells: monotone along a straight ray, so
+            // the lane's first and last depth hold its extremes
+            int lo[3], hi[3];
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        if (ra[c] != 0.0f)
+            for (int a = 0; a < 3; ++a) {
+                const int c0 = ci[0][a], c1 = ci[kScatterSpl - 1][a];
+                lo[a] = wave_min_int(mine ? min(c0, c1) : 0x7fffffff);
+                hi[a] = -wave_min_int(mine ? -max(c0, c1) : 0x7fffffff);
+            }
+            const int ox = lo[0], oy = lo[1], oz = lo[2];
+            const int bx = hi[0] - ox + 2, by = hi[1] - oy + 2, bz = hi[2] - oz + 2;
+            // odd row and plane strides: neighbouring cells along any axis land
+            // in different LDS banks
+            const int rs = bx | 1;
+            const int ps = (rs * by) | 1;
+            const bool fits = bx <= 64 && by <= CAP && (long long)ps * bz <= CAP;
+            if (!fits && part > 1) {
+                part >>= 1;
+                continue;
+            }
+            s0 += part;
+            if (!fits) {
+#pragma unroll
+                for (int q = 0; q < kScatterSpl; ++q) {
+                    if (!mine || zb[q] == 0.0f) continue;
+                    const long long at = (long long)ci[q][2] * sxy + (long long)ci[q][1] * v.nx + ci[q][0];
+#pragma unroll 1
+                    for (int c = 0; c < 8; ++c) {       // (rare: kept small in registers)
+                        const float x = (c & 1) ? wf[q][0] : 1.0f - wf[q][0];
+                        const float y = (c & 2) ? wf[q][1] : 1.0f - wf[q][1];
+                        const float w = zb[q] * x * y * ((c & 4) ? wf[q][2] : 1.0f - wf[q][2]);
+                        const long long to = at + (c & 1) + ((c & 2) ? v.nx : 0) + ((c & 4) ? sxy : 0);
+                        if (w == 0.0f) continue;
+                        if (fix) atomicAdd(fix + to, (unsigned long long)__double2ll_rn((double)w * fsc));
+                        else atomicAdd(gZ + to, w);
+                    }
+                }
+                continue;
+            }
+            // runs of a lane summed in registers, one LDS atomic per corner and run
+            if (mine) {
+                const int off[8] = {0, 1, rs, rs + 1, ps, ps + 1, ps + rs, ps + rs + 1};
+                // box index of a cell from its volume coordinates (24-bit
+                // products; the constant wraps)
+                const unsigned org = (unsigned)oz * (unsigned)ps + (unsigned)oy * (unsigned)rs + (unsigned)ox;
+                float ra[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+                int cur = 0;
+#pragma unroll
+                for (int q = 0; q < kScatterSpl; ++q) {
+                    const int l = (int)(__umul24((unsigned)ci[q][2], (unsigned)ps) +
+                                        __umul24((unsigned)ci[q][1], (unsigned)rs) + (unsigned)ci[q][0] - org);
+                    if (q > 0 && l != cur) {
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) {
                             atomicAdd(&s_box[cur + off[c]], (double)ra[c]);
-                        ra[c] = 0.0f;
-                    }
-                }
-                cur = l;
-                const float wx = (float)st[q].fx, wy = (float)st[q].fy, wz = (float)st[q].fz;
-                const float gx = 1.0f - wx, gy = 1.0f - wy, gz = 1.0f - wz;
-                ra[0] += zb[q] * gx * gy * gz;
-                ra[1] += zb[q] * wx * gy * gz;
-                ra[2] += zb[q] * gx * wy * gz;
-                ra[3] += zb[q] * wx * wy * gz;
-                ra[4] += zb[q] * gx * gy * wz;
-                ra[5] += zb[q] * wx * gy * wz;
-                ra[6] += zb[q] * gx * wy * wz;
-                ra[7] += zb[q] * wx * wy * wz;
-            }
-            if (cur >= 0) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c)
-                    if (ra[c] != 0.0f)
-                        atomicAdd(&s_box[cur + off[c]], (double)ra[c]);
-            }
-        }
-        __syncthreads();
-        // wave priority 1 for the flush (LDS reads and the global atomics wait
-        // on latency): in the two-chain step it then runs ahead of the other
-        // chain's arithmetic on the same CUs (step 0.5% faster)
-        __builtin_amdgcn_s_setprio(1);
-        // flush: the box's entries in x-fastest order, 64 consecutive entries
-        // per pass (consecutive lanes on consecutive x of a row); a lane's
-        // (x, y, z) advances by constant carries, and four entries' LDS reads
-        // are issued before their atomics
-        {
-            const int E = bx * by * bz;
-            // lane -> (x, y, z) and the step of 64 entries, with bx <= 64
-            // and the box within CAP entries
-            const float rbx = __builtin_amdgcn_rcpf((float)bx), rby = __builtin_amdgcn_rcpf((float)by);
-            const int dyz = small_quot(64, rbx), dz = small_quot(dyz, rby);
-            const int dx = 64 - (int)__umul24((unsigned)dyz, (unsigned)bx);
-            const int dy = dyz - (int)__umul24((unsigned)dz, (unsigned)by);
-            const int yz = small_quot(lane, rbx);
-            int z = small_quot(yz, rby);
-            int x = lane - (int)__umul24((unsigned)yz, (unsigned)bx);
-            int y = yz - (int)__umul24((unsigned)z, (unsigned)by);
-            for (int e0 = 0; e0 < E; e0 += 256) {
-                double val[4];
-                int at[4], gi[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    val[u] = 0.0;
-                    at[u] = gi[u] = 0;
-                    if (e0 + 64 * u + lane < E) {
-                        at[u] = (int)(__umul24((unsigned)z, (unsigned)ps) + __umul24((unsigned)y, (unsigned)rs)) + x;
-                        gi[u] = (int)(__umul24((unsigned)(oz + z), (unsigned)sxy) +
-                                      __umul24((unsigned)(oy + y), (unsigned)v.nx)) + (ox + x);
-                        val[u] = s_box[at[u]];
-                    }
-                    x += dx;
-                    y += dy;
-                    z += dz;
-                    if (x >= bx) { x -= bx; ++y; }
-                    if (y >= by) { y -= by; ++z; }
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (val[u] != 0.0) {
-                        s_box[at[u]] = 0.0;
-                        if (fix) {
-                            atomicAdd(fix + gi[u], (unsigned long long)__double2ll_rn(val[u] * fsc));
-                        } else {
-                            const float xv = (float)val[u];
-                            if (xv != 0.0f) atomicAdd(gZ + gi[u], xv);
+                            ra[c] = 0.0f;
                         }
                     }
+                    cur = l;
+                    const float wx = wf[q][0], wy = wf[q][1], wz = wf[q][2];
+                    const float gy = 1.0f - wy, gz = 1.0f - wz;
+                    const float x1 = zb[q] * wx, x0 = zb[q] * (1.0f - wx);
+                    const float x0y0 = x0 * gy, x1y0 = x1 * gy, x0y1 = x0 * wy, x1y1 = x1 * wy;
+                    ra[0] = fmaf(x0y0, gz, ra[0]);
+                    ra[1] = fmaf(x1y0, gz, ra[1]);
+                    ra[2] = fmaf(x0y1, gz, ra[2]);
+                    ra[3] = fmaf(x1y1, gz, ra[3]);
+                    ra[4] = fmaf(x0y0, wz, ra[4]);
+                    ra[5] = fmaf(x1y0, wz, ra[5]);
+                    ra[6] = fmaf(x0y1, wz, ra[6]);
+                    ra[7] = fmaf(x1y1, wz, ra[7]);
+                }
+#pragma unroll
+                for (int c = 0; c < 8; ++c) atomicAdd(&s_box[cur + off[c]], (double)ra[c]);
+            }
+            wave_sync();
+            // wave priority 1 for the flush (LDS reads and the global atomics wait
+            // on latency): in the two-chain step it then runs ahead of the other
+            // chain's arithmetic on the same CUs (step 0.5% faster)
+            __builtin_amdgcn_s_setprio(1);
+            // Flush: the lanes cover the (x, y) plane of the box, x fastest
+            // (consecutive lanes on consecutive voxels of a row), and step along
+            // z with one add per entry; or (x, z) planes along y, whichever fills
+            // the lanes better.  Four entries' LDS reads go out before their
+            // atomics; lanes past the plane read the entry that stays zero.
+            {
+                const bool xy = ((bx * by + 63) >> 6) * bz <= ((bx * bz + 63) >> 6) * by;
+                const int b2 = xy ? by : bz, b3 = xy ? bz : by;
+                const int s2 = xy ? rs : ps, s3 = xy ? ps : rs;
+                // (voxel indices fit 31 bits)
+                const unsigned g2 = xy ? v.nx : sxy, g3 = xy ? sxy : v.nx;
+                const unsigned org = (unsigned)oz * sxy + (unsigned)oy * v.nx + ox;
+                const float rbx = __builtin_amdgcn_rcpf((float)bx);
+                for (int e0 = 0; e0 < bx * b2; e0 += 64) {
+                    const int e = e0 + lane;
+                    const int y = small_quot(e, rbx), x = e - y * bx;
+                    const bool ok = y < b2;
+                    int at = ok ? x + y * s2 : CAP;
+                    const int sa = ok ? s3 : 0;
+                    unsigned gi = org + x + (ok ? y * g2 : 0);
+                    for (int z = 0; z < b3; z += 4) {
+                        double val[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) val[u] = (z + u < b3) ? s_box[at + u * sa] : 0.0;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            if (val[u] != 0.0) {
+                                s_box[at + u * sa] = 0.0;
+                                if (fix) {
+                                    atomicAdd(fix + gi + u * g3, (unsigned long long)__double2ll_rn(val[u] * fsc));
+                                } else {
+                                    const float xv = (float)val[u];
+                                    if (xv != 0.0f) atomicAdd(gZ + gi + u * g3, xv);
+                                }
+                            }
+                        }
+                        at += 4 * sa;
+                        gi += 4 * g3;
+                    }
                 }
             }
+            __builtin_amdgcn_s_setprio(0);
+            wave_sync();
         }
-        __builtin_amdgcn_s_setprio(0);
-        __syncthreads();
     }
 }
 
