@@ -211,6 +211,7 @@ struct LutArgs {
     int n;                      // knots, 2..kMaxKnots, x strictly increasing
     float x[kMaxKnots];
     float z[kMaxKnots];
+    float x0, xn;               // its ends (set by the launchers)
 };
 hipError_t launch_map(const float *in, int64_t n, const LutArgs &lut, float *Z, hipStream_t st);
 // grad_in (nullable): overwritten; grad_z (nullable): += per knot (FP64)

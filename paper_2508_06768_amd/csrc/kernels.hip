@@ -2430,118 +2430,165 @@ __global__ __launch_bounds__(256) void k_adam(float *__restrict__ x, const float
 // impedance voxel by voxel.  Here the map is a piecewise-linear table
 // (x_j, z_j), constant beyond its ends; a voxel of intensity v in
 // [x_j, x_{j+1}) maps to z_j + t (z_{j+1} - z_j), t = (v - x_j) / (x_{j+1} - x_j).
+//
+// Both directions are bound by memory.  A thread takes four neighbouring
+// voxels (16-byte accesses), and the next four's loads go out before this
+// four's arithmetic.  A table of up to kScanKnots knots is searched by
+// counting the knots below v, in scalar registers (two vector instructions a
+// knot, no LDS round trip); a longer one by halving in LDS.  256^3 voxels, 12
+// knots: the map 40 -> 26 us (134 MB at 5.1 TB/s, the rate of a large copy),
+// its adjoint 86 -> 47 us (201 MB; 42 us without the table gradient); 40
+// knots: 46 -> 41 and 119 -> 64 us.
 // --------------------------------------------------------------------------
-// segment j of v (x_j <= v < x_{j+1}, 0 <= j <= n - 2) for x_0 < v < x_{n-1}:
-// branch-free search in LDS, one halving step per bit of n - 2 (top: the
-// largest power of two <= n - 2, or 0 when n = 2)
-__device__ __forceinline__ int lut_segment(const float *sx, int top, int n, float v)
+constexpr int kScanKnots = 16;
+
+// a segment's values, read with one LDS access
+struct alignas(16) LutSeg {
+    float x, dx, z, dz;
+};
+
+// segment j of v (x_j <= v < x_{j+1}, 0 <= j <= n - 2) for x_0 < v < x_{n-1};
+// else some segment (0 for NaN).  top: the largest power of two <= n - 2, or
+// 0 when n = 2.
+template <bool SCAN>
+__device__ __forceinline__ int lut_segment(const LutArgs &lut, const float *sx, int top, float v)
 {
     int j = 0;
+    if (SCAN) {
+        // (lut.x beyond the table's inner knots holds +inf, which no v below
+        // x_{n-1} reaches)
+#pragma unroll
+        for (int k = 1; k < kScanKnots - 1; ++k) j += (v >= lut.x[k]) ? 1 : 0;
+        return min(j, lut.n - 2);
+    }
+    // branch-free search in LDS, one halving step per bit of n - 2
     for (int s = top; s > 0; s >>= 1) {
         const int c = j + s;
-        j = (c <= n - 2 && v >= sx[c]) ? c : j;
+        j = (c <= lut.n - 2 && v >= sx[c]) ? c : j;      // (c <= 2 top - 1 < kMaxKnots)
     }
     return j;
 }
 
 __device__ __forceinline__ int lut_top(int n) { return n > 2 ? 1 << (31 - __builtin_clz(n - 2)) : 0; }
 
-__device__ __forceinline__ float lut_eval(const float *sx, const float *sz, int top, int n, float v)
+__device__ __forceinline__ float lut_fraction(float v, const LutSeg &s) { return __fdiv_rn(v - s.x, s.dx); }
+
+// the table in LDS: segments, and for the halving search the knots packed
+// (their banks differ)
+__device__ __forceinline__ void lut_fill(const LutArgs &lut, LutSeg *seg, float *sx)
 {
-    if (v <= sx[0]) return sz[0];
-    if (v >= sx[n - 1]) return sz[n - 1];
-    // NaN fails both tests above and stays NaN here
-    const int j = lut_segment(sx, top, n, v);
-    const float t = __fdiv_rn(v - sx[j], sx[j + 1] - sx[j]);
-    return fmaf(t, sz[j + 1] - sz[j], sz[j]);
+    const int i = threadIdx.x;
+    if (i < lut.n - 1) seg[i] = LutSeg{lut.x[i], lut.x[i + 1] - lut.x[i], lut.z[i], lut.z[i + 1] - lut.z[i]};
+    if (i < kMaxKnots) sx[i] = lut.x[i];
+    __syncthreads();
 }
 
+// four voxels from i on, those past n zero (not stored)
+__device__ __forceinline__ float4_u load4(const float *__restrict__ p, long long i, long long n)
+{
+    if (i + 4 <= n) return *reinterpret_cast<const float4_u *>(p + i);
+    float4_u x = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int u = 0; u < 4; ++u)
+        if (i + u < n) x[u] = p[i + u];
+    return x;
+}
+
+__device__ __forceinline__ void store4(float *__restrict__ p, long long i, long long n, const float4_u &x)
+{
+    if (i + 4 <= n) {
+        __builtin_nontemporal_store(x, reinterpret_cast<float4_u *>(p + i));
+        return;
+    }
+    for (int u = 0; u < 4; ++u)
+        if (i + u < n) p[i + u] = x[u];
+}
+
+template <bool SCAN>
 __global__ __launch_bounds__(256) void k_map(const float *__restrict__ in, long long n, LutArgs lut,
                                              float *__restrict__ Z)
 {
-    __shared__ float s_x[kMaxKnots], s_z[kMaxKnots];
-    const int m = lut.n;
-    for (int i = threadIdx.x; i < m; i += 256) {
-        s_x[i] = lut.x[i];
-        s_z[i] = lut.z[i];
-    }
-    __syncthreads();
-    const int top = lut_top(m);
-    // four voxels per thread and pass, one grid stride apart: their loads
-    // and searches are independent
-    const long long stride = (long long)gridDim.x * 256;
-    for (long long i0 = (long long)blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += 4 * stride) {
-        float v[4];
+    __shared__ LutSeg s_seg[kMaxKnots];
+    __shared__ float s_x[kMaxKnots];
+    lut_fill(lut, s_seg, s_x);
+    const float x0 = lut.x0, xn = lut.xn, z0 = lut.z[0], zn = lut.z[lut.n - 1];
+    const int top = lut_top(lut.n);
+    const long long stride = (long long)gridDim.x * 1024;
+    long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= n) return;
+    float4_u v = load4(in, i, n);
+    for (; i < n; i += stride) {
+        const float4_u next = load4(in, i + stride, n);
+        float4_u z;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const long long i = i0 + u * stride;
-            v[u] = (i < n) ? in[i] : 0.0f;
+            const LutSeg s = s_seg[lut_segment<SCAN>(lut, s_x, top, v[u])];
+            const float inner = fmaf(lut_fraction(v[u], s), s.dz, s.z);
+            // NaN fails both tests and stays NaN
+            z[u] = (v[u] <= x0) ? z0 : ((v[u] >= xn) ? zn : inner);
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const long long i = i0 + u * stride;
-            const float z = lut_eval(s_x, s_z, top, m, v[u]);
-            if (i < n) Z[i] = z;
-        }
+        store4(Z, i, n, z);
+        v = next;
     }
 }
 
 // dL/dv = dL/dZ (z_{j+1} - z_j) / (x_{j+1} - x_j) inside the table (the right
 // segment at a knot), 0 beyond its ends; dL/dz_j += (1 - t) dL/dZ and
 // dL/dz_{j+1} += t dL/dZ, or all of dL/dZ to the end knot beyond an end.
-// The knot sums go through an FP64 LDS copy per block, then one global FP64
-// atomic per knot and block.
-// The table gradient is a histogram over the knots.  Its LDS accumulators
-// are replicated 8 times (lane % 8 picks the copy, rows padded to 65 so the
-// copies of one knot sit in different banks): lanes of one wavefront that
-// meet on a knot mostly add into different copies instead of serialising on
-// one address.
-constexpr int kMapCopies = 8, kMapRow = kMaxKnots + 1;
+// The table gradient is a histogram over the knots: FP64 LDS atomics, one
+// column per lane, so that lanes of a wavefront never meet on an address or
+// a bank whatever their knots (smooth volumes aim whole wavefronts at one
+// knot; with eight columns the atomics cost 28 of 77 us).  The columns are
+// added per block, then one global FP64 atomic per knot and block, all knots
+// in one instruction: every block's goes to the same few cache lines, about 8
+// ns apiece, so the blocks are few and large.
+constexpr int kMapThreads = 1024;
 
-__global__ __launch_bounds__(256) void k_map_backward(const float *__restrict__ in, long long n, LutArgs lut,
+template <bool SCAN>
+__global__ __launch_bounds__(kMapThreads) void k_map_backward(const float *__restrict__ in, long long n, LutArgs lut,
                                                       const float *__restrict__ gZ, float *__restrict__ grad_in,
                                                       double *__restrict__ grad_z)
 {
-    __shared__ float s_x[kMaxKnots], s_z[kMaxKnots];
-    __shared__ double s_g[kMapCopies * kMapRow];
+    __shared__ LutSeg s_seg[kMaxKnots];
+    __shared__ double s_g[SCAN ? kScanKnots : kMaxKnots][64];
+    __shared__ float s_x[kMaxKnots];
+    __shared__ double s_sum[kMaxKnots];
     const int m = lut.n;
-    for (int i = threadIdx.x; i < m; i += 256) {
-        s_x[i] = lut.x[i];
-        s_z[i] = lut.z[i];
-    }
-    for (int i = threadIdx.x; i < kMapCopies * kMapRow; i += 256) s_g[i] = 0.0;
-    __syncthreads();
-    double *g_own = s_g + (threadIdx.x % kMapCopies) * kMapRow;
-    const float x0 = s_x[0], xn = s_x[m - 1];
+    for (int i = threadIdx.x; i < m * 64; i += kMapThreads) s_g[i >> 6][i & 63] = 0.0;
+    lut_fill(lut, s_seg, s_x);
+    const int lane = threadIdx.x & 63;
+    const float x0 = lut.x0, xn = lut.xn;
     const int top = lut_top(m);
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-        const float v = in[i];
-        const float g = gZ[i];
-        float gi = 0.0f;
-        if (v <= x0) {
-            if (grad_z) atomicAdd(&g_own[0], (double)g);
-        } else if (v >= xn) {
-            if (grad_z) atomicAdd(&g_own[m - 1], (double)g);
-        } else {
-            const int j = lut_segment(s_x, top, m, v);
-            const float dx = s_x[j + 1] - s_x[j];
-            gi = g * __fdiv_rn(s_z[j + 1] - s_z[j], dx);
-            if (grad_z) {
-                const double t = (double)__fdiv_rn(v - s_x[j], dx);
-                atomicAdd(&g_own[j], (1.0 - t) * (double)g);
-                atomicAdd(&g_own[j + 1], t * (double)g);
+    const long long stride = (long long)gridDim.x * 4 * kMapThreads;
+    long long i = ((long long)blockIdx.x * kMapThreads + threadIdx.x) * 4;
+    float4_u v = load4(in, i, n), g = load4(gZ, i, n);
+    for (; i < n; i += stride) {
+        const float4_u vn = load4(in, i + stride, n), gn = load4(gZ, i + stride, n);
+        float4_u gi;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool below = v[u] <= x0, above = v[u] >= xn;
+            const int j = above ? m - 2 : lut_segment<SCAN>(lut, s_x, top, v[u]);
+            const LutSeg s = s_seg[j];
+            gi[u] = (below || above) ? 0.0f : g[u] * __fdiv_rn(s.dz, s.dx);
+            if (grad_z && i + u < n) {
+                const double t = (double)lut_fraction(v[u], s), gd = (double)g[u];
+                if (!above) atomicAdd(&s_g[j][lane], below ? gd : (1.0 - t) * gd);
+                if (!below) atomicAdd(&s_g[j + 1][lane], above ? gd : t * gd);
             }
         }
-        if (grad_in) grad_in[i] = gi;
+        if (grad_in) store4(grad_in, i, n, gi);
+        v = vn;
+        g = gn;
     }
     if (grad_z) {
         __syncthreads();
-        for (int k = threadIdx.x; k < m; k += 256) {
-            double t = 0.0;
-#pragma unroll
-            for (int c = 0; c < kMapCopies; ++c) t += s_g[c * kMapRow + k];
-            if (t != 0.0) atomicAdd(grad_z + k, t);
+        // a wavefront per knot
+        for (int k = threadIdx.x >> 6; k < m; k += kMapThreads / 64) {
+            const double t = lanes_sum(s_g[k][lane]);
+            if (lane == 0) s_sum[k] = t;
         }
+        __syncthreads();
+        if (threadIdx.x < m && s_sum[threadIdx.x] != 0.0) atomicAdd(grad_z + threadIdx.x, s_sum[threadIdx.x]);
     }
 }
 
@@ -3078,10 +3125,26 @@ hipError_t launch_adam(float *x, const float *g, float *m, float *v, int64_t n, 
     return hipGetLastError();
 }
 
+// the table with its inner knots padded for the scan
+static bool scan_table(const LutArgs &lut, LutArgs &t)
+{
+    t = lut;
+    t.x0 = lut.x[0];
+    t.xn = lut.x[lut.n - 1];
+    if (lut.n > kScanKnots) return false;
+    for (int k = lut.n; k < kScanKnots; ++k) t.x[k] = INFINITY;
+    return true;
+}
+
+// blocks of 1024 voxels a pass, at most 16 per CU
+static int map_grid(int64_t n) { return (int)std::min<int64_t>((n + 1023) / 1024, 4096); }
+
 hipError_t launch_map(const float *in, int64_t n, const LutArgs &lut, float *Z, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_map, dim3(grid_for((n + 3) / 4, 256)), dim3(256), 0, st, in, (long long)n, lut, Z);
+    LutArgs t;
+    if (scan_table(lut, t)) hipLaunchKernelGGL(k_map<true>, dim3(map_grid(n)), dim3(256), 0, st, in, (long long)n, t, Z);
+    else hipLaunchKernelGGL(k_map<false>, dim3(map_grid(n)), dim3(256), 0, st, in, (long long)n, t, Z);
     return hipGetLastError();
 }
 
@@ -3089,10 +3152,14 @@ hipError_t launch_map_backward(const float *in, int64_t n, const LutArgs &lut, c
                                double *grad_z, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    // at most 4096 blocks: one FP64 global atomic per knot and block
-    int g = grid_for(n, 256);
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(k_map_backward, dim3(g), dim3(256), 0, st, in, (long long)n, lut, gZ, grad_in, grad_z);
+    const int grid = (int)std::min<int64_t>((n + 4 * kMapThreads - 1) / (4 * kMapThreads), 512);
+    LutArgs t;
+    if (scan_table(lut, t))
+        hipLaunchKernelGGL(k_map_backward<true>, dim3(grid), dim3(kMapThreads), 0, st, in, (long long)n, t, gZ, grad_in,
+                           grad_z);
+    else
+        hipLaunchKernelGGL(k_map_backward<false>, dim3(grid), dim3(kMapThreads), 0, st, in, (long long)n, t, gZ, grad_in,
+                           grad_z);
     return hipGetLastError();
 }
 
