@@ -242,6 +242,14 @@ std::vector<dus::FanTable> build_tables(const dus_fan *fans, int32_t n_poses, bo
     return out;
 }
 
+// every pose renders something (no empty fan)
+bool all_rendered(const std::vector<dus::FanTable> &tabs, int32_t n_poses)
+{
+    int32_t n = 0;
+    for (const auto &t : tabs) n += t.n;
+    return n == n_poses;
+}
+
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
@@ -534,9 +542,13 @@ int dus_render_bmode_backward(const float *Z, const dus_volume *vol, const float
     if (!grad_Z && !grad_pose) return DUS_OK;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     double *acc = reinterpret_cast<double *>((char *)ws + L.acc);
-    if (grad_pose) DUS_HIP(dus::launch_zero_f64(acc, (int64_t)n_poses * dus::kPoseAcc, st), "zero kernel launch");
+    auto tabs = build_tables(fans, n_poses);
+    // every pose in some table: its gradient leaves the pose sums finished;
+    // else (empty fans) through cleared accumulators
+    const bool direct = all_rendered(tabs, n_poses);
+    if (grad_pose && !direct)
+        DUS_HIP(dus::launch_zero_f64(acc, (int64_t)n_poses * dus::kPoseAcc, st), "zero kernel launch");
     if (extent > 0) {
-        const auto tabs = build_tables(fans, n_poses);
         const dus::VolArgs va = vol_args(Z, vol);
         const dus::PhysArgs pa = phys_args(phys);
         const Sched sc = g_sched;
@@ -569,13 +581,15 @@ int dus_render_bmode_backward(const float *Z, const dus_volume *vol, const float
         }
         if (grad_pose) {
             r0 = 0;
-            for (const auto &t : tabs) {
+            for (auto &t : tabs) {
+                t.poses = poses;
+                t.grad_pose = direct ? grad_pose : nullptr;
                 DUS_HIP(dus::launch_pose_reduce(t, rpart + dus::kRayPart * r0, acc, st), "pose reduction kernel");
                 r0 += t.total_rays;
             }
         }
     }
-    if (grad_pose) DUS_HIP(dus::launch_pose_finalize(acc, poses, n_poses, grad_pose, st), "pose kernel launch");
+    if (grad_pose && !direct) DUS_HIP(dus::launch_pose_finalize(acc, poses, n_poses, grad_pose, st), "pose kernel launch");
     return DUS_OK;
 }
 
@@ -913,8 +927,11 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
         zero.a = gZ;
         zero.na = (gZ && (p->flags & DUS_PLAN_ZERO_GRAD_Z)) ? n_vox : 0;
     }
+    // with every pose in some table, its gradient leaves the pose sums
+    // finished; else (empty fans) through cleared accumulators
+    const bool direct = all_rendered(p->tabs, n_poses);
     zero.b = acc;
-    zero.nb = grad_pose ? (int64_t)n_poses * dus::kPoseAcc : 0;
+    zero.nb = (grad_pose && !direct) ? (int64_t)n_poses * dus::kPoseAcc : 0;
     const bool fwd_clears = fwd && p->extent > 0;
     // two chains: the tables alternate between the step's stream and the
     // plan's second stream (forked after the clears, joined before the end).
@@ -936,13 +953,15 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
         DUS_HIP(hipStreamWaitEvent(p->side.st, p->side.fork, 0), "fork wait");
         forked = true;
     }
-    // the tables with the place of their rays' geometry
+    // the tables with the places of their rays' geometry and pose gradients
     std::vector<dus::FanTable> tabs = p->tabs;
     {
         dus::RayGeom *geo = reinterpret_cast<dus::RayGeom *>((char *)ws + p->ws.geo);
         for (auto &t : tabs) {
             t.geom = geo;
             geo += t.total_rays;
+            t.poses = poses;
+            t.grad_pose = direct ? grad_pose : nullptr;
         }
     }
     DUS_HIP(mark(DUS_PHASE_FORWARD), "event");
@@ -1031,16 +1050,16 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     if (adj && grad_pose) {
         r0 = 0;
         for (size_t i = 0; i < tabs.size(); ++i) {
-            const auto &t = tabs[i];
-            DUS_HIP(dus::launch_pose_reduce(t, rpart + dus::kRayPart * r0, acc, tst(i)), "pose reduction kernel");
-            r0 += t.total_rays;
+            DUS_HIP(dus::launch_pose_reduce(tabs[i], rpart + dus::kRayPart * r0, acc, tst(i)), "pose reduction kernel");
+            r0 += tabs[i].total_rays;
         }
     }
     if (two) {
         DUS_HIP(hipEventRecord(p->side.join, p->side.st), "join event");
         DUS_HIP(hipStreamWaitEvent(st, p->side.join, 0), "join wait");
     }
-    DUS_HIP(dus::launch_finish(part, n_part, loss, acc, poses, n_poses, grad_pose, st), "loss and pose kernel");
+    DUS_HIP(dus::launch_finish(part, n_part, loss, acc, poses, n_poses, direct ? nullptr : grad_pose, st),
+            "loss and pose kernel");
     DUS_HIP(mark(DUS_NUM_PHASES), "event");
     return DUS_OK;
 }

@@ -69,6 +69,8 @@ struct FanTable {
     int32_t ray1;           // adjoint without records: the launch's rays are [ray0, ray1)
     RayGeom *geom;          // forward: if not NULL, where to record the rays' geometry; adjoint with
                             // the forward's records: where to find it (else set up again)
+    const float *poses;     // pose sums: with grad_pose, the poses, and where the gradients of the
+    float *grad_pose;       // table's poses go (NULL: into the accumulators)
     FanRec f[kMaxFans];
 };
 
@@ -148,8 +150,9 @@ hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const Phys
                           const double *zcar, const int32_t *, const double *states,
                           const float *gain, hipStream_t st, int span_samples = kSpanSamples,
                           const SideStream *side = nullptr);
-// pose_acc[pose] += the sum of the table's per-ray partials, one wavefront
-// per fan (fixed order)
+// the sum of the table's per-ray partials per fan (fixed order), into
+// t.grad_pose as the pose's finished gradient, or without it added to
+// pose_acc[pose]
 hipError_t launch_pose_reduce(const FanTable &t, const double *pose_part, double *pose_acc, hipStream_t st);
 // fix (nullable): deterministic mode, 64-bit fixed-point sums at the scale
 // fscale[0] (launch_fix_scale) instead of FP32 atomics into gZ; wave_target:
@@ -196,7 +199,7 @@ hipError_t launch_finish(const double *part, int64_t n_part, double *loss, const
 // a[0..na) = 0 and b[0..nb) = 0 in one launch
 hipError_t launch_zero_pair(float *a, int64_t na, double *b, int64_t nb, hipStream_t st);
 // smoothness prior of the reconstruction: per-axis weights w / h^2; one
-// energy partial per block of 256 voxels (smooth_blocks of them)
+// energy partial per block of voxels (smooth_blocks of them)
 int64_t smooth_blocks(int nx, int ny, int nz);
 hipError_t launch_smooth(const float *Z, int nx, int ny, int nz, float wx, float wy, float wz, float *gZ,
                          double *part, hipStream_t st);
