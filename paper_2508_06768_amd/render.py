@@ -18,7 +18,14 @@ from . import _lib
 from ._lib import DusFan, DusPhysics, DusSchedule, DusVolume, check
 
 
+# the current stream's handle without a Stream object (2.8 us on the host,
+# as much as a kernel launch); the public call where torch has no such entry
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
     return int(torch.cuda.current_stream().cuda_stream)
 
 
@@ -82,11 +89,13 @@ class Geometry:
         o = int(self.offsets[p])
         return flat[o:o + int(f.n_rays) * int(f.n_samples)].view(int(f.n_rays), int(f.n_samples))
 
+    def workspace_bytes(self, with_backward: bool) -> int:
+        return int(check(_lib.lib().dus_workspace_bytes(ctypes.byref(self.vol_c), self.fans_c, len(self.fans),
+                                                        ctypes.byref(self.phys_c), int(with_backward)),
+                         "dus_workspace_bytes"))
+
     def workspace(self, with_backward: bool, device) -> torch.Tensor:
-        nb = check(_lib.lib().dus_workspace_bytes(ctypes.byref(self.vol_c), self.fans_c, self.n_poses,
-                                                 ctypes.byref(self.phys_c), int(with_backward)),
-                   "dus_workspace_bytes")
-        return torch.empty(max(int(nb), 1), dtype=torch.uint8, device=device)
+        return torch.empty(max(self.workspace_bytes(with_backward), 1), dtype=torch.uint8, device=device)
 
 
 def physics_record(ph) -> DusPhysics:
@@ -134,19 +143,25 @@ def render(Z: torch.Tensor, poses: torch.Tensor, geom: Geometry, want_pivot: boo
            out: torch.Tensor | None = None, ws: torch.Tensor | None = None):
     """Forward render; returns the packed image (and per-ray min pivots)."""
     _check_inputs(Z, poses, geom)
-    dev = Z.device
+    dev, total = Z.device, geom.total
     if out is None:
-        out = torch.empty(max(geom.total, 1), dtype=torch.float32, device=dev)
-    _check_buffer(out, "out", geom.total, device=dev)
+        out = torch.empty(max(total, 1), dtype=torch.float32, device=dev)
+    else:
+        _check_buffer(out, "out", total, device=dev)
     piv = torch.empty(max(geom.total_rays, 1), dtype=torch.float32, device=dev) if want_pivot else None
     if ws is None:
-        ws = geom.workspace(False, dev)
-    _check_buffer(ws, "ws", 0, torch.uint8, dev)
-    check(_lib.lib().dus_render_bmode(_ptr(Z), ctypes.byref(geom.vol_c), _ptr(poses), geom.fans_c,
-                                      geom.n_poses, ctypes.byref(geom.phys_c), _ptr(out), _ptr(piv),
-                                      _ptr(ws), ws.numel(), _stream()),
+        nb = geom.workspace_bytes(False)
+        if nb > 0:              # none is needed without blur
+            ws = torch.empty(nb, dtype=torch.uint8, device=dev)
+    else:
+        _check_buffer(ws, "ws", 0, torch.uint8, dev)
+        nb = ws.numel()
+    check(_lib.lib().dus_render_bmode(Z.data_ptr(), ctypes.byref(geom.vol_c), poses.data_ptr(), geom.fans_c,
+                                      len(geom.fans), ctypes.byref(geom.phys_c), out.data_ptr(), _ptr(piv),
+                                      _ptr(ws), nb, _stream()),
           "dus_render_bmode")
-    out = out[:geom.total]
+    if out.numel() != total or out.dim() != 1:
+        out = out[:total]
     return (out, piv[:geom.total_rays]) if want_pivot else out
 
 
@@ -156,19 +171,25 @@ def render_backward(Z: torch.Tensor, poses: torch.Tensor, geom: Geometry, grad_b
     """Hand-written adjoint: (dL/dZ, dL/dpose) for dL/dbmode."""
     _check_inputs(Z, poses, geom)
     dev = Z.device
-    g = grad_bmode.contiguous().to(torch.float32)
+    g = grad_bmode
+    if g.dtype != torch.float32 or not g.is_contiguous():
+        g = g.contiguous().to(torch.float32)
     _check_buffer(g, "grad_bmode", geom.total, device=dev)
     gZ = None
     if want_Z:
-        gZ = grad_Z if grad_Z is not None else torch.zeros_like(Z)
-        _check_buffer(gZ, "grad_Z", Z.numel(), device=dev)
+        if grad_Z is None:
+            gZ = torch.zeros_like(Z)
+        else:
+            gZ = grad_Z
+            _check_buffer(gZ, "grad_Z", Z.numel(), device=dev)
     gp = torch.empty((geom.n_poses, 6), dtype=torch.float32, device=dev) if want_pose else None
     if ws is None:
         ws = geom.workspace(True, dev)
-    _check_buffer(ws, "ws", 0, torch.uint8, dev)
-    check(_lib.lib().dus_render_bmode_backward(_ptr(Z), ctypes.byref(geom.vol_c), _ptr(poses),
-                                               geom.fans_c, geom.n_poses, ctypes.byref(geom.phys_c),
-                                               _ptr(g), _ptr(gZ), _ptr(gp), _ptr(ws), ws.numel(),
+    else:
+        _check_buffer(ws, "ws", 0, torch.uint8, dev)
+    check(_lib.lib().dus_render_bmode_backward(Z.data_ptr(), ctypes.byref(geom.vol_c), poses.data_ptr(),
+                                               geom.fans_c, len(geom.fans), ctypes.byref(geom.phys_c),
+                                               g.data_ptr(), _ptr(gZ), _ptr(gp), ws.data_ptr(), ws.numel(),
                                                _stream()),
           "dus_render_bmode_backward")
     return gZ, gp
