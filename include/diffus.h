@@ -332,7 +332,8 @@ typedef struct {
     int32_t span_samples;     /* rays of at least this many samples are walked by several
                                  wavefronts each, which take consecutive tiles of the ray together
                                  (forward; the plan's adjoint): 1..DUS_MAX_SAMPLES, 0 (the default)
-                                 for 4096, -1 for never.  Results do not depend on it, except for
+                                 for 4096 and, where a launch has few rays, for shorter ones too,
+                                 -1 for never.  Results do not depend on it, except for
                                  the rounding of the pose gradient and of the fused loss */
 } dus_schedule;
 

@@ -2712,6 +2712,34 @@ inline int span_rays(const FanTable &t, int span_samples)
 inline int ray_blocks(int w, int n) { return w == 1 ? (n + kBlockRays - 1) / kBlockRays : n; }
 inline int block_group(int w, int rays) { return w == 1 ? std::max(rays / kBlockRays, 1) : rays; }
 
+// Wavefronts per ray (2, 4 or 8: one per tile of the longest ray, as far as
+// they go) where a launch's rays are too few to fill the chip by themselves;
+// 0: the usual split.  A launch of few rays takes as long as its longest ray's
+// chain of tiles, which the wavefronts share: forward (with blur) and
+// pose-only step with one wavefront a ray against several, us:
+//   64 x 300    11.7 ->  11.0    34.3 -> 31.1
+//   256 x 1024  16.2 ->  12.6    42.4 -> 32.9
+//   512 x 1024  17.6 ->  14.8    44.4 -> 36.8
+//   64 x 2048   24.2 ->  13.5    59.8 -> 34.8
+//   512 x 2048  27.5 ->  18.1    65.7 -> 49.4
+//   512 x 3000  39.3 ->  31.6    89.4 -> 72.9
+// The line is where the wavefronts, idle ones included, begin to cost more
+// than the shorter chain saves: 2048 of them, 4096 for rays over 1024
+// samples.  Past it: 1024 x 520 in four wavefronts (4096) 45.8 -> 48.1 and
+// 2048 x 300 in two 49.5 -> 54.5 (pose-only step); 1024 x 1500 in eight
+// (8192) 63.7 -> 75.1, against 64.6 where only its forward takes four.
+// Results are the same but for the order of the pose gradient's and the
+// fused loss's sums, as with the long rays' wavefronts; a schedule that sets
+// another span length than the default keeps to what it says.
+inline int few_ray_waves(const FanTable &t, int tile, int span_samples)
+{
+    if (span_samples != kSpanSamples) return 0;
+    const int s = longest_ray(t);
+    int w = 1;
+    while (w < 8 && w * tile < s) w *= 2;
+    return (w > 1 && (long long)t.total_rays * w <= (s > 1024 ? 4096 : 2048)) ? w : 0;
+}
+
 // the side stream starts after what st has queued; st waits for it at the
 // join (graph capture turns both into graph edges)
 inline hipError_t fork_side(hipStream_t st, const SideStream &s)
@@ -2744,12 +2772,19 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
         else DUS_FWD_LAUNCH_(CH, SPK, WV, false, NG, TAB, ZERO, STR);                            \
     } while (0)
 
+#define DUS_FWD_LONG(CH, WV, NG, ZERO)                                                          \
+    do {                                                                                        \
+        if (p.speckle) DUS_FWD_LAUNCH(CH, true, WV, NG, t, ZERO, sst);                          \
+        else DUS_FWD_LAUNCH(CH, false, WV, NG, t, ZERO, sst);                                   \
+    } while (0)
+
 #define DUS_FWD_CASE(CH)                                                                       \
     case CH:                                                                                   \
-        if (n_span > 0) {                                                                      \
-            if (p.speckle) DUS_FWD_LAUNCH(CH, true, kSpanWaves, n_span, t, ZeroArgs{}, sst);    \
-            else DUS_FWD_LAUNCH(CH, false, kSpanWaves, n_span, t, ZeroArgs{}, sst);             \
-        }                                                                                      \
+        if (few == 2) DUS_FWD_LONG(CH, 2, t.total_rays, zero);                                 \
+        else if (few == 4) DUS_FWD_LONG(CH, 4, t.total_rays, zero);                            \
+        else if (few == 8) DUS_FWD_LONG(CH, 8, t.total_rays, zero);                            \
+        if (few) break;                                                                        \
+        if (n_span > 0) DUS_FWD_LONG(CH, kSpanWaves, n_span, ZeroArgs{});                      \
         if (n_one > 0 || zero.na > 0 || zero.nb > 0) {                                         \
             if (p.speckle) DUS_FWD_LAUNCH(CH, true, 1, t.total_rays, t1, zero, st);            \
             else DUS_FWD_LAUNCH(CH, false, 1, t.total_rays, t1, zero, st);                     \
@@ -2762,8 +2797,12 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
 // 164 against 153 us); on the uneven 64-pose batch, whose rays pad to 1.20x
 // their samples in 512-sample tiles and to 1.09x in 256-sample ones, it
 // takes 217 against 229 us.
-static int auto_fwd_chunk(const FanTable &t)
+// Few rays that share out their tiles take the shorter ones as long as one
+// round of eight holds the ray at least twice over (256 x 1024: 13.6 -> 12.6
+// us; 384 x 1500 in eight 4 x 64 tiles against four of 8 x 64: 20.0 / 16.9).
+static int auto_fwd_chunk(const FanTable &t, int span_samples)
 {
+    if (longest_ray(t) <= 1024 && few_ray_waves(t, 256, span_samples)) return 4;
     long long pad4 = 0, pad8 = 0;
     for (int f = 0; f < t.n; ++f) {
         const long long r = t.f[f].n_rays, s = t.f[f].n_samples;
@@ -2779,11 +2818,13 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
                           hipStream_t st, const ZeroArgs &zero, int span_samples, const SideStream *side)
 {
     if (t.total_rays <= 0) return hipSuccess;
-    if (chunk == 0) chunk = auto_fwd_chunk(t);
+    if (chunk == 0) chunk = auto_fwd_chunk(t, span_samples);
     if (chunk != 4 && chunk != 8 && chunk != 16) return hipErrorInvalidValue;
     // the rays of the table's long fans (its first ones: a table lists its
-    // fans longest first) get kSpanWaves wavefronts each, the rest one
-    const int n_span = span_rays(t, span_samples);
+    // fans longest first) get kSpanWaves wavefronts each, the rest one; all
+    // rays several where they are few
+    const int few = (chunk < 16) ? few_ray_waves(t, 64 * chunk, span_samples) : 0;
+    const int n_span = few ? 0 : span_rays(t, span_samples);
     const int n_one = t.total_rays - n_span;
     // the clears go with the one-wavefront launch (it covers every ray)
     FanTable t1 = t;
@@ -2834,6 +2875,13 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
         }                                                                                      \
         break;
 
+// from the records, few rays
+#define DUS_FEW_CASE(WV)                                                                       \
+    case WV:                                                                                   \
+        if (fused) DUS_BWD_LAUNCH(4, false, true, WV, kRecords, t.total_rays, t, st);           \
+        else DUS_BWD_LAUNCH(4, false, false, WV, kRecords, t.total_rays, t, st);               \
+        break;
+
 // without records (rays of at most kWholeSamples): W wavefronts per ray, one
 // per 256 samples
 #define DUS_WHOLE_CASE(WV)                                                                     \
@@ -2882,7 +2930,16 @@ hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const Phys
     }
     // the fused step records its gains and the rays' geometry
     if ((fused && (spk || !zcar)) || (spk && zcar) || (zcar && !t.geom)) return hipErrorInvalidValue;
-    // several wavefronts per long ray
+    // several wavefronts per long ray, or for every ray where they are few
+    const int few = (chunk == 4 && zcar) ? few_ray_waves(t, 256, span_samples) : 0;
+    if (few) {
+        switch (few) {
+            DUS_FEW_CASE(2)
+            DUS_FEW_CASE(4)
+            DUS_FEW_CASE(8)
+        }
+        return hipGetLastError();
+    }
     const int n_span = span_rays(t, span_samples);
     const int n_one = t.total_rays - n_span;
     t1.ray0 = n_span;
