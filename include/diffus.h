@@ -300,23 +300,24 @@ int dus_footprint_mask(const dus_volume *vol, const float *poses, const dus_fan 
  * and the loss is differentiated with respect to the impedance volume and
  * the poses (as dus_render_bmode_backward does).  The paper prints no loss;
  * the mean squared error per pose is this library's choice.  A plan fixes
- * the volume shape, the fans and the physics; each dus_plan_step replays one
- * captured HIP graph on `stream`.
+ * the volume shape, the fans and the physics; each dus_plan_step launches one
+ * chain of kernels on `stream`, or replays a captured HIP graph there.
  */
 typedef struct dus_plan dus_plan;
 
 enum {
     DUS_PLAN_POSE_ONLY = 1,   /* grad_Z is neither needed nor touched */
     DUS_PLAN_ZERO_GRAD_Z = 2, /* the step clears grad_Z itself (fill kernel) */
-    DUS_PLAN_NO_GRAPH = 4,    /* launch eagerly instead of replaying a graph */
+    DUS_PLAN_NO_GRAPH = 4,    /* launch eagerly, never from a graph */
     DUS_PLAN_DETERMINISTIC = 8, /* dL/dZ bit-identical from step to step: summed as 64-bit fixed
                                    point (scale 2^e set per step from the sum of |dL/dZ| over all
                                    samples, so no sum can overflow) and rounded once to FP32,
                                    instead of FP32 atomics; costs 8 B per voxel of workspace */
     DUS_PLAN_ONE_STREAM = 16   /* every launch on the step's stream, the fans in tables of up to 64
-                                  (by default a plan of two or more fans runs them as two chains of
-                                  launches, half the fans each, on the step's stream and a second
-                                  one, and long rays' launches beside the others) */
+                                  (by default a plan of two or more fans and at least 3 * 2^20
+                                  ray-samples runs them as two chains of launches, half the fans
+                                  each, on the step's stream and a second one, and long rays'
+                                  launches run beside the others) */
 };
 
 /* Ray-to-wavefront schedule; 0 fields select the library default. */
@@ -367,13 +368,14 @@ int dus_plan_set_schedule(dus_plan *plan, const dus_schedule *sched);
 int dus_plan_get_schedule(const dus_plan *plan, dus_schedule *sched);
 /*
  * One fused step of the plan (Sec. 2.3-2.4 forward, MSE, adjoint; see above)
- * on `stream`: the first call, and any call whose pointers or workspace size
- * differ from the previous call's, captures a new HIP graph; the others
- * replay it.  Unless the plan was created with DUS_PLAN_ONE_STREAM, the step
- * also runs launches on the plan's second stream (two chains of launches,
- * or the long rays' launches), forked from `stream` and joined back into it
- * before the step's last launch, so the step is ordered on `stream` all the
- * same; two steps of one plan must not run at the same time.  Z and poses
+ * on `stream`.  Unless the plan was created with DUS_PLAN_ONE_STREAM, large
+ * plans and plans with long rays also run launches on the plan's second
+ * stream (two chains of launches, or the long rays' launches), forked from
+ * `stream` and joined back into it before the step's last launch, so the
+ * step is ordered on `stream` all the same.  Such a step comes from a HIP
+ * graph: the first call, and any call whose pointers or workspace size
+ * differ from the previous call's, captures a new one; the others replay
+ * it.  The other plans launch their kernels directly.  Two steps of one plan must not run at the same time.  Z and poses
  * as for dus_render_bmode; the workspace has at least
  * dus_plan_workspace_bytes(plan) bytes, 256-byte aligned.
  *   target   device FP32, same layout as bmode

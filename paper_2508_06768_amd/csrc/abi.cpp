@@ -446,6 +446,7 @@ struct dus_plan {
     dus::SideStream side{};
     hipEvent_t cleared = nullptr;   // the first table's forward has cleared dL/dZ and the pose sums
     bool two_chains = false;        // the tables alternate between two chains of launches
+    bool use_graph = false;         // the step is replayed from a captured graph
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
     const void *key[9] = {};
@@ -456,22 +457,60 @@ struct dus_plan {
 
 namespace {
 
+// Plans of this many ray-samples or more run two chains of launches, and so
+// do the smallest: too few samples to be of use to a program, they keep the
+// path within reach of the host-side tests that walk its every launch.
+constexpr int64_t kChainSamples = (int64_t)3 << 20;
+constexpr int64_t kTinySamples = 4096;
+
+struct PlanShape {
+    int fans = 0;           // that render something
+    int64_t work = 0;       // ray-samples
+    bool long_rays = false; // some take several wavefronts by their length
+};
+
+PlanShape plan_shape(const dus_plan *p)
+{
+    PlanShape s;
+    for (const auto &f : p->fans) {
+        if (f.n_rays <= 0 || f.n_samples <= 0) continue;
+        ++s.fans;
+        s.work += (int64_t)f.n_rays * f.n_samples;
+        s.long_rays = s.long_rays || (p->sched.span_samples > 0 && f.n_samples >= p->sched.span_samples);
+    }
+    return s;
+}
+
 // Whether a plan's step runs as two chains of launches on two streams, the
 // fans split in two groups of about equal work, so that one chain's kernels
 // fill the other's tails: not for the deterministic plan (one chain), nor
 // for a plan held to one stream, nor when some ray is long enough for
 // several wavefronts (its launches take the second stream), nor for a
-// single fan.
+// single fan, nor for small plans: the second chain's start and join cost
+// more there than its overlap saves.  Two chains (from a graph) against one
+// (launched directly), full step in us: 6 poses x 310 x 339 (0.6 M samples)
+// 84 / 52, 55 x 40 x 946 (2.1 M) 99 / 93, 12 x 439 x 935 (4.9 M) 149 / 158,
+// 64 x 256 x 1024 (16.8 M) 422 / 436; between 2 M and 3 M one chain wins by 4%
+// in the mean of 15 shapes, between 3 M and 5 M it loses 1% in that of 12 and
+// 5% at the worst.
 bool plan_two_chains(const dus_plan *p)
 {
-    int nonempty = 0;
-    bool long_rays = false;
-    for (const auto &f : p->fans) {
-        if (f.n_rays <= 0 || f.n_samples <= 0) continue;
-        ++nonempty;
-        long_rays = long_rays || (p->sched.span_samples > 0 && f.n_samples >= p->sched.span_samples);
-    }
-    return !(nonempty < 2 || long_rays || (p->flags & (DUS_PLAN_DETERMINISTIC | DUS_PLAN_ONE_STREAM)));
+    const PlanShape s = plan_shape(p);
+    return !(s.fans < 2 || (s.work < kChainSamples && s.work >= kTinySamples) || s.long_rays ||
+             (p->flags & (DUS_PLAN_DETERMINISTIC | DUS_PLAN_ONE_STREAM)));
+}
+
+// Whether a plan's step is replayed from a captured graph: where it runs on
+// two streams, whose waits on each other are cheaper inside a graph (skewed
+// batch of 64 fans, one with 64 rays of 16384 samples: 286 us against 359
+// launched directly).  One chain of launches is cheaper without: a graph's
+// own start and end cost about 5 us (3 poses x 106 x 344: 25 / 17 us, 64 x
+// 256 x 1024 on one stream 440 / 436), as much time on the host as its
+// launches take (20 / 13-22 us), and a capture for new buffers.
+bool plan_uses_graph(const dus_plan *p)
+{
+    if (p->flags & DUS_PLAN_NO_GRAPH) return false;
+    return p->two_chains || (!(p->flags & DUS_PLAN_ONE_STREAM) && plan_shape(p).long_rays);
 }
 
 }  // namespace
@@ -807,6 +846,7 @@ int dus_plan_create(dus_plan **out, const dus_volume *vol, const dus_fan *fans, 
     p->phys = *phys;
     p->flags = flags;
     p->two_chains = plan_two_chains(p);
+    p->use_graph = plan_uses_graph(p);
     p->tabs = build_tables(fans, n_poses, p->two_chains);
     p->ws = layout(fans, n_poses, phys, 2, (flags & DUS_PLAN_POSE_ONLY) != 0,
                    (flags & DUS_PLAN_DETERMINISTIC) ? (int64_t)vol->nx * vol->ny * vol->nz : 0);
@@ -852,6 +892,7 @@ int dus_plan_set_schedule(dus_plan *p, const dus_schedule *sc)
         p->two_chains = two;
         p->tabs = build_tables(p->fans.data(), (int32_t)p->fans.size(), two);
     }
+    p->use_graph = plan_uses_graph(p);
     return DUS_OK;
 }
 
@@ -1090,7 +1131,7 @@ int dus_plan_step(dus_plan *p, const float *Z, const float *poses, const float *
         if (!Z || !poses || !target) return fail(DUS_EINVAL, "Z, poses and target are required");
     }
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (p->flags & DUS_PLAN_NO_GRAPH) return plan_enqueue(p, Z, poses, target, bmode, loss, grad_Z, grad_pose, ws, st);
+    if (!p->use_graph) return plan_enqueue(p, Z, poses, target, bmode, loss, grad_Z, grad_pose, ws, st);
     const void *key[9] = {Z, poses, target, bmode, loss, grad_Z, grad_pose, ws, nullptr};
     bool same = p->exec != nullptr && p->key_ws_bytes == ws_bytes;
     for (int i = 0; i < 8 && same; ++i) same = (key[i] == p->key[i]);

@@ -373,11 +373,11 @@ def footprint_voxels(poses: torch.Tensor, geom: Geometry) -> int:
 
 
 class FusedStep:
-    """Batched fused forward + MSE + adjoint over all poses of ``geom``,
-    replayed from a captured HIP graph (``dus_plan``).  ``deterministic``:
-    dL/dZ bit-identical from step to step; ``one_stream``: every launch on
-    the caller's stream (by default the fans run as two chains of launches
-    on two streams)."""
+    """Batched fused forward + MSE + adjoint over all poses of ``geom``
+    (``dus_plan``).  ``deterministic``: dL/dZ bit-identical from step to step;
+    ``one_stream``: every launch on the caller's stream (by default the fans
+    of a large plan run as two chains of launches on two streams, replayed
+    from a captured HIP graph unless ``graph`` is False)."""
 
     def __init__(self, geom: Geometry, pose_only: bool = False, zero_grad_z: bool = True,
                  graph: bool = True, schedule: dict | None = None, deterministic: bool = False,
