@@ -457,6 +457,30 @@ struct dus_plan {
 
 namespace {
 
+// Whether a table's adjoint, where no image is rendered before it, gathers
+// its rays once by itself (one wavefront per 256 samples, 2, 4 or 8 for a
+// longer ray) instead of starting from the records of a forward launch.  In
+// quarter nanoseconds, from pose-only steps of 8192 rays: 21 a wavefront,
+// idle ones included, against 22 a ray and 8 per 256 samples, and about 7 us
+// for the launch more (us, once / records: 200 samples 42 / 69, 500 91 / 85,
+// 700 160 / 101, 1400 360 / 150, 2000 372 / 187; of 256 rays: 500 14 / 18,
+// 2000 18 / 23; of 800 rays: 700 27 / 30, 1400 50 / 43).  The blocks of
+// eight wavefronts have a compute unit to themselves (190 registers), so
+// nothing covers their barriers.
+bool gathers_once(const dus::FanTable &t)
+{
+    if (dus::longest_ray(t) > dus::kWholeSamples) return false;
+    int64_t once = 0, rec = 28000;
+    for (int f = 0; f < t.n; ++f) {
+        const int64_t tiles = (t.f[f].n_samples + dus::kCarryBlock - 1) / dus::kCarryBlock;
+        int64_t w = 1;
+        while (w < tiles) w *= 2;
+        once += 21 * w * t.f[f].n_rays;
+        rec += (22 + 8 * tiles) * t.f[f].n_rays;
+    }
+    return once <= rec;
+}
+
 // Plans of this many ray-samples or more run two chains of launches, and so
 // do the smallest: too few samples to be of use to a program, they keep the
 // path within reach of the host-side tests that walk its every launch.
@@ -952,8 +976,10 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     float *gain = p->ws.gain_bytes ? reinterpret_cast<float *>((char *)ws + p->ws.gain) : nullptr;
     const bool blur = p->phys.blur_on != 0;
     const bool fwd = blur || bmode;               // the forward kernel runs
-    // the pose accumulators and dL/dZ are cleared by the forward kernel's
-    // wavefronts (when it runs and renders something), else by a fill kernel
+    // the forward runs before a table's adjoint, with it or for it alone
+    auto recorded = [&](const dus::FanTable &t) { return fwd || !gathers_once(t); };
+    // the pose accumulators and dL/dZ are cleared by the first forward
+    // kernel's wavefronts (when it runs), else by a fill kernel
     const int64_t n_vox = (int64_t)p->vol.nx * p->vol.ny * p->vol.nz;
     // deterministic plan: dL/dZ is summed in the fixed-point buffer (cleared
     // every step) and written into grad_Z at the end
@@ -973,7 +999,7 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     const bool direct = all_rendered(p->tabs, n_poses);
     zero.b = acc;
     zero.nb = (grad_pose && !direct) ? (int64_t)n_poses * dus::kPoseAcc : 0;
-    const bool fwd_clears = fwd && p->extent > 0;
+    const bool fwd_clears = !p->tabs.empty() && recorded(p->tabs[0]);
     // two chains: the tables alternate between the step's stream and the
     // plan's second stream (forked after the clears, joined before the end).
     // One chain for the phase-timed step, for the deterministic plan (its
@@ -1042,13 +1068,13 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     if (adj)
         for (size_t i = 0; i < tabs.size(); ++i) {
             const auto &t = tabs[i];
-            // without a forward before it, the adjoint needs the records only
-            // for rays too long to gather at once
-            const bool rec = fwd || dus::longest_ray(t) > dus::kWholeSamples;
-            if (rec && !fwd)
+            const bool rec = recorded(t);
+            if (rec && !fwd) {
                 DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, nullptr, nullptr, 0, zc, nullptr,
-                                            cst, gain, tst(i), dus::ZeroArgs{}, sc.span_samples, side),
+                                            cst, gain, tst(i), (i == 0) ? zero : dus::ZeroArgs{}, sc.span_samples, side),
                         "forward kernel launch");
+                if (i == 0 && two) DUS_HIP(hipEventRecord(p->cleared, st), "clear event");
+            }
             // dL/dZ per sample is stored only for the scatter
             DUS_HIP(dus::launch_adjoint(sc.bwd_chunk, sc.xcd_group, va, pa, t, poses, gZ ? rays + r0 : nullptr, eb,
                                         blur ? nullptr : target,

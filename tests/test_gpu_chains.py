@@ -55,3 +55,35 @@ def test_chains_agree(rays, effects):
         assert r[1] == pytest.approx(ref[1], rel=1e-12)
         assert H.rel_l2(r[2], ref[2]) <= 1e-6
         np.testing.assert_allclose(r[3], ref[3], rtol=1e-6, atol=1e-6 * np.abs(ref[3]).max())
+
+
+# the adjoint of a step that renders no image gathers its rays once, or
+# starts from the records of a forward: ray counts on both sides of the line
+@pytest.mark.parametrize("rays,samples", [(736, 700), (737, 700), (341, 2000), (342, 2000), (5608, 300), (5620, 300)])
+@pytest.mark.parametrize("effects", [False, True])
+def test_adjoint_without_image(rays, samples, effects):
+    """With and without the image asked for (with it, the forward runs): the
+    same loss and gradients within rounding, and cleared outputs."""
+    from paper_2508_06768_amd.render import FusedStep, Geometry
+    print("without image", rays, samples, effects, flush=True)
+    rng = np.random.default_rng(53)
+    Z = torch.from_numpy(rng.uniform(1.4, 1.8, size=(48, 40, 44)).astype(np.float32)).to(DEV)
+    poses = torch.tensor([[21.0, 19.0, 0.0, 0.0, 0.0, 0.0], [20.0, 20.0, 1.0, 0.1, 0.0, 0.1]], device=DEV)
+    fans = [synth.FanSpec(rays, samples, 1.2, 48.0 / samples, 0.5, 0), synth.FanSpec(2, 3, 0.1, 1.0, 0.0, 1)]
+    ph = synth.PhysicsSpec(refl_mode=1, speckle_on=effects, blur_on=False, seed=5)
+    geom = Geometry(tuple(Z.shape), (1.0, 1.0, 1.0), (0.0, 0.0, 0.0), fans, ph)
+    target = torch.full((geom.total,), 0.05, device=DEV)
+    runs = []
+    for image in (True, False):
+        step = FusedStep(geom)
+        loss = torch.full((1,), float("nan"), dtype=torch.float64, device=DEV)
+        bm = torch.empty(geom.total, device=DEV) if image else None
+        gZ, gp = torch.full_like(Z, float("nan")), torch.full((2, 6), float("nan"), device=DEV)
+        step.step(Z, poses, target, bmode=bm, loss=loss, grad_Z=gZ, grad_pose=gp)
+        torch.cuda.synchronize()
+        step.close()
+        runs.append((loss.item(), gZ.cpu().numpy().astype(np.float64), gp.cpu().numpy().astype(np.float64)))
+    a, b = runs
+    assert b[0] == pytest.approx(a[0], rel=1e-10)
+    assert H.rel_l2(b[1], a[1]) <= 1e-6
+    np.testing.assert_allclose(b[2], a[2], rtol=1e-6, atol=1e-6 * np.abs(a[2]).max())
