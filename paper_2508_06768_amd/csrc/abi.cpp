@@ -428,6 +428,33 @@ int enqueue_forward(const Sched &sc, const dus::VolArgs &va, const dus::PhysArgs
     return DUS_OK;
 }
 
+// Whether a table's adjoint, where no image is rendered before it, gathers
+// its rays once by itself (one wavefront per 256 samples, 2, 4 or 8 for a
+// longer ray) instead of starting from the records of a forward launch.  In
+// quarter nanoseconds, from pose-only steps of 8192 rays: 21 a wavefront,
+// idle ones included, against 22 a ray and 8 per 256 samples, and a fixed
+// `start`: about 7 us for the launch more, 16 us in the direct adjoint, which
+// reads states without geometry with one wavefront a ray (pose-only steps, us, once / records: 200 samples 42 / 69, 500 91 / 85,
+// 700 160 / 101, 1400 360 / 150, 2000 372 / 187; of 256 rays: 500 14 / 18,
+// 2000 18 / 23; of 800 rays: 700 27 / 30, 1400 50 / 43; direct adjoint of 512 rays: 2000 38 / 49, of
+// 1024: 1000 36 / 42, 1400 63 / 55, of 8192: 1400 420 / 222).  The blocks of
+// eight wavefronts have a compute unit to themselves (190 registers), so
+// nothing covers their barriers.
+constexpr int64_t kStepStart = 28000, kDirectStart = 64000;
+bool gathers_once(const dus::FanTable &t, int64_t start)
+{
+    if (dus::longest_ray(t) > dus::kWholeSamples) return false;
+    int64_t once = 0, rec = start;
+    for (int f = 0; f < t.n; ++f) {
+        const int64_t tiles = (t.f[f].n_samples + dus::kCarryBlock - 1) / dus::kCarryBlock;
+        int64_t w = 1;
+        while (w < tiles) w *= 2;
+        once += 21 * w * t.f[f].n_rays;
+        rec += (22 + 8 * tiles) * t.f[f].n_rays;
+    }
+    return once <= rec;
+}
+
 }  // namespace
 
 struct dus_plan {
@@ -456,30 +483,6 @@ struct dus_plan {
 
 
 namespace {
-
-// Whether a table's adjoint, where no image is rendered before it, gathers
-// its rays once by itself (one wavefront per 256 samples, 2, 4 or 8 for a
-// longer ray) instead of starting from the records of a forward launch.  In
-// quarter nanoseconds, from pose-only steps of 8192 rays: 21 a wavefront,
-// idle ones included, against 22 a ray and 8 per 256 samples, and about 7 us
-// for the launch more (us, once / records: 200 samples 42 / 69, 500 91 / 85,
-// 700 160 / 101, 1400 360 / 150, 2000 372 / 187; of 256 rays: 500 14 / 18,
-// 2000 18 / 23; of 800 rays: 700 27 / 30, 1400 50 / 43).  The blocks of
-// eight wavefronts have a compute unit to themselves (190 registers), so
-// nothing covers their barriers.
-bool gathers_once(const dus::FanTable &t)
-{
-    if (dus::longest_ray(t) > dus::kWholeSamples) return false;
-    int64_t once = 0, rec = 28000;
-    for (int f = 0; f < t.n; ++f) {
-        const int64_t tiles = (t.f[f].n_samples + dus::kCarryBlock - 1) / dus::kCarryBlock;
-        int64_t w = 1;
-        while (w < tiles) w *= 2;
-        once += 21 * w * t.f[f].n_rays;
-        rec += (22 + 8 * tiles) * t.f[f].n_rays;
-    }
-    return once <= rec;
-}
 
 // Plans of this many ray-samples or more run two chains of launches, and so
 // do the smallest: too few samples to be of use to a program, they keep the
@@ -626,9 +629,9 @@ int dus_render_bmode_backward(const float *Z, const dus_volume *vol, const float
         for (const auto &t : tabs) {
             dus::RayRec *rays = reinterpret_cast<dus::RayRec *>((char *)ws + L.rays) + r0;
             float *zb = reinterpret_cast<float *>((char *)ws + L.zb);
-            // rays too long to gather at once: the forward's states first, in
+            // rays that are not gathered once: the forward's states first, in
             // the rows that dL/dZ then overwrites
-            double *states = dus::longest_ray(t) > dus::kWholeSamples ? reinterpret_cast<double *>(zb) : nullptr;
+            double *states = !gathers_once(t, kDirectStart) ? reinterpret_cast<double *>(zb) : nullptr;
             if (states)
                 DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, nullptr, nullptr, 0, nullptr,
                                             nullptr, states, nullptr, st, dus::ZeroArgs{}, sc.span_samples, nullptr),
@@ -977,7 +980,7 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     const bool blur = p->phys.blur_on != 0;
     const bool fwd = blur || bmode;               // the forward kernel runs
     // the forward runs before a table's adjoint, with it or for it alone
-    auto recorded = [&](const dus::FanTable &t) { return fwd || !gathers_once(t); };
+    auto recorded = [&](const dus::FanTable &t) { return fwd || !gathers_once(t, kStepStart); };
     // the pose accumulators and dL/dZ are cleared by the first forward
     // kernel's wavefronts (when it runs), else by a fill kernel
     const int64_t n_vox = (int64_t)p->vol.nx * p->vol.ny * p->vol.nz;

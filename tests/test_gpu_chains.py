@@ -59,7 +59,7 @@ def test_chains_agree(rays, effects):
 
 # the adjoint of a step that renders no image gathers its rays once, or
 # starts from the records of a forward: ray counts on both sides of the line
-@pytest.mark.parametrize("rays,samples", [(736, 700), (737, 700), (341, 2000), (342, 2000), (5608, 300), (5620, 300)])
+@pytest.mark.parametrize("rays,samples", [(737, 700), (738, 700), (341, 2000), (342, 2000), (7004, 300), (7005, 300)])
 @pytest.mark.parametrize("effects", [False, True])
 def test_adjoint_without_image(rays, samples, effects):
     """With and without the image asked for (with it, the forward runs): the
@@ -87,3 +87,32 @@ def test_adjoint_without_image(rays, samples, effects):
     assert b[0] == pytest.approx(a[0], rel=1e-10)
     assert H.rel_l2(b[1], a[1]) <= 1e-6
     np.testing.assert_allclose(b[2], a[2], rtol=1e-6, atol=1e-6 * np.abs(a[2]).max())
+
+
+@pytest.mark.parametrize("rays,samples", [(1684, 700), (1685, 700), (780, 2000), (781, 2000)])
+@pytest.mark.parametrize("effects", [False, True])
+def test_direct_adjoint_states(rays, samples, effects):
+    """The direct adjoint on both sides of its own line, against the adjoint
+    of the fused step (from the records of a forward)."""
+    from paper_2508_06768_amd.render import FusedStep, Geometry, render, render_backward
+    print("direct adjoint", rays, samples, effects, flush=True)
+    rng = np.random.default_rng(55)
+    Z = torch.from_numpy(rng.uniform(1.4, 1.8, size=(48, 40, 44)).astype(np.float32)).to(DEV)
+    poses = torch.tensor([[21.0, 19.0, 0.0, 0.0, 0.0, 0.0], [20.0, 20.0, 1.0, 0.1, 0.0, 0.1]], device=DEV)
+    fans = [synth.FanSpec(rays, samples, 1.2, 48.0 / samples, 0.5, 0), synth.FanSpec(2, 3, 0.1, 1.0, 0.0, 1)]
+    ph = synth.PhysicsSpec(refl_mode=0, speckle_on=effects, blur_on=effects, seed=5)
+    geom = Geometry(tuple(Z.shape), (1.0, 1.0, 1.0), (0.0, 0.0, 0.0), fans, ph)
+    # target 0: the residual of the fused step is 2 / P times the image
+    bm = render(Z, poses, geom)
+    n = torch.cat([torch.full((f.n_rays * f.n_samples,), float(f.n_rays * f.n_samples), device=DEV) for f in fans])
+    gZ, gp = render_backward(Z, poses, geom, 2.0 * bm / n)
+    step = FusedStep(geom)
+    sZ, sp, img = torch.empty_like(Z), torch.empty((2, 6), device=DEV), torch.empty(geom.total, device=DEV)
+    step.step(Z, poses, torch.zeros(geom.total, device=DEV), bmode=img, grad_Z=sZ, grad_pose=sp)
+    torch.cuda.synchronize()
+    step.close()
+    np.testing.assert_array_equal(img.cpu().numpy(), bm.cpu().numpy())
+    # FP32 residuals formed two ways: a few roundings of 2^-24 each
+    assert H.rel_l2(gZ.cpu().numpy().astype(np.float64), sZ.cpu().numpy().astype(np.float64)) <= 2e-6
+    a, b = gp.cpu().numpy().astype(np.float64), sp.cpu().numpy().astype(np.float64)
+    np.testing.assert_allclose(a, b, rtol=1e-5, atol=1e-5 * np.abs(b).max())
