@@ -1483,8 +1483,9 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
 // box of the volume (neighbouring rays of a fan overlap); the runs go into an
 // LDS copy of that box with LDS atomics, and the box is then flushed with one
 // global atomic per touched voxel, consecutive lanes on consecutive x.  A
-// group whose box does not fit takes its rays in halves (quarters, ...), and
-// a single ray whose box does not fit goes to per-sample global atomics.
+// group whose box does not fit takes its rays in halves (quarters, ...), or
+// at coarse steps its depths, and what still does not fit goes to per-sample
+// global atomics.
 //
 // The box holds FP64: FP64 LDS atomics (ds_add_f64) run at the rate of
 // plain LDS stores on gfx950, FP32 LDS atomics several times slower.  The
@@ -1601,10 +1602,12 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
     // for coarse steps (one sample per voxel and more); the wavefront's
     // first ray decides (the rays of a fan share their step length)
     int spl;
+    bool coarse;
     {
         const double s2 = ray.du[0] * ray.du[0] + ray.du[1] * ray.du[1] + ray.du[2] * ray.du[2];
         spl = (s2 <= 0.35 * 0.35) ? 4 : ((s2 <= 0.7 * 0.7) ? 2 : 1);
         spl = __builtin_amdgcn_readfirstlane(spl);
+        coarse = __builtin_amdgcn_readfirstlane((int)(s2 > 1.2 * 1.2)) != 0;
     }
     const int G = LPR * spl;                     // depths per group (divides LPR kScatterSpl)
     // deterministic mode: 64-bit fixed-point sums (integer adds, in any
@@ -1678,11 +1681,18 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
                 }
             }
         }
-        // A box for all the rays at once, or for halves, quarters, ... of them
-        // where that box would not fit (rays of a coarse fan lie far apart)
-        int part = RB;
-        for (int s0 = 0; s0 < RB;) {
-            const bool mine = (unsigned)(slot - s0) < (unsigned)part;
+        // A box for all the lanes at once, or for halves, quarters, ... of the
+        // rays where that box would not fit (rays of a coarse fan lie far
+        // apart).  At steps over 1.2 voxels for halves and quarters of the
+        // depths: the group is long, and near the probe its rays share cells
+        // that are worth a box; past that its samples share too few for one
+        // (full step's scatter by rays / by depths, us: 12 poses x 40 x 147 at
+        // 1.2 voxels 41 / 28, 18 x 257 x 95 at 1.8 34 / 25, 12 x 287 x 73 at 2.3
+        // 74 / 25; 25 x 82 x 178 at 1.16 37 / 41).
+        const int key = coarse ? ch : slot, all = coarse ? LPR : RB, least = coarse ? min(4, LPR) : 1;
+        int part = all;
+        for (int s0 = 0; s0 < all;) {
+            const bool mine = (unsigned)(key - s0) < (unsigned)part;
             // (opaque, or the weights' products would be held across the loop)
 #pragma unroll
             for (int q = 0; q < kScatterSpl; ++q)
@@ -1703,7 +1713,7 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
             const int rs = bx | 1;
             const int ps = (rs * by) | 1;
             const bool fits = bx <= 64 && by <= CAP && (long long)ps * bz <= CAP;
-            if (!fits && part > 1) {
+            if (!fits && part > least) {
                 part >>= 1;
                 continue;
             }
@@ -2991,9 +3001,12 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
             u += (long long)((t.f[f].n_rays + rb - 1) / rb) * ((t.f[f].n_samples + sg - 1) / sg);
         return u;
     };
-    // 0: automatic.  Eight rays per wavefront, unless even the shortest
-    // segments leave fewer than two wavefronts per SIMD; then two
-    if (scatter_rays == 0) scatter_rays = (units(8, 32) < 2048) ? 2 : 8;
+    // 0: eight rays per wavefront, also where that leaves few wavefronts: a
+    // box of two rays and four times the depths is longer than LDS holds, and
+    // the cells where the rays meet take four times the global atomics (two
+    // rays / eight, us: 2 poses x 46 x 224 24 / 16, 9 x 93 x 142 50 / 23, 23 x 77
+    // x 142 72 / 12, 6 x 488 x 90 150 / 27)
+    if (scatter_rays == 0) scatter_rays = 8;
     int seg = 256 / scatter_rays, seg_shift = 0;
     while (seg < DUS_MAX_SAMPLES && units(scatter_rays, seg) > std::max(wave_target, 1024)) seg *= 2;
     while ((1 << seg_shift) < seg) ++seg_shift;
