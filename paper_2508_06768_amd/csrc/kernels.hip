@@ -1552,8 +1552,7 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
     // depth chunk of this lane, rotated by the ray slot: in one instruction
     // the rays of the wavefront sit at different depths (>= 1 mm apart), so
     // lanes of one LDS atomic rarely meet in one cell
-    constexpr int SH = LPR / RB;
-    const int ch = (ll + slot * SH) % LPR;
+    const int ch = (ll + slot * LPR / RB) % LPR;
     // block -> (fan, depth segment, first ray).  Each fan owns ceil(n_rays /
     // RB) ray blocks.  One-dimensional grid: the fans one after the other,
     // each with its ceil(n_samples / seg) segments of ray blocks (ray blocks
@@ -2982,6 +2981,28 @@ hipError_t launch_pose_reduce(const FanTable &t, const double *pose_part, double
     return hipGetLastError();
 }
 
+// Whether most of a table's samples lie in fans whose scatter does better with
+// boxes of sixteen rays and half the depths: fewer voxels are flushed twice.
+// At least 128 rays, at most 0.65 voxels apart at mid-depth, and steps of at
+// least 0.22 voxels, since shorter ones leave a group of sixteen depths a few
+// cells (eight rays / sixteen, us: 64 poses x 256 x 1024 at 0.25 voxels 140 /
+// 126, 56 x 432 x 72 at 1.7 70 / 45, 43 x 181 x 108 at 0.5 28 / 23; 64 x 256 x 512
+// at 0.2 69 / 84, 64 x 512 x 2048 uneven at 0.12 155 / 185; rays a voxel
+// apart, 61 x 72 x 213, 34 / 41).
+static bool dense_fans(const VolArgs &v, const FanTable &t)
+{
+    const float h = std::min(v.h[0], std::min(v.h[1], v.h[2]));
+    long long all = 0, dense = 0;
+    for (int f = 0; f < t.n; ++f) {
+        const FanRec &r = t.f[f];
+        const long long n = (long long)r.n_rays * r.n_samples;
+        const float mid = r.r0 + 0.5f * r.ds * (float)r.n_samples;
+        all += n;
+        if (r.n_rays >= 128 && r.ds >= 0.22f * h && r.aperture * mid <= 0.65f * h * (float)r.n_rays) dense += n;
+    }
+    return 2 * dense > all;
+}
+
 hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, const FanTable &t,
                           const RayRec *rays, const float *zbar, float *gZ, hipStream_t st,
                           unsigned long long *fix, const double *fscale, int wave_target)
@@ -3001,12 +3022,14 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
             u += (long long)((t.f[f].n_rays + rb - 1) / rb) * ((t.f[f].n_samples + sg - 1) / sg);
         return u;
     };
-    // 0: eight rays per wavefront, also where that leaves few wavefronts: a
+    // 0: sixteen rays per wavefront where most samples lie in dense fans (below),
+    // else eight, also where that leaves few wavefronts: a
     // box of two rays and four times the depths is longer than LDS holds, and
     // the cells where the rays meet take four times the global atomics (two
     // rays / eight, us: 2 poses x 46 x 224 24 / 16, 9 x 93 x 142 50 / 23, 23 x 77
     // x 142 72 / 12, 6 x 488 x 90 150 / 27)
-    if (scatter_rays == 0) scatter_rays = 8;
+    if (scatter_rays == 0) scatter_rays = dense_fans(v, t) ? 16 : 8;
+    else if (scatter_rays == 16) return hipErrorInvalidValue;
     int seg = 256 / scatter_rays, seg_shift = 0;
     while (seg < DUS_MAX_SAMPLES && units(scatter_rays, seg) > std::max(wave_target, 1024)) seg *= 2;
     while ((1 << seg_shift) < seg) ++seg_shift;
@@ -3046,6 +3069,10 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
         break;
     case 8:
         hipLaunchKernelGGL((k_scatter<8>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, xcd_group,
+                           fix, fscale);
+        break;
+    case 16:
+        hipLaunchKernelGGL((k_scatter<16>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, xcd_group,
                            fix, fscale);
         break;
     default:

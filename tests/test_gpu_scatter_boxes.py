@@ -1,6 +1,6 @@
 """The dL/dZ scatter where its LDS box changes form: rays too far apart for
 one box (halves, quarters, single rays), depths too long for a box at steps
-below and above 1.2 voxels, the volume's faces (clamped cells) and the segment and row ends.  Against the
+below and above 1.2 voxels, sixteen rays to a box, the volume's faces (clamped cells) and the segment and row ends.  Against the
 oracle at the suite's 1e-5 bars, at every number of rays per wavefront.
 """
 import numpy as np
@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 FANS = {"dense": (19, 301, 0.3, 0.25), "half": (9, 600, 0.9, 0.1), "quarter": (10, 700, 2.0, 0.08),
         "single": (8, 3000, 3.0, 0.02), "two_per_lane": (13, 130, 0.8, 0.5), "one_per_lane": (11, 65, 1.2, 0.9),
         "no_box": (5, 40, 0.5, 6.0), "below_coarse": (21, 50, 1.5, 1.19), "coarse": (37, 49, 1.5, 1.22),
-        "coarse_parts": (70, 25, 1.0, 2.6), "leaving": (33, 257, 2.8, 0.3)}
+        "coarse_parts": (70, 25, 1.0, 2.6), "sixteen": (128, 41, 1.2, 0.23), "sixteen_part": (139, 33, 1.2, 1.7),
+        "leaving": (33, 257, 2.8, 0.3)}
 
 
 @pytest.mark.parametrize("rays_per_wave", [0, 2, 4, 8])
