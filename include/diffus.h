@@ -328,7 +328,8 @@ typedef struct {
     int32_t bwd_chunk;        /* same for the adjoint: 4 or 8 */
     int32_t xcd_group;        /* consecutive rays kept on one XCD: 1..64 */
     int32_t scatter_rays;     /* neighbouring rays per wavefront (one LDS box) in the dL/dZ scatter:
-                                 2, 4 or 8; 0 (the default) picks 8, or 16 for dense fans */
+                                 2, 4 or 8; 0 (the default) picks 8, 16 for dense fans, or 2 for few
+                                 rays that run on outside the volume */
     int32_t span_samples;     /* rays of at least this many samples are walked by several
                                  wavefronts each, which take consecutive tiles of the ray together
                                  (forward; the plan's adjoint): 1..DUS_MAX_SAMPLES, 0 (the default)

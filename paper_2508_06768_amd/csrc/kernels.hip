@@ -1649,6 +1649,7 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
         // weight) the low word.  Lanes past the segment repeat its last depth.
         int ci[kScatterSpl][3];
         float wf[kScatterSpl][3];
+        bool inside;
         {
             const double kk = (double)min(kl, k_end - 1);
             const int last = min(spl - 1, max(k_end - 1 - kl, 0));
@@ -1667,7 +1668,8 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
                 }
                 in = in && (unsigned)(int)(u >> 32) < top;
             }
-            if (__ballot(!in) != 0ull) {         // uniform: clamped, in FP64
+            inside = __ballot(!in) == 0ull;
+            if (!inside) {                       // uniform: clamped, in FP64
 #pragma unroll
                 for (int q = 0; q < kScatterSpl; ++q) {
                     const Stencil st = stencil_at(v, ray, min(kl + min(q, last), k_end - 1));
@@ -1684,11 +1686,14 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
         // rays where that box would not fit (rays of a coarse fan lie far
         // apart).  At steps over 1.2 voxels for halves and quarters of the
         // depths: the group is long, and near the probe its rays share cells
-        // that are worth a box; past that its samples share too few for one
+        // that are worth a box; past that its samples share too few for one.
+        // (Not where samples lie outside the volume: those are many to a voxel
+        // at its faces, and are summed in FP64 ray by ray.)
         // (full step's scatter by rays / by depths, us: 12 poses x 40 x 147 at
         // 1.2 voxels 41 / 28, 18 x 257 x 95 at 1.8 34 / 25, 12 x 287 x 73 at 2.3
         // 74 / 25; 25 x 82 x 178 at 1.16 37 / 41).
-        const int key = coarse ? ch : slot, all = coarse ? LPR : RB, least = coarse ? min(4, LPR) : 1;
+        const bool deep = coarse && inside;
+        const int key = deep ? ch : slot, all = deep ? LPR : RB, least = deep ? min(4, LPR) : 1;
         int part = all;
         for (int s0 = 0; s0 < all;) {
             const bool mine = (unsigned)(key - s0) < (unsigned)part;
@@ -3003,6 +3008,16 @@ static bool dense_fans(const VolArgs &v, const FanTable &t)
     return 2 * dense > all;
 }
 
+// whether some ray is longer than the volume's diagonal
+static bool runs_outside(const VolArgs &v, const FanTable &t)
+{
+    const float x = v.h[0] * (float)v.nx, y = v.h[1] * (float)v.ny, z = v.h[2] * (float)v.nz;
+    const float diag = sqrtf(x * x + y * y + z * z);
+    for (int f = 0; f < t.n; ++f)
+        if (t.f[f].r0 + t.f[f].ds * (float)t.f[f].n_samples > diag) return true;
+    return false;
+}
+
 hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, const FanTable &t,
                           const RayRec *rays, const float *zbar, float *gZ, hipStream_t st,
                           unsigned long long *fix, const double *fscale, int wave_target)
@@ -3022,13 +3037,18 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
             u += (long long)((t.f[f].n_rays + rb - 1) / rb) * ((t.f[f].n_samples + sg - 1) / sg);
         return u;
     };
-    // 0: sixteen rays per wavefront where most samples lie in dense fans (below),
-    // else eight, also where that leaves few wavefronts: a
+    // 0: sixteen rays per wavefront where most samples lie in dense fans (above);
+    // two where few rays run on outside the volume: their samples there meet in
+    // few voxels, and groups of four times the depths add to them a quarter as
+    // often (35 x 607, 22 x 1297 and 7 x 1434 rays of up to 1600 mm past a volume
+    // of 39 mm: largest error 1e-6 of the largest voxel, 3e-6 with eight); else
+    // eight, also where that leaves few wavefronts: a
     // box of two rays and four times the depths is longer than LDS holds, and
     // the cells where the rays meet take four times the global atomics (two
     // rays / eight, us: 2 poses x 46 x 224 24 / 16, 9 x 93 x 142 50 / 23, 23 x 77
     // x 142 72 / 12, 6 x 488 x 90 150 / 27)
-    if (scatter_rays == 0) scatter_rays = dense_fans(v, t) ? 16 : 8;
+    if (scatter_rays == 0)
+        scatter_rays = (units(8, 32) < 2048 && runs_outside(v, t)) ? 2 : (dense_fans(v, t) ? 16 : 8);
     else if (scatter_rays == 16) return hipErrorInvalidValue;
     int seg = 256 / scatter_rays, seg_shift = 0;
     while (seg < DUS_MAX_SAMPLES && units(scatter_rays, seg) > std::max(wave_target, 1024)) seg *= 2;
