@@ -490,6 +490,10 @@ namespace {
 constexpr int64_t kChainSamples = (int64_t)3 << 20;
 constexpr int64_t kTinySamples = 4096;
 
+// Up to this many loss partials are left to one block of 256 threads (past it
+// they would outlast the pose sums; a launch of 1024 threads sums 16384 in 6 us).
+constexpr int64_t kFoldParts = 4096;
+
 struct PlanShape {
     int fans = 0;           // that render something
     int64_t work = 0;       // ray-samples
@@ -1117,6 +1121,14 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
                     "fixed-point conversion kernel");
     }
     DUS_HIP(mark(DUS_PHASE_FINISH), "event");
+    // a step of one table and few partials sums its loss in a block of the
+    // pose sums' launch
+    const bool with_poses = loss && adj && grad_pose && direct && tabs.size() == 1 && n_part <= kFoldParts;
+    if (with_poses) {
+        tabs[0].loss_part = part;
+        tabs[0].n_part = (int32_t)n_part;
+        tabs[0].loss = loss;
+    }
     if (adj && grad_pose) {
         r0 = 0;
         for (size_t i = 0; i < tabs.size(); ++i) {
@@ -1128,7 +1140,8 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
         DUS_HIP(hipEventRecord(p->side.join, p->side.st), "join event");
         DUS_HIP(hipStreamWaitEvent(st, p->side.join, 0), "join wait");
     }
-    DUS_HIP(dus::launch_finish(part, n_part, loss, acc, poses, n_poses, direct ? nullptr : grad_pose, st),
+    DUS_HIP(dus::launch_finish(part, n_part, with_poses ? nullptr : loss, acc, poses, n_poses,
+                               direct ? nullptr : grad_pose, st),
             "loss and pose kernel");
     DUS_HIP(mark(DUS_NUM_PHASES), "event");
     return DUS_OK;

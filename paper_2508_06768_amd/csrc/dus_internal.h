@@ -72,6 +72,9 @@ struct FanTable {
                             // the forward's records: where to find it (else set up again)
     const float *poses;     // pose sums: with grad_pose, the poses, and where the gradients of the
     float *grad_pose;       // table's poses go (NULL: into the accumulators)
+    const double *loss_part;    // pose sums: with loss, one more block writes there the sum of the n_part
+    double *loss;               // partials at loss_part
+    int32_t n_part;
     FanRec f[kMaxFans];
 };
 

@@ -2147,14 +2147,29 @@ __global__ __launch_bounds__(192) void k_pose_finalize(const double *__restrict_
 
 // One block per fan of a table: the per-ray partials of the adjoint summed
 // (in a fixed order) and, with tab.grad_pose, turned into the pose's gradient
-// at once; without, added into the pose's accumulator.
+// at once; without, added into the pose's accumulator.  With tab.loss, one
+// block more sums a small step's loss partials, which saves it a launch
+// (pose-only step of 4 poses x 296 rays x 127 samples 18.7 -> 15.8 us, full
+// step of 6 x 171 x 729 54 -> 52).
 __global__ __launch_bounds__(256) void k_pose_reduce(FanTable tab, const double *__restrict__ part,
                                                      double *__restrict__ acc)
 {
     __shared__ double s_w[4][kRayPart];
     __shared__ double s_a[kPoseAcc];
-    const FanRec fr = tab.f[blockIdx.x];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if ((int)blockIdx.x == tab.n) {
+        double x[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int i = threadIdx.x; i < tab.n_part; i += 1024) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] += (i + 256 * u < tab.n_part) ? tab.loss_part[i + 256 * u] : 0.0;
+        }
+        const double t = lanes_sum((x[0] + x[1]) + (x[2] + x[3]));
+        if (lane == 0) s_w[wv][0] = t;
+        __syncthreads();
+        if (threadIdx.x == 0) *tab.loss = (s_w[0][0] + s_w[1][0]) + (s_w[2][0] + s_w[3][0]);
+        return;
+    }
+    const FanRec fr = tab.f[blockIdx.x];
     double s[kRayPart];
 #pragma unroll
     for (int c = 0; c < kRayPart; ++c) s[c] = 0.0;
@@ -2982,7 +2997,7 @@ hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const Phys
 hipError_t launch_pose_reduce(const FanTable &t, const double *pose_part, double *pose_acc, hipStream_t st)
 {
     if (t.n <= 0 || t.total_rays <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pose_reduce, dim3(t.n), dim3(256), 0, st, t, pose_part, pose_acc);
+    hipLaunchKernelGGL(k_pose_reduce, dim3(t.n + (t.loss ? 1 : 0)), dim3(256), 0, st, t, pose_part, pose_acc);
     return hipGetLastError();
 }
 

@@ -116,3 +116,32 @@ def test_direct_adjoint_states(rays, samples, effects):
     assert H.rel_l2(gZ.cpu().numpy().astype(np.float64), sZ.cpu().numpy().astype(np.float64)) <= 2e-6
     a, b = gp.cpu().numpy().astype(np.float64), sp.cpu().numpy().astype(np.float64)
     np.testing.assert_allclose(a, b, rtol=1e-5, atol=1e-5 * np.abs(b).max())
+
+
+# the loss of a step without blur has one partial per ray: with the pose
+# sums up to 4096 of them, in a launch of its own past that
+@pytest.mark.parametrize("rays", [1, 255, 257, 1025, 4096, 4097])
+def test_loss_beside_pose_sums(rays):
+    from paper_2508_06768_amd.render import FusedStep, Geometry
+    print("loss beside pose sums", rays, flush=True)
+    rng = np.random.default_rng(57)
+    Z = torch.from_numpy(rng.uniform(1.4, 1.8, size=(24, 20, 22)).astype(np.float32)).to(DEV)
+    poses = torch.tensor([[10.0, 9.0, 0.0, 0.0, 0.0, 0.0]], device=DEV)
+    ph = synth.PhysicsSpec(refl_mode=0, speckle_on=False, blur_on=False, seed=5)
+    geom = Geometry(tuple(Z.shape), (1.0, 1.0, 1.0), (0.0, 0.0, 0.0), [synth.FanSpec(rays, 40, 1.2, 0.4, 0.5, 0)], ph)
+    target = torch.full((geom.total,), 0.05, device=DEV)
+    out = []
+    for with_pose in (True, False):
+        step = FusedStep(geom)
+        loss = torch.full((1,), float("nan"), dtype=torch.float64, device=DEV)
+        bm, gZ, gp = torch.empty(geom.total, device=DEV), torch.empty_like(Z), torch.empty((1, 6), device=DEV)
+        step.step(Z, poses, target, bmode=bm, loss=loss, grad_Z=gZ, grad_pose=gp if with_pose else None)
+        torch.cuda.synchronize()
+        step.close()
+        out.append(loss.item())
+    d = bm.cpu().numpy() - np.float32(0.05)         # the residual is formed in FP32
+    ref = np.mean(d.astype(np.float64) ** 2)
+    # each side sums the same FP64 partials in its own order; against numpy the
+    # rounding of the FP32 square, up to 2^-24 a sample
+    assert out[0] == pytest.approx(out[1], rel=1e-12)
+    assert out[0] == pytest.approx(ref, rel=2e-7)
