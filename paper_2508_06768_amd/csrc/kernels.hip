@@ -1496,11 +1496,12 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
 // Bound by LDS instructions: every 64-bit LDS store or atomic of a wavefront
 // takes about 8 clocks of its CU however many lanes are active (measured), and
 // a group of 256 samples issues about 32 to accumulate and 16 to flush; and by
-// the global atomics where many rays meet (40 of the bench step's 131 us).
-// 64 poses x 256 rays x 1024 samples 139 -> 134 us with half the vector
+// the global atomics where many rays meet (40 of 131 us with eight rays to a
+// box).  64 poses x 256 rays x 1024 samples 139 -> 134 us with half the vector
 // instructions (cells stepped in fixed point, box by register reductions, a
 // flush that steps along one axis), 63 fans of 256 x 256 and one of 64 x 16384
-// 218 -> 101 us with boxes for parts of the rays.
+// 218 -> 101 us with boxes for parts of the rays; 134 -> 129 and 101 -> 94 us
+// with sixteen rays to a box.
 constexpr int kScatterSpl = 4;     // consecutive depths per lane, at most
 
 // floor(a / b) for a >= 0, b >= 1, a + b < 2^21, from rb = rcp(b) (within
@@ -2822,10 +2823,10 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
 
 // automatic forward tile (chunk 0): 8 x 64 samples, unless the table's rays
 // fill 512-sample tiles clearly worse than 256-sample ones.  On full tiles
-// the 4 x 64 tile costs about 7% more per sample (64 poses x 256 x 1024:
-// 164 against 153 us); on the uneven 64-pose batch, whose rays pad to 1.20x
-// their samples in 512-sample tiles and to 1.09x in 256-sample ones, it
-// takes 217 against 229 us.
+// the 4 x 64 tile costs 20% more per sample (64 poses x 256 x 1024: 141
+// against 118 us), so the uneven batch of 64 fans of up to 512 x 2048, whose
+// rays pad to 1.1 times as many samples in the longer tiles, is still faster
+// in those (163 against 189 us); rays of 600 samples pad to 1.33 times.
 // Few rays that share out their tiles take the shorter ones as long as one
 // round of eight holds the ray at least twice over (256 x 1024: 13.6 -> 12.6
 // us; 384 x 1500 in eight 4 x 64 tiles against four of 8 x 64: 20.0 / 16.9).
@@ -2838,7 +2839,7 @@ static int auto_fwd_chunk(const FanTable &t, int span_samples)
         pad4 += r * ((s + 255) / 256) * 256;
         pad8 += r * ((s + 511) / 512) * 512;
     }
-    return (pad8 * 100 > pad4 * 107) ? 4 : 8;
+    return (pad8 * 100 > pad4 * 120) ? 4 : 8;
 }
 
 hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const PhysArgs &p,
