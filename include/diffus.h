@@ -333,7 +333,8 @@ typedef struct {
     int32_t span_samples;     /* rays of at least this many samples are walked by several
                                  wavefronts each, which take consecutive tiles of the ray together
                                  (forward; the plan's adjoint): 1..DUS_MAX_SAMPLES, 0 (the default)
-                                 for 4096 and, where a launch has few rays, for shorter ones too,
+                                 for 4096 (where a launch has few rays, for shorter ones too, and
+                                 where it has many long ones, for none),
                                  -1 for never.  Results do not depend on it, except for
                                  the rounding of the pose gradient and of the fused loss */
 } dus_schedule;

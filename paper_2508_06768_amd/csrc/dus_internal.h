@@ -11,8 +11,8 @@ constexpr int kMaxFans = 64;
 // rays of at least span_samples samples (kSpanSamples by default; <= 0:
 // none) are walked by kSpanWaves wavefronts each, which take consecutive
 // tiles of the ray together (forward and plan adjoint); shorter rays by one
-// wavefront, or at the default by several too where a launch has few rays
-// (few_ray_waves)
+// wavefront.  At the default also shorter rays take several where a launch
+// has few (few_ray_waves), and long ones one where there are many (span_rays)
 constexpr int kSpanSamples = 4096;
 constexpr int kSpanWaves = 8;
 

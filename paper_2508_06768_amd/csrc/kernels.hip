@@ -2727,14 +2727,19 @@ inline int grid_for(long long n, int block)
     return (int)g;
 }
 
-// rays of the fans at the front of a table whose rays are walked by
-// kSpanWaves wavefronts each (a table lists its fans longest first)
+// Rays of the fans at the front of a table whose rays are walked by
+// kSpanWaves wavefronts each (a table lists its fans longest first).  At the
+// default length only up to 512 of them: more fill the chip with one
+// wavefront each (direct adjoint and forward, kSpanWaves / one, us: 512 x 5000
+// 67 + 30 / 80 + 34, 1024 x 5000 132 + 58 / 92 + 36, 3072 x 5000 391 + 187 / 158
+// + 64).
+constexpr int kSpanRays = 512;
 inline int span_rays(const FanTable &t, int span_samples)
 {
     int n = 0;
     if (span_samples <= 0) return 0;
     for (int f = 0; f < t.n && t.f[f].n_samples >= span_samples; ++f) n += t.f[f].n_rays;
-    return n;
+    return (span_samples == kSpanSamples && n > kSpanRays) ? 0 : n;
 }
 
 // adjoint blocks for n rays of w wavefronts each, and how many consecutive

@@ -5,7 +5,8 @@ each ray 2, 4 or 8 wavefronts when the rays are too few to fill the chip.
 With ``span_samples = -1`` every ray has one.  The state and the adjoint
 carried across tiles take the same operations either way, so images, loss and
 the deterministic dL/dZ are the same bit for bit, and the pose gradients
-differ only in the order of their FP64 sums.  Lengths are the edges of one,
+differ only in the order of their FP64 sums; so with rays of 4096 samples and
+more, which take eight up to 512 of them.  Lengths are the edges of one,
 two, four and eight tiles of 256 samples and of 512; ray counts the ends of
 the range.
 """
@@ -32,7 +33,7 @@ def few_case(rays, samples, refl=0) -> synth.Case:
 
 @pytest.mark.parametrize("rays,samples", [(1, 256), (1, 257), (2, 511), (1, 513), (2, 1024), (1, 1025), (1, 2047),
                                           (2, 2049), (1, 4096), (1019, 300), (1020, 300), (507, 1000), (508, 1000),
-                                          (507, 1100), (508, 1100)])
+                                          (507, 1100), (508, 1100), (512, 4100), (513, 4100)])
 def test_few_rays_bit_identical(rays, samples):
     case = few_case(rays, samples, refl=rays % 2)
     print("few rays", rays, samples, flush=True)
