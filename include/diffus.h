@@ -324,7 +324,8 @@ enum {
 typedef struct {
     int32_t fwd_chunk;        /* interfaces per lane per tile, forward: 4, 8 or 16; 0 (the default)
                                  picks 8 per fan table, or 4 when the table's rays fill 512-sample
-                                 tiles more than 20% worse than 256-sample ones */
+                                 tiles more than 20% (a plan's: 7%) worse than 256-sample ones, and
+                                 4 for renders of few rays and steps without an image */
     int32_t bwd_chunk;        /* same for the adjoint: 4 or 8 */
     int32_t xcd_group;        /* consecutive rays kept on one XCD: 1..64 */
     int32_t scatter_rays;     /* neighbouring rays per wavefront (one LDS box) in the dL/dZ scatter:

@@ -1076,8 +1076,11 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
         for (size_t i = 0; i < tabs.size(); ++i) {
             const auto &t = tabs[i];
             const bool rec = recorded(t);
+            // (in the adjoint's 4 x 64 tiles: with others the last place of a
+            // pixel next to a pole, and with it the loss, could differ
+            // between rays gathered once and recorded ones)
             if (rec && !fwd) {
-                DUS_HIP(dus::launch_forward(sc.fwd_chunk, sc.xcd_group, va, pa, t, poses, nullptr, nullptr, 0, zc, nullptr,
+                DUS_HIP(dus::launch_forward(sc.fwd_chunk ? sc.fwd_chunk : 4, sc.xcd_group, va, pa, t, poses, nullptr, nullptr, 0, zc, nullptr,
                                             cst, gain, tst(i), (i == 0) ? zero : dus::ZeroArgs{}, sc.span_samples, side),
                         "forward kernel launch");
                 if (i == 0 && two) DUS_HIP(hipEventRecord(p->cleared, st), "clear event");

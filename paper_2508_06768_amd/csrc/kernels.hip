@@ -2835,16 +2835,20 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
 // Few rays that share out their tiles take the shorter ones as long as one
 // round of eight holds the ray at least twice over (256 x 1024: 13.6 -> 12.6
 // us; 384 x 1500 in eight 4 x 64 tiles against four of 8 x 64: 20.0 / 16.9).
-static int auto_fwd_chunk(const FanTable &t, int span_samples)
+// A plan's forward (step) keeps to the line of 7% and to its own tile for few
+// rays: the last place of a pixel next to a pole depends on the tile, one
+// such pixel can hold most of an FP64 loss (seen to move it by 2e-7), and the
+// step gains 1% at most.
+static int auto_fwd_chunk(const FanTable &t, int span_samples, bool step)
 {
-    if (longest_ray(t) <= 1024 && few_ray_waves(t, 256, span_samples)) return 4;
+    if (!step && longest_ray(t) <= 1024 && few_ray_waves(t, 256, span_samples)) return 4;
     long long pad4 = 0, pad8 = 0;
     for (int f = 0; f < t.n; ++f) {
         const long long r = t.f[f].n_rays, s = t.f[f].n_samples;
         pad4 += r * ((s + 255) / 256) * 256;
         pad8 += r * ((s + 511) / 512) * 512;
     }
-    return (pad8 * 100 > pad4 * 120) ? 4 : 8;
+    return (pad8 * 100 > pad4 * (step ? 107 : 120)) ? 4 : 8;
 }
 
 hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const PhysArgs &p,
@@ -2853,7 +2857,7 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
                           hipStream_t st, const ZeroArgs &zero, int span_samples, const SideStream *side)
 {
     if (t.total_rays <= 0) return hipSuccess;
-    if (chunk == 0) chunk = auto_fwd_chunk(t, span_samples);
+    if (chunk == 0) chunk = auto_fwd_chunk(t, span_samples, zcar != nullptr);
     if (chunk != 4 && chunk != 8 && chunk != 16) return hipErrorInvalidValue;
     // the rays of the table's long fans (its first ones: a table lists its
     // fans longest first) get kSpanWaves wavefronts each, the rest one; all
