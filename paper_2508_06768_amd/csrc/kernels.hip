@@ -1224,7 +1224,15 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
         __builtin_amdgcn_s_setprio(0);
         ray_sync<W>();
 
-        if (FROM != kRecords) chunk_gains<C, SPK>(p, gk, k0, t0, j, fr.speckle_id, postc, s_xir, gn);
+        if (FROM != kRecords) {
+            chunk_gains<C, SPK>(p, gk, k0, t0, j, fr.speckle_id, postc, s_xir, gn);
+            // past the ray's end the depth fraction exceeds 1 and its power may
+            // overflow: no gain there (0 times infinity would reach the sums)
+            if (k0 + C > S) {
+#pragma unroll
+                for (int i = 0; i < C; ++i) gn[i] = (k0 + i < S) ? gn[i] : 1.0f;
+            }
+        }
 
         // the chunk's samples, those on either side of it, and its interfaces
         double z[C], rho[C], dq[C];
