@@ -1295,9 +1295,11 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
             be[i] = eb * e[i];
             lsum += be[i];
             const double tom = tt * om;
-            // below 1e-150 O (about t^2 dl/de) over t is far under FP32's
-            // smallest number, and near t's own underflow it is 0 / 0
-            const double inv = (tom < 1e-150) ? 0.0 : rcp64(tom);
+            // for |t| below 1e-150 O (about t^2 dl/de) over t is far under FP32's
+            // smallest number, and near t's own underflow it is 0 / 0.  (t is
+            // negative past an interface with |R| > 1, which impedances of
+            // both signs give.)
+            const double inv = (fabs(tt) < 1e-150) ? 0.0 : rcp64(tom);
             const double N = fma(onep * pp, pp, fma(w, w, -1.0));
             co[i] = dq[i] * inv * N;
             cl[i] = 2.0 * dq[i] * fma(r * tt, inv, w * q);

@@ -1,7 +1,8 @@
 """The adjoint where its arithmetic could leave the finite numbers or lose
-them: lanes past a ray's end under a steep speckle law.  Against the oracle,
-through the direct adjoint (whole rays, and rays with a forward's states) and
-the fused step without an image.
+them: lanes past a ray's end under a steep speckle law, a negative or an
+underflowing determinant.  Against the oracle, through the direct adjoint
+(whole rays, and rays with a forward's states) and the fused step without an
+image.
 """
 import numpy as np
 import pytest
@@ -56,3 +57,41 @@ def test_steep_speckle_past_the_end(samples, gamma):
         assert H.rel_l2(gZ, rV) <= tol
         assert np.abs(gp - rp).max() <= tol * np.linalg.norm(rp)
     assert loss == pytest.approx(ref_loss, rel=tol, abs=0.0)
+
+
+# one tile, several wavefronts a ray, and rays with a forward's states
+@pytest.mark.parametrize("samples", [60, 900, 3000])
+def test_negative_impedance(samples):
+    """Impedances of both signs (an optimiser's unclamped step): behind an
+    interface with |R| > 1 the determinant is negative.  (The signed
+    convention; |R| has no derivative that both sides agree on there.)"""
+    print("negative impedance", samples, flush=True)
+    Z = synth.brain_volume(5, 32, 1.0, semi_range=(3.0, 9.0))
+    Z[12:14, 15, 15] = -0.2
+    case = synth.Case("negative", Z, (1.0,) * 3, (0.0,) * 3, np.array([[15.0, 15.0, 1.0, 0.0, 0.0, 0.0]], np.float32),
+                      [synth.FanSpec(3, samples, 0.05, 25.0 / samples, 0.5, 0)],
+                      synth.PhysicsSpec(refl_mode=1, speckle_on=False, blur_on=False, seed=4))
+    w = np.random.default_rng(samples).standard_normal(3 * samples).astype(np.float32)
+    got, loss = _adjoints(case, w)
+    refs, ref_loss = _references(case, w)
+    for (gZ, gp), (rV, rp) in zip(got, refs):
+        assert H.rel_l2(gZ, rV) <= 1e-5
+        assert np.abs(gp - rp).max() <= 1e-5 * np.linalg.norm(rp)
+    assert loss == pytest.approx(ref_loss, rel=1e-5)
+
+
+def test_absorbed_ray():
+    """A ray whose amplitude underflows on the way: finite gradients, and
+    those of the part that is left agree with the oracle."""
+    print("absorbed ray", flush=True)
+    Z = synth.brain_volume(5, 32, 1.0, semi_range=(3.0, 9.0))
+    case = synth.Case("absorbed", Z, (1.0,) * 3, (0.0,) * 3, np.array([[15.0, 15.0, 1.0, 0.0, 0.0, 0.0]], np.float32),
+                      [synth.FanSpec(3, 1500, 0.05, 0.02, 0.5, 0)],
+                      synth.PhysicsSpec(refl_mode=1, speckle_on=False, blur_on=False, seed=4, alpha=200.0, freq=7.0))
+    w = np.random.default_rng(7).standard_normal(3 * 1500).astype(np.float32)
+    got, _ = _adjoints(case, w)
+    refs, _ = _references(case, w)
+    for (gZ, gp), (rV, rp) in zip(got, refs):
+        assert np.isfinite(gZ).all() and np.isfinite(gp).all()
+        assert H.rel_l2(gZ, rV) <= 1e-5
+        assert np.abs(gp - rp).max() <= 1e-5 * np.linalg.norm(rp)
