@@ -1508,7 +1508,7 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
 // a group of 256 samples issues about 32 to accumulate and 16 to flush; and by
 // the global atomics where many rays meet (40 of 131 us with eight rays to a
 // box).  64 poses x 256 rays x 1024 samples 139 -> 134 us with half the vector
-// instructions (cells stepped in fixed point, box by register reductions, a
+// instructions (no clamps inside the volume, box by register reductions, a
 // flush that steps along one axis), 63 fans of 256 x 256 and one of 64 x 16384
 // 218 -> 101 us with boxes for parts of the rays; 134 -> 129 and 101 -> 94 us
 // with sixteen rays to a box.
@@ -1527,13 +1527,6 @@ template <int RB>
 struct ScatterBox {
     static constexpr int cap = RB == 2 ? 4096 : (RB == 4 ? 2048 : 1024);   // FP64 entries
 };
-
-// voxel coordinate in 32.32 fixed point (floor and fraction; rounded down)
-__device__ __forceinline__ long long to_fixed(double u)
-{
-    const unsigned lo = (unsigned)(__builtin_amdgcn_fract(u) * 0x1p32);
-    return (long long)(((unsigned long long)(unsigned)(int)floor(u) << 32) | lo);
-}
 
 // smallest value over the wavefront (every lane active), in a scalar register
 __device__ __forceinline__ int wave_min_int(int x)
@@ -1595,14 +1588,12 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
     const int k_end = min(S, k_begin + seg);
     // RB rays per wavefront, their geometry as the adjoint set it up
     Ray ray;
-    long long step[3];
     {
         const RayRec &r = rays[fr.ray_begin + jr];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             ray.u0[a] = r.u0[a];
             ray.du[a] = r.du[a];
-            step[a] = to_fixed(r.du[a]);
         }
     }
     const float *zrow = zbar + fr.out_offset + (long long)jr * S;
@@ -1653,45 +1644,24 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
         if (k0 + G < k_end) load(kl + G, zn);
         if (__ballot(zb[0] != 0.0f || zb[1] != 0.0f || zb[2] != 0.0f || zb[3] != 0.0f) == 0ull)
             continue;                            // nothing to scatter in this group (uniform)
-        // Cells and weights of the lane's depths.  Inside the volume (every
-        // lane's first and last depth: the position is affine) they step in
-        // 32.32 fixed point from the first depth's FP64 position: the cell is
-        // the high word, the fraction (within 2^-30 of FP64's, and FP32 as a
-        // weight) the low word.  Lanes past the segment repeat its last depth.
+        // Cells and weights of the lane's depths, from their FP64 positions;
+        // without the clamps where every lane's first and last depth, and so
+        // (the position is affine) all between, lie inside the volume.  Lanes
+        // past the segment repeat its last depth.
         int ci[kScatterSpl][3];
         float wf[kScatterSpl][3];
-        bool inside;
-        {
-            const double kk = (double)min(kl, k_end - 1);
-            const int last = min(spl - 1, max(k_end - 1 - kl, 0));
-            const int n[3] = {v.nx, v.ny, v.nz};
-            bool in = true;
+        const int kf = min(kl, k_end - 1), kb = min(kl + spl - 1, k_end - 1);
+        const bool inside = __ballot(!segment_inside(v, ray, kf, kb)) == 0ull;
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                long long u = to_fixed(fma(kk, ray.du[a], ray.u0[a]));
-                const unsigned top = (unsigned)(n[a] - 1);
-                in = in && (unsigned)(int)(u >> 32) < top;
-#pragma unroll
-                for (int q = 0; q < kScatterSpl; ++q) {
-                    ci[q][a] = (int)(u >> 32);
-                    wf[q][a] = (float)(unsigned)(u & 0xffffffffll) * 0x1p-32f;
-                    if (q < last) u += step[a];
-                }
-                in = in && (unsigned)(int)(u >> 32) < top;
-            }
-            inside = __ballot(!in) == 0ull;
-            if (!inside) {                       // uniform: clamped, in FP64
-#pragma unroll
-                for (int q = 0; q < kScatterSpl; ++q) {
-                    const Stencil st = stencil_at(v, ray, min(kl + min(q, last), k_end - 1));
-                    ci[q][0] = st.ix;
-                    ci[q][1] = st.iy;
-                    ci[q][2] = st.iz;
-                    wf[q][0] = (float)st.fx;
-                    wf[q][1] = (float)st.fy;
-                    wf[q][2] = (float)st.fz;
-                }
-            }
+        for (int q = 0; q < kScatterSpl; ++q) {
+            const int k = min(kf + q, kb);
+            const Stencil st = inside ? stencil_at<true>(v, ray, k) : stencil_at<false>(v, ray, k);
+            ci[q][0] = st.ix;
+            ci[q][1] = st.iy;
+            ci[q][2] = st.iz;
+            wf[q][0] = (float)st.fx;
+            wf[q][1] = (float)st.fy;
+            wf[q][2] = (float)st.fz;
         }
         // A box for all the lanes at once, or for halves, quarters, ... of the
         // rays where that box would not fit (rays of a coarse fan lie far
