@@ -109,6 +109,15 @@ __device__ __forceinline__ double rcp64(double b)
     return fma(fma(-b, r, 1.0), r, r);
 }
 
+// a / b correctly rounded but for the last place, from ib = rcp64(b): the
+// quotient's residual corrects it (as it stands, rcp64 is good to 2^-48.7;
+// next to a pole of the echo the recurrence magnifies that)
+__device__ __forceinline__ double quot64(double a, double b, double ib)
+{
+    const double q = a * ib;
+    return fma(fma(-b, q, a), ib, q);
+}
+
 // partial unroll of the sample-gather loops: enough independent gathers in
 // flight without holding every tile sample in registers
 #ifndef GATHER_UNROLL
@@ -932,7 +941,7 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
                 // the volume and the images in the caches
                 if ((i % kStateStride) == 0 && srow && k < S && (k > 0 || zcar)) {
                     const double iv = rcp64(v1);
-                    const double2_u st = {v0 * iv, D * iv * iv};
+                    const double2_u st = {quot64(v0, v1, iv), quot64(quot64(D, v1, iv), v1, iv)};
                     __builtin_nontemporal_store(st, reinterpret_cast<double2_u *>(srow + k));
                 }
                 const double r = rho[i];
@@ -1266,8 +1275,8 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
             }
             const double v0 = fma(c0, X.a, c1 * X.c), v1 = fma(c0, X.b, c1 * X.d);
             const double iv = rcp64(v1);
-            w = v0 * iv;
-            tt = cD * xd * iv * iv;
+            w = quot64(v0, v1, iv);
+            tt = quot64(quot64(cD * xd, v1, iv), v1, iv);
         }
 
         // walk down the chunk: every interface's pixel e and be = e dl/de, and
@@ -1280,7 +1289,8 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
         for (int i = 0; i < C; ++i) {
             const double r = rho[i];
             const double pp = fma(w, r, 1.0);
-            const double q = rcp64(pp);
+            double q = rcp64(pp);
+            q = fma(fma(-pp, q, 1.0), q, q);      // (carried on in w: to the last place)
             const double r2 = r * r, om = 1.0 - r2;
             const double x = tt * q;
             e[i] = r * x;
