@@ -198,6 +198,10 @@ struct Ray {
     // normal T = R (cz, 0, -sx) and the fan plane's normal N = R (0, 1, 0),
     // each component over the voxel spacing of its axis
     double bd[3], bt[3], bn[3];
+    // set_base: the voxel that VolArgs::Z points to after it, and whether all of
+    // the ray's samples lie within 4 GiB of it
+    unsigned first;
+    bool narrow;
 };
 
 // wave_uniform: every lane of the wavefront traces the same ray (its
@@ -351,24 +355,50 @@ __device__ __forceinline__ double lerp(double a, double b, double t) { return fm
 // two neighbouring voxels, at any multiple of 4 bytes
 typedef float float2_u __attribute__((ext_vector_type(2), aligned(4)));
 
-// voxels idx and idx + 1 of the row Z points into.  NARROW: the volume spans
-// less than 4 GiB, so the offset is 32 bits beside a scalar base and the four
-// rows of a stencil share it (a 64-bit address per row takes an add each).
-template <bool NARROW>
-__device__ __forceinline__ float2_u voxel_pair(const float *__restrict__ Z, int idx)
+// Gathers address the volume from Z with 32-bit offsets (a 64-bit address per
+// row takes an add each).  A volume of up to 4 GiB is within reach from its
+// start; in a larger one Z moves to the lowest slice the ray's samples touch,
+// which serves if they span no more than 4 GiB (`narrow`; else, and where
+// tiles are clamped, the offsets have 64 bits).  1100 x 1024 x 1024 voxels, 16
+// poses x 256 x 1024, every tile clamped with 64 bits / so: forward 102 / 89 us,
+// pose adjoint 210 / 185; inside with 64 bits 102 / 213.
+__host__ __device__ inline bool in_reach(const VolArgs &v) { return (long long)v.nx * v.ny * v.nz <= (1ll << 30); }
+
+__device__ __forceinline__ void set_base(VolArgs &v, Ray &ray, int S)
 {
-    if (NARROW)
-        return *reinterpret_cast<const float2_u *>(reinterpret_cast<const char *>(Z) + ((unsigned)idx << 2));
-    return *reinterpret_cast<const float2_u *>(Z + idx);
+    ray.first = 0;
+    ray.narrow = true;
+    if (in_reach(v)) return;
+    const int sxy = v.nx * v.ny;
+    int za, zb;
+    double f;
+    axis_cell<false>(ray.u0[2], v.nz, za, f);
+    axis_cell<false>(fma((double)(S - 1), ray.du[2], ray.u0[2]), v.nz, zb, f);
+    const int lo = __builtin_amdgcn_readfirstlane(min(za, zb)), hi = __builtin_amdgcn_readfirstlane(max(za, zb));
+    ray.first = (unsigned)lo * (unsigned)sxy;
+    ray.narrow = (long long)(hi + 2 - lo) * sxy <= (1ll << 30);
+    v.Z += ray.first;
+}
+
+// voxels idx and idx + 1 of the row that Z points into, `first` voxels on
+// (NARROW: 32-bit offsets)
+template <bool NARROW>
+__device__ __forceinline__ float2_u voxel_pair(const float *__restrict__ Z, int idx, unsigned first)
+{
+    if (NARROW)         // (the subtraction goes with the shift)
+        return *reinterpret_cast<const float2_u *>(reinterpret_cast<const char *>(Z) +
+                                                   (((unsigned)idx << 2) - (first << 2)));
+    return *reinterpret_cast<const float2_u *>(Z + ((unsigned)idx - first));
 }
 
 // trilinear value (lerp along x, then y, then z), FP64 from FP32 corners
 template <bool NARROW = false>
 __device__ __forceinline__ double trilinear(const float *__restrict__ Z, int nx, int sxy,
-                                            const Stencil &s, double *grad)
+                                            const Stencil &s, double *grad, unsigned first = 0)
 {
-    const float2_u p00 = voxel_pair<NARROW>(Z, s.idx), p10 = voxel_pair<NARROW>(Z + nx, s.idx);
-    const float2_u p01 = voxel_pair<NARROW>(Z + sxy, s.idx), p11 = voxel_pair<NARROW>(Z + sxy + nx, s.idx);
+    const float2_u p00 = voxel_pair<NARROW>(Z, s.idx, first), p10 = voxel_pair<NARROW>(Z + nx, s.idx, first);
+    const float2_u p01 = voxel_pair<NARROW>(Z + sxy, s.idx, first);
+    const float2_u p11 = voxel_pair<NARROW>(Z + sxy + nx, s.idx, first);
     const double c000 = p00.x, c100 = p00.y;
     const double c010 = p10.x, c110 = p10.y;
     const double c001 = p01.x, c101 = p01.y;
@@ -584,7 +614,7 @@ __device__ __forceinline__ double gather_tile_body(const VolArgs &v, const Ray &
         const int k = t0 + i;
         const Stencil st = stencil_at<INSIDE>(v, ray, min(k, S - 1));
         double gu[3];
-        z = trilinear<INSIDE>(v.Z, v.nx, sxy, st, KEEPG ? gu : nullptr);
+        z = trilinear<INSIDE>(v.Z, v.nx, sxy, st, KEEPG ? gu : nullptr, ray.first);
         s_z[zi(i)] = z;
         if (k == 0) s_z[zi(-1)] = z;
         if (KEEPG) {
@@ -616,10 +646,9 @@ __device__ __forceinline__ double gather_tile(const VolArgs &v, const Ray &ray, 
                                               float *s_g = nullptr)
 {
     // a tile whose samples all lie inside the volume skips the clamps, and
-    // takes 32-bit offsets in a volume below 4 GiB (the ray is the same on
-    // every lane, so the branch is uniform)
-    const bool narrow = (long long)v.nx * v.ny * v.nz < (1ll << 30);
-    if (narrow && segment_inside(v, ray, t0, min(t0 + 64 * C - 1, S - 1)))
+    // takes 32-bit offsets where they reach (the ray is the same on every lane,
+    // so the branch is uniform)
+    if (ray.narrow && segment_inside(v, ray, t0, min(t0 + 64 * C - 1, S - 1)))
         return gather_tile_body<C, KEEPG, true, W>(v, ray, t0, S, lane, s_z, s_g);
     return gather_tile_body<C, KEEPG, false, W>(v, ray, t0, S, lane, s_z, s_g);
 }
@@ -855,6 +884,7 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
     Ray ray;
     setup_ray(v, p, fr, poses, j, ray);
     if (tab.geom && threadIdx.x == 0) store_geom(ray, tab.geom + g);
+    set_base(v, ray, S);
     const bool absm = (p.refl == 0);
     const double sgn = absm ? 1.0 : -1.0;
     const double a2 = ray.a2;
@@ -874,7 +904,7 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
         const bool act = (W == 1) || (t0 < S);      // uniform over the wavefront
         if (W > 1 && act && t0 > 0) {
             const Stencil st = stencil_at<false>(v, ray, t0 - 1);
-            zprev = trilinear(v.Z, v.nx, v.nx * v.ny, st, nullptr);
+            zprev = trilinear(v.Z, v.nx, v.nx * v.ny, st, nullptr, ray.first);
         }
         if (act) {
             if (lane == 0 && t0 > 0) s_z[zi(-1)] = zprev;
@@ -1105,8 +1135,11 @@ __device__ __forceinline__ void load_chunk(const float *__restrict__ row, int k0
 
 enum { kRecords = 0, kRows = 1, kWholeRay = 2 };
 
-template <int C, bool SPK, bool FUSED, int W, int FROM>
-__global__ __launch_bounds__(64 * adjoint_waves(W), (C == 4 && W == 1 && FROM == kRecords && !FUSED) ? 4 : 1)
+// NEAR: the volume lies within 4 GiB (in_reach), known at the launch: the
+// recorded one-wavefront instances are short of scalar registers for a base of
+// their own (pose-only step of 32 x 384 x 1536: 309 us, 317 with it).
+template <int C, bool SPK, bool FUSED, int W, int FROM, bool NEAR = false>
+__global__ __launch_bounds__(64 * adjoint_waves(W), (C == 4 && W == 1 && FROM == kRecords && !FUSED && NEAR) ? 4 : 1)
 void k_backward(VolArgs v, PhysArgs p, FanTable tab,
                                                  const float *__restrict__ poses,
                                                  RayRec *__restrict__ rays_out,
@@ -1154,6 +1187,12 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
     Ray ray;
     if (FROM == kRecords) load_geom(fr, geom + g, ray);
     else setup_ray(v, p, fr, poses, j, ray);
+    if (NEAR) {
+        ray.first = 0;
+        ray.narrow = in_reach(v);       // (a constant here costs six spilled registers: 138 -> 151 us)
+    } else {
+        set_base(v, ray, S);
+    }
     if (rays_out && lane == 0 && wv == 0) {
         // the ray's geometry for the scatter
         RayRec r;
@@ -1208,7 +1247,7 @@ void k_backward(VolArgs v, PhysArgs p, FanTable tab,
                     zm = zcar[crec + t0 / kCarryBlock];
                 } else {
                     const Stencil st = stencil_at<false>(v, ray, t0 - 1);
-                    zm = trilinear(v.Z, v.nx, v.nx * v.ny, st, nullptr);
+                    zm = trilinear(v.Z, v.nx, v.nx * v.ny, st, nullptr, ray.first);
                 }
             }
         }
@@ -2881,8 +2920,9 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
     return e;
 }
 
-#define DUS_BWD_LAUNCH(CH, SPK, FUSED, WV, FROM, NG, TAB, STR)                                    \
-    hipLaunchKernelGGL((k_backward<CH, SPK, FUSED, WV, FROM>), dim3(ray_blocks(WV, NG)), dim3(64 * adjoint_waves(WV)), \
+#define DUS_BWD_LAUNCH(CH, SPK, FUSED, WV, FROM, NG, TAB, STR) DUS_BWD_LAUNCH_(CH, SPK, FUSED, WV, FROM, false, NG, TAB, STR)
+#define DUS_BWD_LAUNCH_(CH, SPK, FUSED, WV, FROM, NEAR, NG, TAB, STR)                             \
+    hipLaunchKernelGGL((k_backward<CH, SPK, FUSED, WV, FROM, NEAR>), dim3(ray_blocks(WV, NG)), dim3(64 * adjoint_waves(WV)), \
                        0, STR, v, p, TAB, poses, zbar ? rays : nullptr, gsrc, target, zbar, pose_acc ? pose_part : nullptr, \
                        loss, zcar, reinterpret_cast<const float *>(states), t.geom, gain, block_group(WV, xcd_group))
 
@@ -2897,9 +2937,11 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
             else DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, kRecords, n_span, t, sst);       \
         }                                                                                      \
         if (n_one > 0) {                                                                       \
-            if (fused) DUS_BWD_LAUNCH(CH, false, true, 1, kRecords, t.total_rays, t1, st);               \
+            if (fused && in_reach(v)) DUS_BWD_LAUNCH_(CH, false, true, 1, kRecords, true, t.total_rays, t1, st); \
+            else if (fused) DUS_BWD_LAUNCH(CH, false, true, 1, kRecords, t.total_rays, t1, st);         \
             else if (spk) DUS_BWD_LAUNCH(CH, true, false, 1, kRows, t.total_rays, t1, st);            \
             else if (!zcar) DUS_BWD_LAUNCH(CH, false, false, 1, kRows, t.total_rays, t1, st); \
+            else if (in_reach(v)) DUS_BWD_LAUNCH_(CH, false, false, 1, kRecords, true, t.total_rays, t1, st); \
             else DUS_BWD_LAUNCH(CH, false, false, 1, kRecords, t.total_rays, t1, st);                    \
         }                                                                                      \
         break;
