@@ -484,11 +484,14 @@ struct dus_plan {
 
 namespace {
 
-// Plans of this many ray-samples or more run two chains of launches, and so
-// do the smallest: too few samples to be of use to a program, they keep the
-// path within reach of the host-side tests that walk its every launch.
+// Plans of this many ray-samples or more run two chains of launches.  (A build
+// of this file under AddressSanitizer holds no kernels: it takes every plan of
+// two fans as large, so that plans of a few samples walk both chains.)
+#ifdef __SANITIZE_ADDRESS__
+constexpr int64_t kChainSamples = 0;
+#else
 constexpr int64_t kChainSamples = (int64_t)3 << 20;
-constexpr int64_t kTinySamples = 4096;
+#endif
 
 // Up to this many loss partials are left to one block of 256 threads (past it
 // they would outlast the pose sums; a launch of 1024 threads sums 16384 in 6 us).
@@ -527,7 +530,7 @@ PlanShape plan_shape(const dus_plan *p)
 bool plan_two_chains(const dus_plan *p)
 {
     const PlanShape s = plan_shape(p);
-    return !(s.fans < 2 || (s.work < kChainSamples && s.work >= kTinySamples) || s.long_rays ||
+    return !(s.fans < 2 || s.work < kChainSamples || s.long_rays ||
              (p->flags & (DUS_PLAN_DETERMINISTIC | DUS_PLAN_ONE_STREAM)));
 }
 
