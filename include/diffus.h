@@ -315,9 +315,10 @@ enum {
                                    instead of FP32 atomics; costs 8 B per voxel of workspace */
     DUS_PLAN_ONE_STREAM = 16   /* every launch on the step's stream, the fans in tables of up to 64
                                   (by default a plan of two or more fans and at least 3 * 2^20
-                                  ray-samples runs them as two chains of launches, half the fans
-                                  each, on the step's stream and a second one, and long rays'
-                                  launches run beside the others) */
+                                  ray-samples, or of more than 64 fans (384 if pose-only), runs
+                                  them as two chains of launches, half the fans each, on the
+                                  step's stream and a second one, and long rays' launches run
+                                  beside the others) */
 };
 
 /* Ray-to-wavefront schedule; 0 fields select the library default. */
@@ -371,11 +372,11 @@ int dus_plan_get_schedule(const dus_plan *plan, dus_schedule *sched);
 /*
  * One fused step of the plan (Sec. 2.3-2.4 forward, MSE, adjoint; see above)
  * on `stream`.  Unless the plan was created with DUS_PLAN_ONE_STREAM, large
- * plans and plans with long rays also run launches on the plan's second
- * stream (two chains of launches, or the long rays' launches), forked from
+ * plans, plans of many fans and plans with long rays also run launches on the
+ * plan's second stream (two chains of launches, or the long rays' launches), forked from
  * `stream` and joined back into it before the step's last launch, so the
- * step is ordered on `stream` all the same.  Such a step comes from a HIP
- * graph: the first call, and any call whose pointers or workspace size
+ * step is ordered on `stream` all the same.  Such a step (but for that of a
+ * plan of many small fans) comes from a HIP graph: the first call, and any call whose pointers or workspace size
  * differ from the previous call's, captures a new one; the others replay
  * it.  The other plans launch their kernels directly.  Two steps of one plan must not run at the same time.  Z and poses
  * as for dus_render_bmode; the workspace has at least

@@ -193,8 +193,11 @@ std::vector<dus::FanTable> build_tables(const dus_fan *fans, int32_t n_poses, bo
         int64_t total = 0;
         for (int i : by_work) total += work(i);
         int64_t load[2] = {-total / 64, 0};
+        // (no group needs a table more than half the fans do: 65 and 63 of 128
+        // equal fans would take three)
+        const size_t most = (by_work.size() + 2 * dus::kMaxFans - 1) / (2 * dus::kMaxFans) * dus::kMaxFans;
         for (int i : by_work) {
-            const int h = (load[1] < load[0]) ? 1 : 0;
+            const int h = (half[0].size() == most || (load[1] < load[0] && half[1].size() < most)) ? 1 : 0;
             half[h].push_back(i);
             load[h] += work(i);
         }
@@ -515,22 +518,33 @@ PlanShape plan_shape(const dus_plan *p)
     return s;
 }
 
+// Plans of many small fans: more than one fan table, or with poses alone more
+// than six.
+bool many_tables(const dus_plan *p, int fans)
+{
+    const int tables = (fans + dus::kMaxFans - 1) / dus::kMaxFans;
+    return tables > ((p->flags & DUS_PLAN_POSE_ONLY) ? 6 : 1);
+}
+
 // Whether a plan's step runs as two chains of launches on two streams, the
 // fans split in two groups of about equal work, so that one chain's kernels
 // fill the other's tails: not for the deterministic plan (one chain), nor
 // for a plan held to one stream, nor when some ray is long enough for
 // several wavefronts (its launches take the second stream), nor for a
-// single fan, nor for small plans: the second chain's start and join cost
-// more there than its overlap saves.  Two chains (from a graph) against one
-// (launched directly), full step in us: 6 poses x 310 x 339 (0.6 M samples)
-// 84 / 52, 55 x 40 x 946 (2.1 M) 99 / 93, 12 x 439 x 935 (4.9 M) 149 / 158,
-// 64 x 256 x 1024 (16.8 M) 422 / 436; between 2 M and 3 M one chain wins by 4%
-// in the mean of 15 shapes, between 3 M and 5 M it loses 1% in that of 12 and
-// 5% at the worst.
+// single fan, nor for small plans of few launches: the second chain's start
+// and join cost more there than its overlap saves.  Two chains against one,
+// full step in us: 6 poses x 310 x 339 (0.6 M samples) 84 / 52, 55 x 40 x 946
+// (2.1 M) 99 / 93, 12 x 439 x 935 (4.9 M) 149 / 158, 64 x 256 x 1024 (16.8 M)
+// 422 / 436; between 2 M and 3 M one chain wins by 4% in the mean of 15
+// shapes, between 3 M and 5 M it loses 1% in that of 12 and 5% at the worst.
+// Small fans by the hundred are launches that leave most of the chip idle,
+// about 12 us each in one chain (8 with poses alone): 100 poses x 8 x 64 137 /
+// 103, 256 x 16 x 200 291 / 190, 1000 x 8 x 64 1034 / 563; poses alone, 129 x 16
+// x 200 50 / 74, 400 x 16 x 200 118 / 118, 640 x 16 x 200 170 / 138.
 bool plan_two_chains(const dus_plan *p)
 {
     const PlanShape s = plan_shape(p);
-    return !(s.fans < 2 || s.work < kChainSamples || s.long_rays ||
+    return !(s.fans < 2 || (s.work < kChainSamples && !many_tables(p, s.fans)) || s.long_rays ||
              (p->flags & (DUS_PLAN_DETERMINISTIC | DUS_PLAN_ONE_STREAM)));
 }
 
@@ -540,11 +554,14 @@ bool plan_two_chains(const dus_plan *p)
 // launched directly).  One chain of launches is cheaper without: a graph's
 // own start and end cost about 5 us (3 poses x 106 x 344: 25 / 17 us, 64 x
 // 256 x 1024 on one stream 440 / 436), as much time on the host as its
-// launches take (20 / 13-22 us), and a capture for new buffers.
+// launches take (20 / 13-22 us), and a capture for new buffers; nor is one
+// captured for two chains of small fans, where it saves 10 to 20 us a step and
+// costs some hundreds for new buffers.
 bool plan_uses_graph(const dus_plan *p)
 {
     if (p->flags & DUS_PLAN_NO_GRAPH) return false;
-    return p->two_chains || (!(p->flags & DUS_PLAN_ONE_STREAM) && plan_shape(p).long_rays);
+    const PlanShape s = plan_shape(p);
+    return (p->two_chains && s.work >= kChainSamples) || (!(p->flags & DUS_PLAN_ONE_STREAM) && s.long_rays);
 }
 
 }  // namespace

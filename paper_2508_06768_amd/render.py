@@ -377,7 +377,8 @@ class FusedStep:
     (``dus_plan``).  ``deterministic``: dL/dZ bit-identical from step to step;
     ``one_stream``: every launch on the caller's stream (by default the fans
     of a large plan run as two chains of launches on two streams, replayed
-    from a captured HIP graph unless ``graph`` is False)."""
+    from a captured HIP graph unless ``graph`` is False, and so do, without a
+    graph, those of a small plan of many fans)."""
 
     def __init__(self, geom: Geometry, pose_only: bool = False, zero_grad_z: bool = True,
                  graph: bool = True, schedule: dict | None = None, deterministic: bool = False,

@@ -3,19 +3,10 @@
 // runtime and the kernels (no device pointer is dereferenced).  Built with
 // -fsanitize=undefined, so that the lines between the forms are the library's.
 #include <stdint.h>
-#include <stdio.h>
 #include <string.h>
 
-#include <vector>
-
 #include "../../include/diffus.h"
-
-extern "C" {
-void stub_fail_launch(long n);
-long stub_launches(void);
-int stub_unjoined_captures(void);
-long stub_open_work(void);
-}
+#include "abi_stubs.cpp"
 
 namespace {
 int failures = 0;
@@ -84,6 +75,32 @@ struct Plan {
         return stub_launches() - l0;
     }
 
+    // whether a step launches on two streams, and whether from a graph
+    bool two()
+    {
+        const long a = on_others();
+        expect(step() == DUS_OK, "step");
+        return on_others() > a;
+    }
+
+    bool graph()
+    {
+        g_was_captured = 0;
+        expect(step() == DUS_OK, "step");
+        for (Obj *t : g_streams) g_was_captured += t->was_origin;
+        return g_was_captured > 0;
+    }
+
+    static long on_others()
+    {
+        long n = 0;
+        for (Obj *t : g_streams)
+            if (!t->was_origin) n += t->ops;
+        return n;
+    }
+
+    int g_was_captured = 0;
+
     // every launch of a step failing in turn: reported, nothing left unjoined
     void fail_each()
     {
@@ -115,7 +132,22 @@ int main()
         expect(Plan({{3, 525, 2000}}, flags | DUS_PLAN_ONE_STREAM).launches() == kOne, "one stream");
         expect(Plan({{3, 524, 2000}}, flags | DUS_PLAN_POSE_ONLY).launches() == kPoseOne, "pose only, below");
         expect(Plan({{3, 525, 2000}}, flags | DUS_PLAN_POSE_ONLY).launches() == kPoseTwo, "pose only, above");
+        // many small fans: past one table with dL/dZ, past six with poses alone
+        expect(!Plan({{64, 8, 64}}, flags).two(), "one table");
+        expect(Plan({{65, 8, 64}}, flags).two(), "two tables");
+        expect(!Plan({{65, 8, 64}}, flags | DUS_PLAN_DETERMINISTIC).two(), "two tables, deterministic");
+        expect(!Plan({{65, 8, 64}}, flags | DUS_PLAN_ONE_STREAM).two(), "two tables, one stream");
+        expect(!Plan({{65, 8, 64}, {200, 0, 64}}, flags | DUS_PLAN_POSE_ONLY).two(), "empty fans");
+        expect(!Plan({{384, 8, 64}}, flags | DUS_PLAN_POSE_ONLY).two(), "six tables, pose only");
+        expect(Plan({{385, 8, 64}}, flags | DUS_PLAN_POSE_ONLY).two(), "seven tables, pose only");
+        expect(!Plan({{65, 8, 64}}, flags).graph(), "no graph for small fans");
+        expect(Plan({{3, 525, 2000}}, flags).graph() == (flags == 0), "graph above the line");
+        // equal fans split into two groups of no more tables than they need
+        for (int n : {65, 127, 128, 129, 192, 255, 256, 257})
+            expect(Plan({{n, 8, 64}}, flags).launches() == 5 * (n <= 128 ? 2 : n == 129 ? 3 : n <= 256 ? 4 : 5) + 1,
+                   "tables of", n);
         Plan({{4, 5, 100}}, flags).fail_each();
+        Plan({{130, 5, 100}}, flags).fail_each();
         Plan({{3, 525, 2000}}, flags).fail_each();
     }
     if (failures) {

@@ -21,7 +21,6 @@ def test_plan_chains(tmp_path):
     subprocess.check_call([gxx, "-std=c++17", "-g", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all",
                            "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-o", exe,
                            os.path.join(HERE, "sanitize", "chains_driver.cpp"),
-                           os.path.join(HERE, "sanitize", "abi_stubs.cpp"),
                            os.path.join(ROOT, "paper_2508_06768_amd", "csrc", "abi.cpp")])
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
