@@ -471,10 +471,11 @@ struct dus_plan {
     int64_t extent;
     hipStream_t cap = nullptr;
     // second stream, forked from the step's stream and joined back into it:
-    // the second chain of launches (half the tables), or, when some ray is
-    // long, the launches of the long rays beside the one-wavefront ones
+    // the second chain of launches (half the tables), or the launches of long
+    // rays beside those of the others
     dus::SideStream side{};
     hipEvent_t cleared = nullptr;   // the first table's forward has cleared dL/dZ and the pose sums
+    bool beside = false;            // launches of long rays run beside those of others
     bool two_chains = false;        // the tables alternate between two chains of launches
     bool use_graph = false;         // the step is replayed from a captured graph
     hipGraphExec_t exec = nullptr;
@@ -503,7 +504,7 @@ constexpr int64_t kFoldParts = 4096;
 struct PlanShape {
     int fans = 0;           // that render something
     int64_t work = 0;       // ray-samples
-    bool long_rays = false; // some take several wavefronts by their length
+    bool long_rays = false; // some have at least the schedule's span_samples
 };
 
 PlanShape plan_shape(const dus_plan *p)
@@ -529,9 +530,11 @@ bool many_tables(const dus_plan *p, int fans)
 // Whether a plan's step runs as two chains of launches on two streams, the
 // fans split in two groups of about equal work, so that one chain's kernels
 // fill the other's tails: not for the deterministic plan (one chain), nor
-// for a plan held to one stream, nor when some ray is long enough for
-// several wavefronts (its launches take the second stream), nor for a
-// single fan, nor for small plans of few launches: the second chain's start
+// for a plan held to one stream, nor with long rays (their launches may take
+// the second stream beside those of the others; and where they don't, half of
+// them last as long as all: 3 poses x 256 x 5000 193 / 210 us in two chains, 10 x
+// 100 x 5000 with 8 x 256 x 1000 240 / 261, 12 x 256 x 5000 415 / 413),
+// nor for a single fan, nor for small plans of few launches: the second chain's start
 // and join cost more there than its overlap saves.  Two chains against one,
 // full step in us: 6 poses x 310 x 339 (0.6 M samples) 84 / 52, 55 x 40 x 946
 // (2.1 M) 99 / 93, 12 x 439 x 935 (4.9 M) 149 / 158, 64 x 256 x 1024 (16.8 M)
@@ -541,9 +544,8 @@ bool many_tables(const dus_plan *p, int fans)
 // about 12 us each in one chain (8 with poses alone): 100 poses x 8 x 64 137 /
 // 103, 256 x 16 x 200 291 / 190, 1000 x 8 x 64 1034 / 563; poses alone, 129 x 16
 // x 200 50 / 74, 400 x 16 x 200 118 / 118, 640 x 16 x 200 170 / 138.
-bool plan_two_chains(const dus_plan *p)
+bool plan_two_chains(const dus_plan *p, const PlanShape &s)
 {
-    const PlanShape s = plan_shape(p);
     return !(s.fans < 2 || (s.work < kChainSamples && !many_tables(p, s.fans)) || s.long_rays ||
              (p->flags & (DUS_PLAN_DETERMINISTIC | DUS_PLAN_ONE_STREAM)));
 }
@@ -553,15 +555,30 @@ bool plan_two_chains(const dus_plan *p)
 // batch of 64 fans, one with 64 rays of 16384 samples: 286 us against 359
 // launched directly).  One chain of launches is cheaper without: a graph's
 // own start and end cost about 5 us (3 poses x 106 x 344: 25 / 17 us, 64 x
-// 256 x 1024 on one stream 440 / 436), as much time on the host as its
+// 256 x 1024 on one stream 440 / 436, one fan of 64 x 5000 73 / 69), as much time on the host as its
 // launches take (20 / 13-22 us), and a capture for new buffers; nor is one
 // captured for two chains of small fans, where it saves 10 to 20 us a step and
 // costs some hundreds for new buffers.
-bool plan_uses_graph(const dus_plan *p)
+bool plan_uses_graph(const dus_plan *p, const PlanShape &s)
 {
     if (p->flags & DUS_PLAN_NO_GRAPH) return false;
+    return (p->two_chains && s.work >= kChainSamples) || (p->beside && !(p->flags & DUS_PLAN_ONE_STREAM));
+}
+
+// The plan's streams and tables for its schedule.
+void plan_lay_out(dus_plan *p)
+{
     const PlanShape s = plan_shape(p);
-    return (p->two_chains && s.work >= kChainSamples) || (!(p->flags & DUS_PLAN_ONE_STREAM) && s.long_rays);
+    const int n = (int)p->fans.size();
+    p->tabs = build_tables(p->fans.data(), n);
+    p->beside = false;
+    const int fc = p->sched.fwd_chunk ? p->sched.fwd_chunk : dus::kFewFwdChunk;
+    for (const auto &t : p->tabs)
+        p->beside = p->beside || dus::split_rays(t, fc, dus::kFewFwdChunk, p->sched.span_samples).both() ||
+                    dus::split_rays(t, p->sched.bwd_chunk, dus::kFewBwdChunk, p->sched.span_samples).both();
+    p->two_chains = plan_two_chains(p, s);
+    if (p->two_chains) p->tabs = build_tables(p->fans.data(), n, true);
+    p->use_graph = plan_uses_graph(p, s);
 }
 
 }  // namespace
@@ -896,9 +913,7 @@ int dus_plan_create(dus_plan **out, const dus_volume *vol, const dus_fan *fans, 
     p->fans.assign(fans, fans + n_poses);
     p->phys = *phys;
     p->flags = flags;
-    p->two_chains = plan_two_chains(p);
-    p->use_graph = plan_uses_graph(p);
-    p->tabs = build_tables(fans, n_poses, p->two_chains);
+    plan_lay_out(p);
     p->ws = layout(fans, n_poses, phys, 2, (flags & DUS_PLAN_POSE_ONLY) != 0,
                    (flags & DUS_PLAN_DETERMINISTIC) ? (int64_t)vol->nx * vol->ny * vol->nz : 0);
     p->extent = image_extent(fans, n_poses);
@@ -938,12 +953,7 @@ int dus_plan_set_schedule(dus_plan *p, const dus_schedule *sc)
     if ((s = make_sched(sc, n)) != DUS_OK) return s;
     p->sched = n;
     plan_drop_graph(p);
-    const bool two = plan_two_chains(p);
-    if (two != p->two_chains) {
-        p->two_chains = two;
-        p->tabs = build_tables(p->fans.data(), (int32_t)p->fans.size(), two);
-    }
-    p->use_graph = plan_uses_graph(p);
+    plan_lay_out(p);
     return DUS_OK;
 }
 
@@ -1037,9 +1047,8 @@ static int plan_enqueue_body(dus_plan *p, const float *Z, const float *poses, co
     const bool two = (ev == nullptr) && p->tabs.size() >= 2 && !fix && p->two_chains;
     auto tst = [&](size_t i) { return (two && (i % 2)) ? p->side.st : st; };
     // the long rays' launches take the second stream unless the step keeps
-    // to one stream (one-stream plan, phase-timed step) or it carries the
-    // second chain
-    const dus::SideStream *side = (two || ev || (p->flags & DUS_PLAN_ONE_STREAM)) ? nullptr : &p->side;
+    // to one stream (one-stream plan, phase-timed step)
+    const dus::SideStream *side = (!p->beside || ev || (p->flags & DUS_PLAN_ONE_STREAM)) ? nullptr : &p->side;
     DUS_HIP(mark(DUS_PHASE_CLEAR), "event");
     if (!fwd_clears) DUS_HIP(dus::launch_zero_pair(zero.a, zero.na, zero.b, zero.nb, st), "zero kernel");
     if (two) {

@@ -86,6 +86,69 @@ inline int longest_ray(const FanTable &t)
     return s;
 }
 
+// Rays of the fans at the front of a table whose rays are walked by
+// kSpanWaves wavefronts each (a table lists its fans longest first).  At the
+// default length only up to 512 of them: more fill the chip with one
+// wavefront each (direct adjoint and forward, kSpanWaves / one, us: 512 x 5000
+// 67 + 30 / 80 + 34, 1024 x 5000 132 + 58 / 92 + 36, 3072 x 5000 391 + 187 / 158
+// + 64).
+constexpr int kSpanRays = 512;
+inline int span_rays(const FanTable &t, int span_samples)
+{
+    int n = 0;
+    if (span_samples <= 0) return 0;
+    for (int f = 0; f < t.n && t.f[f].n_samples >= span_samples; ++f) n += t.f[f].n_rays;
+    return (span_samples == kSpanSamples && n > kSpanRays) ? 0 : n;
+}
+
+// Wavefronts per ray (2, 4 or 8: one per tile of the longest ray, as far as
+// they go) where a launch's rays are too few to fill the chip by themselves;
+// 0: the usual split.  A launch of few rays takes as long as its longest ray's
+// chain of tiles, which the wavefronts share: forward (with blur) and
+// pose-only step with one wavefront a ray against several, us:
+//   64 x 300    11.7 ->  11.0    34.3 -> 31.1
+//   256 x 1024  16.2 ->  12.6    42.4 -> 32.9
+//   512 x 1024  17.6 ->  14.8    44.4 -> 36.8
+//   64 x 2048   24.2 ->  13.5    59.8 -> 34.8
+//   512 x 2048  27.5 ->  18.1    65.7 -> 49.4
+//   512 x 3000  39.3 ->  31.6    89.4 -> 72.9
+// The line is where the wavefronts, idle ones included, begin to cost more
+// than the shorter chain saves: 2048 of them, 4096 for rays over 1024
+// samples.  Past it: 1024 x 520 in four wavefronts (4096) 45.8 -> 48.1 and
+// 2048 x 300 in two 49.5 -> 54.5 (pose-only step); 1024 x 1500 in eight
+// (8192) 63.7 -> 75.1, against 64.6 where only its forward takes four.
+// Results are the same but for the order of the pose gradient's and the
+// fused loss's sums, as with the long rays' wavefronts; a schedule that sets
+// another span length than the default keeps to what it says.
+inline int few_ray_waves(const FanTable &t, int tile, int span_samples)
+{
+    if (span_samples != kSpanSamples) return 0;
+    const int s = longest_ray(t);
+    int w = 1;
+    while (w < 8 && w * tile < s) w *= 2;
+    return (w > 1 && (long long)t.total_rays * w <= (s > 1024 ? 4096 : 2048)) ? w : 0;
+}
+
+// How a launch with tiles of 64 * chunk samples walks a table's rays: all of
+// them by `few` wavefronts each (up to chunk `most`, whose registers allow
+// it), or else the first n_span (a table lists its fans longest first) by
+// kSpanWaves each and the n_one others by one.  With both, the n_span may take
+// the side stream; a plan asks the same question to lay out its streams.
+struct RaySplit {
+    int few, n_span, n_one;
+    bool both() const { return n_span > 0 && n_one > 0; }
+};
+
+inline RaySplit split_rays(const FanTable &t, int chunk, int most, int span_samples)
+{
+    RaySplit r;
+    r.few = chunk <= most ? few_ray_waves(t, 64 * chunk, span_samples) : 0;
+    r.n_span = r.few ? 0 : span_rays(t, span_samples);
+    r.n_one = t.total_rays - r.n_span;
+    return r;
+}
+constexpr int kFewFwdChunk = 8, kFewBwdChunk = 4;
+
 struct VolArgs {
     const float *Z;
     int32_t nx, ny, nz, pad_;

@@ -2756,53 +2756,10 @@ inline int grid_for(long long n, int block)
     return (int)g;
 }
 
-// Rays of the fans at the front of a table whose rays are walked by
-// kSpanWaves wavefronts each (a table lists its fans longest first).  At the
-// default length only up to 512 of them: more fill the chip with one
-// wavefront each (direct adjoint and forward, kSpanWaves / one, us: 512 x 5000
-// 67 + 30 / 80 + 34, 1024 x 5000 132 + 58 / 92 + 36, 3072 x 5000 391 + 187 / 158
-// + 64).
-constexpr int kSpanRays = 512;
-inline int span_rays(const FanTable &t, int span_samples)
-{
-    int n = 0;
-    if (span_samples <= 0) return 0;
-    for (int f = 0; f < t.n && t.f[f].n_samples >= span_samples; ++f) n += t.f[f].n_rays;
-    return (span_samples == kSpanSamples && n > kSpanRays) ? 0 : n;
-}
-
 // adjoint blocks for n rays of w wavefronts each, and how many consecutive
 // blocks keep `rays` consecutive rays on one XCD
 inline int ray_blocks(int w, int n) { return w == 1 ? (n + kBlockRays - 1) / kBlockRays : n; }
 inline int block_group(int w, int rays) { return w == 1 ? std::max(rays / kBlockRays, 1) : rays; }
-
-// Wavefronts per ray (2, 4 or 8: one per tile of the longest ray, as far as
-// they go) where a launch's rays are too few to fill the chip by themselves;
-// 0: the usual split.  A launch of few rays takes as long as its longest ray's
-// chain of tiles, which the wavefronts share: forward (with blur) and
-// pose-only step with one wavefront a ray against several, us:
-//   64 x 300    11.7 ->  11.0    34.3 -> 31.1
-//   256 x 1024  16.2 ->  12.6    42.4 -> 32.9
-//   512 x 1024  17.6 ->  14.8    44.4 -> 36.8
-//   64 x 2048   24.2 ->  13.5    59.8 -> 34.8
-//   512 x 2048  27.5 ->  18.1    65.7 -> 49.4
-//   512 x 3000  39.3 ->  31.6    89.4 -> 72.9
-// The line is where the wavefronts, idle ones included, begin to cost more
-// than the shorter chain saves: 2048 of them, 4096 for rays over 1024
-// samples.  Past it: 1024 x 520 in four wavefronts (4096) 45.8 -> 48.1 and
-// 2048 x 300 in two 49.5 -> 54.5 (pose-only step); 1024 x 1500 in eight
-// (8192) 63.7 -> 75.1, against 64.6 where only its forward takes four.
-// Results are the same but for the order of the pose gradient's and the
-// fused loss's sums, as with the long rays' wavefronts; a schedule that sets
-// another span length than the default keeps to what it says.
-inline int few_ray_waves(const FanTable &t, int tile, int span_samples)
-{
-    if (span_samples != kSpanSamples) return 0;
-    const int s = longest_ray(t);
-    int w = 1;
-    while (w < 8 && w * tile < s) w *= 2;
-    return (w > 1 && (long long)t.total_rays * w <= (s > 1024 ? 4096 : 2048)) ? w : 0;
-}
 
 // the side stream starts after what st has queued; st waits for it at the
 // join (graph capture turns both into graph edges)
@@ -2844,12 +2801,12 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
 
 #define DUS_FWD_CASE(CH)                                                                       \
     case CH:                                                                                   \
-        if (few == 2) DUS_FWD_LONG(CH, 2, t.total_rays, zero);                                 \
-        else if (few == 4) DUS_FWD_LONG(CH, 4, t.total_rays, zero);                            \
-        else if (few == 8) DUS_FWD_LONG(CH, 8, t.total_rays, zero);                            \
-        if (few) break;                                                                        \
-        if (n_span > 0) DUS_FWD_LONG(CH, kSpanWaves, n_span, ZeroArgs{});                      \
-        if (n_one > 0 || zero.na > 0 || zero.nb > 0) {                                         \
+        if (r.few == 2) DUS_FWD_LONG(CH, 2, t.total_rays, zero);                               \
+        else if (r.few == 4) DUS_FWD_LONG(CH, 4, t.total_rays, zero);                          \
+        else if (r.few == 8) DUS_FWD_LONG(CH, 8, t.total_rays, zero);                          \
+        if (r.few) break;                                                                      \
+        if (r.n_span > 0) DUS_FWD_LONG(CH, kSpanWaves, r.n_span, r.n_one > 0 ? ZeroArgs{} : zero); \
+        if (r.n_one > 0) {                                                                     \
             if (p.speckle) DUS_FWD_LAUNCH(CH, true, 1, t.total_rays, t1, zero, st);            \
             else DUS_FWD_LAUNCH(CH, false, 1, t.total_rays, t1, zero, st);                     \
         }                                                                                      \
@@ -2888,17 +2845,12 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
     if (t.total_rays <= 0) return hipSuccess;
     if (chunk == 0) chunk = auto_fwd_chunk(t, span_samples, zcar != nullptr);
     if (chunk != 4 && chunk != 8 && chunk != 16) return hipErrorInvalidValue;
-    // the rays of the table's long fans (its first ones: a table lists its
-    // fans longest first) get kSpanWaves wavefronts each, the rest one; all
-    // rays several where they are few
-    const int few = (chunk < 16) ? few_ray_waves(t, 64 * chunk, span_samples) : 0;
-    const int n_span = few ? 0 : span_rays(t, span_samples);
-    const int n_one = t.total_rays - n_span;
-    // the clears go with the one-wavefront launch (it covers every ray)
+    const RaySplit r = split_rays(t, chunk, kFewFwdChunk, span_samples);
+    // the clears go with the one-wavefront launch where there is one
     FanTable t1 = t;
-    t1.ray0 = n_span;
+    t1.ray0 = r.n_span;
     hipStream_t sst = st;
-    if (n_span > 0 && side) {
+    if (r.both() && side) {
         hipError_t e = fork_side(st, *side);
         if (e != hipSuccess) return e;
         sst = side->st;
@@ -2930,13 +2882,13 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
 // kSpanWaves * 4 / C wavefronts each (the registers of C = 8 allow half as many)
 #define DUS_BWD_CASE(CH)                                                                       \
     case CH:                                                                                   \
-        if (n_span > 0) {                                                                      \
-            if (fused) DUS_BWD_LAUNCH(CH, false, true, kSpanWaves * 4 / CH, kRecords, n_span, t, sst);  \
-            else if (spk) DUS_BWD_LAUNCH(CH, true, false, kSpanWaves * 4 / CH, kRows, n_span, t, sst); \
-            else if (!zcar) DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, kRows, n_span, t, sst); \
-            else DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, kRecords, n_span, t, sst);       \
+        if (r.n_span > 0) {                                                                      \
+            if (fused) DUS_BWD_LAUNCH(CH, false, true, kSpanWaves * 4 / CH, kRecords, r.n_span, t, sst);  \
+            else if (spk) DUS_BWD_LAUNCH(CH, true, false, kSpanWaves * 4 / CH, kRows, r.n_span, t, sst); \
+            else if (!zcar) DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, kRows, r.n_span, t, sst); \
+            else DUS_BWD_LAUNCH(CH, false, false, kSpanWaves * 4 / CH, kRecords, r.n_span, t, sst);       \
         }                                                                                      \
-        if (n_one > 0) {                                                                       \
+        if (r.n_one > 0) {                                                                       \
             if (fused && in_reach(v)) DUS_BWD_LAUNCH_(CH, false, true, 1, kRecords, true, t.total_rays, t1, st); \
             else if (fused) DUS_BWD_LAUNCH(CH, false, true, 1, kRecords, t.total_rays, t1, st);         \
             else if (spk) DUS_BWD_LAUNCH(CH, true, false, 1, kRows, t.total_rays, t1, st);            \
@@ -3002,20 +2954,18 @@ hipError_t launch_adjoint(int chunk, int xcd_group, const VolArgs &v, const Phys
     // the fused step records its gains and the rays' geometry
     if ((fused && (spk || !zcar)) || (spk && zcar) || (zcar && !t.geom)) return hipErrorInvalidValue;
     // several wavefronts per long ray, or for every ray where they are few
-    const int few = (chunk == 4 && zcar) ? few_ray_waves(t, 256, span_samples) : 0;
-    if (few) {
-        switch (few) {
+    const RaySplit r = split_rays(t, zcar ? chunk : kFewBwdChunk + 1, kFewBwdChunk, span_samples);
+    if (r.few) {
+        switch (r.few) {
             DUS_FEW_CASE(2)
             DUS_FEW_CASE(4)
             DUS_FEW_CASE(8)
         }
         return hipGetLastError();
     }
-    const int n_span = span_rays(t, span_samples);
-    const int n_one = t.total_rays - n_span;
-    t1.ray0 = n_span;
+    t1.ray0 = r.n_span;
     hipStream_t sst = st;
-    if (n_span > 0 && side) {
+    if (r.both() && side) {
         hipError_t e = fork_side(st, *side);
         if (e != hipSuccess) return e;
         sst = side->st;

@@ -85,10 +85,11 @@ struct Plan {
 
     bool graph()
     {
-        g_was_captured = 0;
+        for (Obj *t : g_streams) t->was_origin = false;
         expect(step() == DUS_OK, "step");
-        for (Obj *t : g_streams) g_was_captured += t->was_origin;
-        return g_was_captured > 0;
+        bool captured = false;
+        for (Obj *t : g_streams) captured = captured || t->was_origin;
+        return captured;
     }
 
     static long on_others()
@@ -98,8 +99,6 @@ struct Plan {
             if (!t->was_origin) n += t->ops;
         return n;
     }
-
-    int g_was_captured = 0;
 
     // every launch of a step failing in turn: reported, nothing left unjoined
     void fail_each()
@@ -142,6 +141,23 @@ int main()
         expect(Plan({{385, 8, 64}}, flags | DUS_PLAN_POSE_ONLY).two(), "seven tables, pose only");
         expect(!Plan({{65, 8, 64}}, flags).graph(), "no graph for small fans");
         expect(Plan({{3, 525, 2000}}, flags).graph() == (flags == 0), "graph above the line");
+        // long rays: beside others on the second stream (from a graph), unless
+        // they are few or many, or no others are there
+        const std::vector<std::vector<int>> beside = {{2, 100, 5000}, {8, 256, 1000}};
+        expect(Plan(beside, flags).launches() == kOne && Plan(beside, flags).graph() == (flags == 0), "long beside short");
+        expect(!Plan(beside, flags | DUS_PLAN_ONE_STREAM).graph(), "long beside short, one stream");
+        for (std::vector<int> k : {std::vector<int>{1, 64, 5000}, {12, 256, 5000}, {2, 256, 8000}, {1, 512, 9000}}) {
+            Plan p({k}, flags);
+            expect(p.launches() == kOne && !p.two() && !p.graph(), "long rays alone", k[0] * k[1]);
+            // without spans they are rays like others
+            dus_schedule sc = {0, 0, 0, 0, -1};
+            expect(dus_plan_set_schedule(p.p, &sc) == DUS_OK, "schedule");
+            expect(p.launches() == (k[0] > 1 ? kTwo : kOne), "long rays, no spans", k[0] * k[1]);
+            // tiles and chunks that few rays cannot share, and an explicit length
+            sc = {16, 8, 0, 0, 4000};
+            expect(dus_plan_set_schedule(p.p, &sc) == DUS_OK, "schedule");
+            expect(p.launches() == kOne && !p.graph(), "long rays alone, explicit", k[0] * k[1]);
+        }
         // equal fans split into two groups of no more tables than they need
         for (int n : {65, 127, 128, 129, 192, 255, 256, 257})
             expect(Plan({{n, 8, 64}}, flags).launches() == 5 * (n <= 128 ? 2 : n == 129 ? 3 : n <= 256 ? 4 : 5) + 1,

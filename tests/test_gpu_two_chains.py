@@ -77,3 +77,22 @@ def test_two_chains_agree(which, effects):
         step.close()
         ref = ref or runs[0]
         _agree(runs, ref)
+
+
+def test_schedule_changes_the_chains():
+    """One plan through every form: few long rays on one chain; without spans
+    two chains from a graph; with every ray in several wavefronts (whose
+    launch then clears dL/dZ) one chain again.  Against a one-stream plan."""
+    from paper_2508_06768_amd.render import FusedStep
+    print("schedule changes", flush=True)
+    geom, Z, poses = _plan(2, 250, 6500, True, seed=63)
+    assert geom.total >= 3 << 20
+    for image in (True, False):
+        one = FusedStep(geom, one_stream=True, schedule={"fwd_chunk": 4})
+        ref = _steps(one, geom, Z, poses, image, 1)[0]
+        one.close()
+        step = FusedStep(geom)
+        for span in (0, -1, 1, -1, 0):
+            step.set_schedule(fwd_chunk=4, span_samples=span)
+            _agree(_steps(step, geom, Z, poses, image, 2), ref)
+        step.close()
