@@ -1691,8 +1691,8 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
         // the segment's last group loads nothing ahead (the next segment
         // belongs to another wavefront)
         if (k0 + G < k_end) load(kl + G, zn);
-        if (__ballot(zb[0] != 0.0f || zb[1] != 0.0f || zb[2] != 0.0f || zb[3] != 0.0f) == 0ull)
-            continue;                            // nothing to scatter in this group (uniform)
+        const bool some = zb[0] != 0.0f || zb[1] != 0.0f || zb[2] != 0.0f || zb[3] != 0.0f;
+        if (__ballot(some) == 0ull) continue;    // nothing to scatter in this group (uniform)
         // Cells and weights of the lane's depths, from their FP64 positions;
         // without the clamps where every lane's first and last depth, and so
         // (the position is affine) all between, lie inside the volume.  Lanes
@@ -1719,14 +1719,24 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
         // that are worth a box; past that its samples share too few for one.
         // (Not where samples lie outside the volume: those are many to a voxel
         // at its faces, and are summed in FP64 ray by ray.)
+        // Rays at steps of 0.35 and 0.7 voxels and more down to two and four at a
+        // time: a box of its own for a single ray's 16 or 8 depths costs more than
+        // their atomics (9 voxels apart: 1 pose x 8 x 103 55 / 26 us).
         // (full step's scatter by rays / by depths, us: 12 poses x 40 x 147 at
         // 1.2 voxels 41 / 28, 18 x 257 x 95 at 1.8 34 / 25, 12 x 287 x 73 at 2.3
         // 74 / 25; 25 x 82 x 178 at 1.16 37 / 41).
         const bool deep = coarse && inside;
-        const int key = deep ? ch : slot, all = deep ? LPR : RB, least = deep ? min(4, LPR) : 1;
+        const int key = deep ? ch : slot, all = deep ? LPR : RB;
+        const int least = deep ? min(4, LPR) : (inside ? 4 / spl : 1);
         int part = all;
         for (int s0 = 0; s0 < all;) {
-            const bool mine = (unsigned)(key - s0) < (unsigned)part;
+            // (lanes with zeros alone take no part: those past a fan of few rays
+            // lie on its last ray, and their atomics would queue behind its own)
+            const bool mine = some && (unsigned)(key - s0) < (unsigned)part;
+            if (__ballot(mine) == 0ull) {
+                s0 += part;
+                continue;
+            }
             // (opaque, or the weights' products would be held across the loop)
 #pragma unroll
             for (int q = 0; q < kScatterSpl; ++q)
@@ -3015,6 +3025,32 @@ static bool dense_fans(const VolArgs &v, const FanTable &t)
     return 2 * dense > all;
 }
 
+// Whether most of a table's samples lie in fans of few rays, or of rays more
+// than two voxels apart at mid-depth
+static bool sparse_fans(const VolArgs &v, const FanTable &t)
+{
+    const float h = std::min(v.h[0], std::min(v.h[1], v.h[2]));
+    long long all = 0, sparse = 0;
+    for (int f = 0; f < t.n; ++f) {
+        const FanRec &r = t.f[f];
+        const long long n = (long long)r.n_rays * r.n_samples;
+        const float mid = r.r0 + 0.5f * r.ds * (float)r.n_samples;
+        all += n;
+        if (r.n_rays < 8 || r.aperture * mid > 2.0f * h * (float)r.n_rays) sparse += n;
+    }
+    return 2 * sparse > all;
+}
+
+// the most depths that a lane takes in any fan (k_scatter's rule, by the step
+// along the widest spacing)
+static int depths_per_lane(const VolArgs &v, const FanTable &t)
+{
+    const float h = std::max(v.h[0], std::max(v.h[1], v.h[2]));
+    float ds = t.f[0].ds;
+    for (int f = 1; f < t.n; ++f) ds = std::min(ds, t.f[f].ds);
+    return ds <= 0.35f * h ? 4 : (ds <= 0.7f * h ? 2 : 1);
+}
+
 // whether some ray is longer than the volume's diagonal
 static bool runs_outside(const VolArgs &v, const FanTable &t)
 {
@@ -3032,7 +3068,9 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
     if (t.total_rays <= 0 || (!gZ && !fix)) return hipSuccess;
     if (!zbar || !rays || (fix && !fscale)) return hipErrorInvalidValue;
     // depth segments, the same power-of-two length for every fan, a whole
-    // number of the largest groups (256 / RB depths): the shortest that
+    // number of the largest groups (256 / RB depths, or in a small launch
+    // those of its shortest steps, so that no wavefront walks several groups
+    // while others are missing: 140 sparse fans 1.36 times as fast): the shortest that
     // keeps the launch within wave_target wavefronts, about 32 per SIMD over
     // the launches that run at the same time (a wavefront's set-up is a few
     // loads, so short segments cost little and even out the finishing times;
@@ -3053,11 +3091,18 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
     // box of two rays and four times the depths is longer than LDS holds, and
     // the cells where the rays meet take four times the global atomics (two
     // rays / eight, us: 2 poses x 46 x 224 24 / 16, 9 x 93 x 142 50 / 23, 23 x 77
-    // x 142 72 / 12, 6 x 488 x 90 150 / 27)
+    // x 142 72 / 12, 6 x 488 x 90 150 / 27); or four where those wavefronts' rays
+    // are few or far apart and would be taken in quarters and singly (direct
+    // adjoint, two rays / eight / four, us: 1 pose x 8 x 150 9 voxels apart 33 / 44
+    // / 24, 4 x 13 x 105 at 7 36 / 46 / 29, 2 x 14 x 161 at 7 35 / 45 / 34; over
+    // 140 fans of 2 to 64 rays four are 11% faster than eight in the mean).
+    // Over 310 small launches dL/dZ is 0.90 (few rays 0.98, rays running on
+    // outside 0.95) times as far from 64 bits, rel. l2, as with two throughout.
+    const bool few = units(8, 32) < 2048;
     if (scatter_rays == 0)
-        scatter_rays = (units(8, 32) < 2048 && runs_outside(v, t)) ? 2 : (dense_fans(v, t) ? 16 : 8);
+        scatter_rays = (few && runs_outside(v, t)) ? 2 : (dense_fans(v, t) ? 16 : (few && sparse_fans(v, t) ? 4 : 8));
     else if (scatter_rays == 16) return hipErrorInvalidValue;
-    int seg = 256 / scatter_rays, seg_shift = 0;
+    int seg = 64 * (few ? depths_per_lane(v, t) : kScatterSpl) / scatter_rays, seg_shift = 0;
     while (seg < DUS_MAX_SAMPLES && units(scatter_rays, seg) > std::max(wave_target, 1024)) seg *= 2;
     while ((1 << seg_shift) < seg) ++seg_shift;
     const long long nunits = units(scatter_rays, seg);
