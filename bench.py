@@ -82,6 +82,13 @@ def profile_field(path, name):
         return None
 
 
+def profiled_schedule(kernel, schedule):
+    """Whether a step under this schedule runs the instance of the kernel that
+    the counter summaries were taken with (the default schedule's)."""
+    return {"forward": schedule["fwd_chunk"] in (0, 8), "adjoint": schedule["bwd_chunk"] == 4,
+            "scatter": schedule["scatter_rays"] == 0}[kernel]
+
+
 def measured_traffic():
     """HBM bytes per adjoint launch (FETCH_SIZE + WRITE_SIZE, calibrated)."""
     return profile_field(TRAFFIC_FILE, "traffic_bytes_per_launch")
@@ -420,7 +427,8 @@ def main():
     # the committed instruction counters (lane-operations = SQ_INSTS_VALU x
     # 64 per launch), which decide the bound while they match the source
     hbm_frac = kern[dom]["GBs"] / HBM_PEAK_GBS
-    lane_ops = profile_field(VALU_FILE, f"valu_lane_ops_per_launch_{dom}")
+    profiled = profiled_schedule(dom, step.get_schedule())
+    lane_ops = profile_field(VALU_FILE, f"valu_lane_ops_per_launch_{dom}") if profiled else None
     alu = None
     if lane_ops is not None:
         ach = lane_ops / (kern[dom]["ms"] * 1e-3)
@@ -471,7 +479,7 @@ def main():
             "unit": "GB/s",
             "frac": hbm_frac,
             "frac_of": "hbm",
-            "traffic": measured_traffic() if dom == "adjoint" else None,
+            "traffic": measured_traffic() if dom == "adjoint" and profiled else None,
             "alg_bytes": kern[dom]["alg_bytes"],
             "ms": kern[dom]["ms"],
             "alu": alu,

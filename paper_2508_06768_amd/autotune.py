@@ -9,7 +9,8 @@ length from which several wavefronts share a ray (``span_samples``: never,
 or 1024..8192 samples, tried only up to the plan's longest ray).
 ``autotune`` times the candidates on the caller's actual plan and inputs
 with HIP events (coordinate descent in that order, each candidate over
-``reps`` steps), installs the fastest on the plan and remembers it in a JSON
+``reps`` steps; one that is faster only within the timings' noise is not
+taken), installs the fastest on the plan and remembers it in a JSON
 cache keyed by GPU architecture and a shape class of the workload.
 
 Cache file: ``$DUS_AUTOTUNE_CACHE`` or ``~/.cache/diffus_autotune.json``.
@@ -26,6 +27,10 @@ BWD_CHUNKS = (4, 8)
 XCD_GROUPS = (1, 4, 8, 16, 32, 64)
 SCATTER_RAYS = (2, 4, 8)
 SPAN_SAMPLES = (-1, 1024, 2048, 4096, 8192)
+# a candidate replaces the best so far when it is faster by more than this:
+# two timings of one schedule differ by up to 0.6% (the same step at 0.4280 and
+# 0.4307 ms)
+MARGIN = 0.01
 
 
 def _cache_path() -> str:
@@ -100,7 +105,7 @@ def autotune(step, run, reps: int = 10, use_cache: bool = True, verbose: bool = 
             print("autotune", cand, f"{ms:.3f} ms", flush=True)
         return ms
 
-    best_ms = trial(best)
+    best_ms = min(trial(best), trial(best))      # (the first one also warms up)
     longest = max((int(f.n_samples) for f in step.geom.fans), default=0)
     spans = tuple(v for v in SPAN_SAMPLES if v <= longest)
     for field, values in (("fwd_chunk", FWD_CHUNKS), ("bwd_chunk", BWD_CHUNKS), ("scatter_rays", SCATTER_RAYS),
@@ -110,7 +115,7 @@ def autotune(step, run, reps: int = 10, use_cache: bool = True, verbose: bool = 
                 continue
             cand = dict(best, **{field: val})
             ms = trial(cand)
-            if ms < best_ms:
+            if ms < (1.0 - MARGIN) * best_ms:
                 best, best_ms = cand, ms
     step.set_schedule(**best)
     out = {"schedule": best, "ms": best_ms, "trials": trials}
