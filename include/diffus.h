@@ -330,14 +330,16 @@ typedef struct {
     int32_t bwd_chunk;        /* same for the adjoint: 4 or 8 */
     int32_t xcd_group;        /* consecutive rays kept on one XCD: 1..64 */
     int32_t scatter_rays;     /* neighbouring rays per wavefront (one LDS box) in the dL/dZ scatter:
-                                 2, 4 or 8; 0 (the default) picks 8, 16 for dense fans, or 2 for few
-                                 rays that run on outside the volume */
+                                 2, 4 or 8; 0 (the default) picks 8, 16 for dense fans (automatic
+                                 only), 4 for few rays of sparse fans, or 2 for few rays that run
+                                 on outside the volume */
     int32_t span_samples;     /* rays of at least this many samples are walked by several
                                  wavefronts each, which take consecutive tiles of the ray together
                                  (forward; the plan's adjoint): 1..DUS_MAX_SAMPLES, 0 (the default)
                                  for 4096 (where a launch has few rays, for shorter ones too, and
-                                 where it has many long ones, for none),
-                                 -1 for never.  Results do not depend on it, except for
+                                 where it has many long ones, for none; dus_get_schedule reports
+                                 it as 4096, and 4096 asks for it: 4095 or 4097 for a line there
+                                 without exceptions), -1 for never.  Results do not depend on it, except for
                                  the rounding of the pose gradient and of the fused loss */
 } dus_schedule;
 
@@ -393,12 +395,15 @@ int dus_plan_step(dus_plan *plan, const float *Z, const float *poses, const floa
 
 /*
  * Phases of a plan step, in launch order (measurement and tracing):
- *   CLEAR      fill kernel for the pose accumulators and grad_Z, when the
- *              forward kernel does not run (else its wavefronts clear them)
- *   FORWARD    forward kernel (pixels, tile carries, per-pixel gains)
+ *   CLEAR      fill kernel for the pose accumulators and grad_Z, when no
+ *              forward kernel runs (else its wavefronts clear them)
+ *   FORWARD    forward kernel (pixels, states for the adjoint, per-pixel gains)
  *   BLUR_LOSS  blur, MSE residual and loss partials, blur transpose (blur on)
- *   ADJOINT    adjoint scan kernel (dL/dZ per sample, pose sums; with blur
- *              off it also forms the loss partials)
+ *   ADJOINT    adjoint kernel (dL/dZ per sample, pose sums; with blur off it
+ *              also forms the loss partials).  Where no image is wanted (bmode
+ *              NULL, blur off) and the rays are many or long, a forward kernel
+ *              that only records states, and makes the clears, runs before it
+ *              and counts here
  *   SCATTER    trilinear scatter of dL/dZ into grad_Z
  *   FINISH     loss reduction and pose-gradient kernel
  */

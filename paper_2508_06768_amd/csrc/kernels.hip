@@ -124,10 +124,6 @@ __device__ __forceinline__ double quot64(double a, double b, double ib)
 #define GATHER_UNROLL 4
 #endif
 
-// LDS index padding: doubles (one pad word per 16) and floats (per 32)
-__device__ __forceinline__ int pad8(int i) { return i + (i >> 4); }
-__device__ __forceinline__ int pad4(int i) { return i + (i >> 5); }
-
 // blocks are handed to the 8 XCDs round-robin; keep runs of `grp`
 // consecutive rays (neighbours in the fan, sharing voxels) on one XCD's L2
 __device__ __forceinline__ int remap_block(int b, int G, int grp)
@@ -2809,18 +2805,20 @@ inline hipError_t join_side(hipStream_t st, const SideStream &s)
         else DUS_FWD_LAUNCH(CH, false, WV, NG, t, ZERO, sst);                                   \
     } while (0)
 
-#define DUS_FWD_CASE(CH)                                                                       \
-    case CH:                                                                                   \
-        if (r.few == 2) DUS_FWD_LONG(CH, 2, t.total_rays, zero);                               \
-        else if (r.few == 4) DUS_FWD_LONG(CH, 4, t.total_rays, zero);                          \
-        else if (r.few == 8) DUS_FWD_LONG(CH, 8, t.total_rays, zero);                          \
-        if (r.few) break;                                                                      \
-        if (r.n_span > 0) DUS_FWD_LONG(CH, kSpanWaves, r.n_span, r.n_one > 0 ? ZeroArgs{} : zero); \
-        if (r.n_one > 0) {                                                                     \
-            if (p.speckle) DUS_FWD_LAUNCH(CH, true, 1, t.total_rays, t1, zero, st);            \
-            else DUS_FWD_LAUNCH(CH, false, 1, t.total_rays, t1, zero, st);                     \
-        }                                                                                      \
-        break;
+// few rays (chunk 4 and 8: split_rays gives none past kFewFwdChunk)
+#define DUS_FWD_FEW(CH)                                                                        \
+    if (r.few == 2) DUS_FWD_LONG(CH, 2, t.total_rays, zero);                                   \
+    else if (r.few == 4) DUS_FWD_LONG(CH, 4, t.total_rays, zero);                              \
+    else if (r.few == 8) DUS_FWD_LONG(CH, 8, t.total_rays, zero);                              \
+    if (r.few) break;
+
+#define DUS_FWD_SPLIT(CH)                                                                      \
+    if (r.n_span > 0) DUS_FWD_LONG(CH, kSpanWaves, r.n_span, r.n_one > 0 ? ZeroArgs{} : zero); \
+    if (r.n_one > 0) {                                                                         \
+        if (p.speckle) DUS_FWD_LAUNCH(CH, true, 1, t.total_rays, t1, zero, st);                \
+        else DUS_FWD_LAUNCH(CH, false, 1, t.total_rays, t1, zero, st);                         \
+    }                                                                                          \
+    break;
 
 // automatic forward tile (chunk 0): 8 x 64 samples, unless the table's rays
 // fill 512-sample tiles clearly worse than 256-sample ones.  On full tiles
@@ -2866,9 +2864,14 @@ hipError_t launch_forward(int chunk, int xcd_group, const VolArgs &v, const Phys
         sst = side->st;
     }
     switch (chunk) {
-        DUS_FWD_CASE(4)
-        DUS_FWD_CASE(8)
-        DUS_FWD_CASE(16)
+    case 4:
+        DUS_FWD_FEW(4)
+        DUS_FWD_SPLIT(4)
+    case 8:
+        DUS_FWD_FEW(8)
+        DUS_FWD_SPLIT(8)
+    case 16:
+        DUS_FWD_SPLIT(16)
     default:
         return hipErrorInvalidValue;
     }
