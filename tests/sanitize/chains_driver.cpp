@@ -146,6 +146,9 @@ int main()
         const std::vector<std::vector<int>> beside = {{2, 100, 5000}, {8, 256, 1000}};
         expect(Plan(beside, flags).launches() == kOne && Plan(beside, flags).graph() == (flags == 0), "long beside short");
         expect(!Plan(beside, flags | DUS_PLAN_ONE_STREAM).graph(), "long beside short, one stream");
+        expect(Plan({{1, 20, 5000}, {3, 200, 300}}, flags).graph() == (flags == 0), "few long beside many short");
+        expect(Plan(beside, flags | DUS_PLAN_DETERMINISTIC).graph() == (flags == 0), "long beside short, deterministic");
+        expect(!Plan({{3, 525, 2000}}, flags | DUS_PLAN_DETERMINISTIC).graph(), "deterministic");
         for (std::vector<int> k : {std::vector<int>{1, 64, 5000}, {12, 256, 5000}, {2, 256, 8000}, {1, 512, 9000}}) {
             Plan p({k}, flags);
             expect(p.launches() == kOne && !p.two() && !p.graph(), "long rays alone", k[0] * k[1]);

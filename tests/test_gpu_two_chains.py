@@ -1,11 +1,13 @@
-"""Two chains of launches against the same plan held to one stream: the same
+"""Plans on two streams against the same plan held to one: the same
 image bit for bit, the loss and the gradients within the rounding of sums in
 another order, step after step into outputs filled with NaN.
 
 * many small fans (more than one fan table, launched directly);
-* large plans from a graph: more than 64 fans, and no image asked for (the
+* large plans, from a graph and launched directly: more than 64 fans, and no image asked for (the
   forward that only records states then clears dL/dZ, and the second chain
-  waits for it), with blur and without.
+  waits for it), with blur and without;
+* long rays beside others, from a graph and launched directly, with FP32
+  atomics and in the deterministic plan.
 """
 import numpy as np
 import pytest
@@ -71,8 +73,8 @@ def test_two_chains_agree(which, effects):
     geom, Z, poses = _plan(n, rays, samples, effects)
     assert (geom.total >= 3 << 20) == which.startswith("large")
     ref = None
-    for one in (True, False):
-        step = FusedStep(geom, one_stream=one)
+    for options in ({"one_stream": True}, {}, {"graph": False}):
+        step = FusedStep(geom, **options)
         runs = _steps(step, geom, Z, poses, image)
         step.close()
         ref = ref or runs[0]
@@ -96,3 +98,24 @@ def test_schedule_changes_the_chains():
             step.set_schedule(fwd_chunk=4, span_samples=span)
             _agree(_steps(step, geom, Z, poses, image, 2), ref)
         step.close()
+
+
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("image", [False, True])
+def test_long_rays_beside_others(image, deterministic):
+    """20 rays of 5000 samples take eight wavefronts each beside 600 of 300."""
+    from paper_2508_06768_amd.render import FusedStep, Geometry
+    print("long rays beside others", image, deterministic, flush=True)
+    small, Z, poses = _plan(4, 200, 300, True, seed=65)
+    fans = [synth.FanSpec(20, 5000, 0.5, 0.009, 0.5, 0)] + list(small.fans[1:])
+    geom = Geometry(tuple(Z.shape), (1.0, 1.0, 1.0), (0.0, 0.0, 0.0), fans, small.phys)
+    runs = {}
+    for name, options in (("one", {"one_stream": True}), ("graph", {}), ("direct", {"graph": False})):
+        step = FusedStep(geom, deterministic=deterministic, **options)
+        runs[name] = _steps(step, geom, Z, poses, image)
+        step.close()
+    for r in runs.values():
+        _agree(r, runs["one"][0])
+        if deterministic:
+            for x in r:
+                np.testing.assert_array_equal(x[2], runs["one"][0][2])
