@@ -1588,7 +1588,8 @@ __device__ __forceinline__ int wave_min_int(int x)
 template <int RB>
 __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const RayRec *__restrict__ rays,
                                                 const float *__restrict__ zbar, float *__restrict__ gZ,
-                                                int seg_shift, int xgrp, unsigned long long *__restrict__ fix,
+                                                int seg_shift, int few, int xgrp,
+                                                unsigned long long *__restrict__ fix,
                                                 const double *__restrict__ fscale)
 {
     constexpr int LPR = 64 / RB;                 // lanes per ray
@@ -1715,15 +1716,17 @@ __global__ __launch_bounds__(64) void k_scatter(VolArgs v, FanTable tab, const R
         // that are worth a box; past that its samples share too few for one.
         // (Not where samples lie outside the volume: those are many to a voxel
         // at its faces, and are summed in FP64 ray by ray.)
-        // Rays at steps of 0.35 and 0.7 voxels and more down to two and four at a
-        // time: a box of its own for a single ray's 16 or 8 depths costs more than
-        // their atomics (9 voxels apart: 1 pose x 8 x 103 55 / 26 us).
+        // In small launches (few) rays at steps of 0.35 and 0.7 voxels and more
+        // down to two and four at a time: boxes for single rays' 16 or 8 depths,
+        // one after the other, take longer than their atomics (9 voxels apart: 1
+        // pose x 8 x 103 55 / 26 us); where many wavefronts' atomics meet near the
+        // probes they don't (64 poses x 85 x 267 120 / 179).
         // (full step's scatter by rays / by depths, us: 12 poses x 40 x 147 at
         // 1.2 voxels 41 / 28, 18 x 257 x 95 at 1.8 34 / 25, 12 x 287 x 73 at 2.3
         // 74 / 25; 25 x 82 x 178 at 1.16 37 / 41).
         const bool deep = coarse && inside;
         const int key = deep ? ch : slot, all = deep ? LPR : RB;
-        const int least = deep ? min(4, LPR) : (inside ? 4 / spl : 1);
+        const int least = deep ? min(4, LPR) : (few && inside ? 4 / spl : 1);
         int part = all;
         for (int s0 = 0; s0 < all;) {
             // (lanes with zeros alone take no part: those past a fan of few rays
@@ -3135,19 +3138,19 @@ hipError_t launch_scatter(int scatter_rays, int xcd_group, const VolArgs &v, con
     }
     switch (scatter_rays) {
     case 2:
-        hipLaunchKernelGGL((k_scatter<2>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, xcd_group,
+        hipLaunchKernelGGL((k_scatter<2>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, few, xcd_group,
                            fix, fscale);
         break;
     case 4:
-        hipLaunchKernelGGL((k_scatter<4>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, xcd_group,
+        hipLaunchKernelGGL((k_scatter<4>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, few, xcd_group,
                            fix, fscale);
         break;
     case 8:
-        hipLaunchKernelGGL((k_scatter<8>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, xcd_group,
+        hipLaunchKernelGGL((k_scatter<8>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, few, xcd_group,
                            fix, fscale);
         break;
     case 16:
-        hipLaunchKernelGGL((k_scatter<16>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, xcd_group,
+        hipLaunchKernelGGL((k_scatter<16>), grid, dim3(64), 0, st, v, ts, rays, zbar, gZ, seg_shift, few, xcd_group,
                            fix, fscale);
         break;
     default:
