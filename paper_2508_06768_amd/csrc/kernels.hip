@@ -1048,11 +1048,12 @@ __global__ __launch_bounds__(64 * W) void k_forward(VolArgs v, PhysArgs p, FanTa
 // Lane l takes the chunk 63 - l of the tile's interfaces, so that the sums
 // run over the lanes below.
 //
-// Bound by memory latency and VALU issue (0.62 busy at 4 wavefronts per SIMD,
+// Bound by memory latency and VALU issue (0.66 busy at 3.1 wavefronts per SIMD,
 // 128 VGPRs).  64 poses x 256 rays x 1024 samples with the forward's records,
 // one launch: 239 us with the (v0, v1, D) adjoint, 151 us with the sums, 132
 // us with the rays' geometry handed over, 32-bit gather offsets, loads ahead
-// of the gather and no barrier that drains them.
+// of the gather and no barrier that drains them, 134 us with the quotients
+// taken to the last place.
 //
 // Where the state (w, t) at a chunk's start comes from (FROM):
 //   kRecords: the records of the fused step's forward (states, zcar, geom).
